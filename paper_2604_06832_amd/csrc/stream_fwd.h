@@ -1125,29 +1125,44 @@ __device__ inline bool stream_attention_local(const MegaArgs& a, FwdCtx& fc, Fwd
     const int kvh = ct / n_ct, ctk = ct - kvh * n_ct;
     const int cidx = ctk * 16 + col;
     const int hq = cidx / Mp, row = cidx - hq * Mp;
-    // partial of chunk ch of this tile: the workgroup with w = ch * CT + ctl of this XCD
-    float mx = kNegBig;
-    for (int ch = 0; ch < lp.NCH; ++ch) mx = fmaxf(mx, pm[(size_t)((ch * lp.CT + ctl) * a.n_xcd + x) * 16 + col]);
+    // partial of chunk ch of this tile: the workgroup with w = ch * CT + ctl of this XCD.  Eight chunks per batch, and
+    // two batches requested before the first is used (up to 16 chunks, all that a forward of at most 16 rows has, cost
+    // one round trip to the L2); a running maximum carries from batch to batch, chunks in order.  What bounds the merge
+    // is that latency: with a loop over the maxima ahead of the loads (one round trip per chunk) the phase took 12.0 us
+    // per layer at 1 row and 10.5 at 32 rows (1024 keys), a forward 2270 and 2512 us; in this form 2116 and 2422 us.
+    float mx = kNegBig, lsum = 0.f;
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-    float lsum = 0.f;
-    for (int ch0 = 0; ch0 < lp.NCH; ch0 += 8) {
-      f32x4 pv[8];
-      float pmv[8], plv[8];
+    struct Batch { f32x4 o[8]; float m[8], l[8]; };
+    auto fetch = [&](Batch& b, int ch0) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int chc = min(ch0 + u, lp.NCH - 1);
-        const size_t it = (size_t)((chc * lp.CT + ctl) * a.n_xcd + x);
-        pv[u] = *reinterpret_cast<const f32x4*>(pO + (it * DT + dt) * 64 * 4 + (size_t)lane * 4);
-        pmv[u] = pm[it * 16 + col];
-        plv[u] = pl[it * 16 + col];
+        const size_t it = (size_t)((min(ch0 + u, lp.NCH - 1) * lp.CT + ctl) * a.n_xcd + x);
+        b.m[u] = pm[it * 16 + col];
+        b.l[u] = pl[it * 16 + col];
+        b.o[u] = *reinterpret_cast<const f32x4*>(pO + (it * DT + dt) * 64 * 4 + (size_t)lane * 4);
       }
+    };
+    auto fold = [&](const Batch& b, int ch0) {
+      float mn = mx;
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (ch0 + u < lp.NCH) {
-          const float wq = exp2f(pmv[u] - mx);
-          acc += pv[u] * wq;
-          lsum += plv[u] * wq;
-        }
+      for (int u = 0; u < 8; ++u) mn = fmaxf(mn, b.m[u]);                // (a repeated last chunk does not move the maximum)
+      const float f = exp2f(mx - mn);
+      acc *= f;
+      lsum *= f;
+      mx = mn;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const float wq = ch0 + u < lp.NCH ? exp2f(b.m[u] - mn) : 0.f;
+        acc += b.o[u] * wq;
+        lsum += b.l[u] * wq;
+      }
+    };
+    for (int ch0 = 0; ch0 < lp.NCH; ch0 += 16) {
+      Batch b0, b1;
+      fetch(b0, ch0);
+      if (ch0 + 8 < lp.NCH) fetch(b1, ch0 + 8);
+      fold(b0, ch0);
+      if (ch0 + 8 < lp.NCH) fold(b1, ch0 + 8);
     }
     acc *= 1.f / lsum;
     if (row < a.M) {
