@@ -53,6 +53,7 @@ struct bd_ctx {
   int scattered = 0;               // blocks in use that do not sit in the page of their own number (0: the cache is contiguous)
   int rows_max = 0;                // most rows any forward can have: Mp_max, or the rows of a quadratic forward through the large-M kernels
   MegaPlan plan;
+  WaveTab* wtab = nullptr;         // the plan per wavefront, for the streaming kernel
   // weights
   u16* wstream = nullptr;          // all matrices, in per-wavefront streaming order
   u16* embed = nullptr;            // bf16 [V][H] row-major (gathered, not streamed)
@@ -332,7 +333,7 @@ int forward(bd_ctx* c, int M, int mode, bool want_lm, const float* embeds, int n
 // or only the last one as row 0), and the clean-up afterwards.
 int lm_head_of_rows(bd_ctx* c, const float* xrows, int M, int mode, bool skippable, int quad_B) {
   hipStream_t s = c->stream;
-  const int ver = 2 * c->L, parts = phase_tile_slots(c->plan, PH_DOWN);
+  const int ver = 2 * c->L, parts = phase_tiles(c->plan, PH_DOWN);
   const DevState* skip = skippable ? c->st : nullptr;
   float* ssq = c->ssq + (size_t)ver * c->ssq_parts * c->Mp_max;
   // (the LM head takes as many rows at a time as the decode kernels' buffers hold)
@@ -400,13 +401,13 @@ int forward(bd_ctx* c, int M, int mode, bool want_lm, const float* embeds, int n
   }
   MegaArgs a{};
   a.P = c->plan;
+  a.wtab = c->wtab;
   a.wstream = reinterpret_cast<const bf16x8*>(c->wstream);
   a.st = c->st; a.bar = c->bar; a.bar_epoch = c->bar_epoch;
   a.M = M; a.MT = MT; a.mode = mode; a.want_lm = want_lm ? 1 : 0;
   a.skippable = skippable ? 1 : 0;
   a.xv = c->xv; a.xb = c->xb; a.xb_elems = c->xb_elems; a.ssq = c->ssq; a.ssq_parts = c->ssq_parts; a.Mp = Mp; a.gains = c->gains; a.rms_eps = c->cfg.rms_eps;
   a.fp8 = c->fp8 ? 1 : 0; a.wscale = c->wscale; a.wscale_layer = c->wscale_layer;
-  for (int i = 0; i < 4; ++i) a.wscale_off[i] = c->wscale_off[i];
   a.rope = c->rope; a.Q = c->q; a.Kc = c->Kc; a.Vc = c->Vc; a.kv_layer_elems = c->kv_layer_elems; a.max_kb = c->max_kb;
   a.kv_pages = page_table(c);
   a.ap = c->ap; a.ap_elems = c->ap_elems; a.act = c->act; a.act_elems = c->act_elems;
@@ -550,11 +551,29 @@ int bd_create(const bd_config* cfg, void* hip_stream, bd_ctx** out) {
 #define A(ptr, bytes) { int rc_ = dev_alloc(c, reinterpret_cast<void**>(&(ptr)), (bytes)); if (rc_ != BD_OK) return fail(rc_); }
   const size_t Mp = c->Mp_max, L = c->L;
   A(c->wstream, (size_t)P.nwg * kWavesPerWG * P.wave_stride * 16);
-  A(c->embed, (size_t)c->V * c->H * 2);
-  A(c->gains, (2 * L + 1) * c->H * 4);
   if (c->fp8) {
     c->wscale_off[0] = 0; c->wscale_off[1] = c->NQKV; c->wscale_off[2] = c->NQKV + c->H; c->wscale_off[3] = c->NQKV + c->H + 2 * c->F;
     c->wscale_layer = c->NQKV + 2 * c->H + 2 * c->F;
+  }
+  {
+    std::vector<WaveTab> tab((size_t)P.nwg * kWavesPerWG);
+    for (int wg = 0; wg < P.nwg; ++wg)
+      for (int w = 0; w < kWavesPerWG; ++w) {
+        WaveTab& t = tab[(size_t)wg * kWavesPerWG + w];
+        for (int p = 0; p < PH_LM; ++p) {
+          const WavePhase wp = wave_phase(P, p, wg, w);
+          t.ph[p] = make_int4(wp.row0, wp.rows >> 4 | std::max(0, std::min(wp.KW, P.ph[p].KS - wp.w0)) << 16, wp.w0, wp.KW | (c->fp8 ? c->wscale_off[p] << 5 : 0));
+        }
+        t.frags = (int)((long long)P.L * wave_layer_units(P, wg, w) / 64);
+      }
+    A(c->wtab, tab.size() * sizeof(WaveTab));
+    hipError_t e = hipMemcpyAsync(c->wtab, tab.data(), tab.size() * sizeof(WaveTab), hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) { set_last_error("plan upload failed: %s", hipGetErrorString(e)); return fail(BD_E_HIP); }
+  }
+  A(c->embed, (size_t)c->V * c->H * 2);
+  A(c->gains, (2 * L + 1) * c->H * 4);
+  if (c->fp8) {
     A(c->wscale, L * (size_t)c->wscale_layer * 4);
   }
   A(c->Kc, c->kv_layer_elems * L * 2);
@@ -562,7 +581,7 @@ int bd_create(const bd_config* cfg, void* hip_stream, bd_ctx** out) {
   A(c->xv, (2 * L + 1) * Mp * c->H * 4);
   c->xb_elems = (size_t)c->H * Mp;
   A(c->xb, (2 * L + 1) * c->xb_elems * 2);
-  c->ssq_parts = std::max(phase_tile_slots(P, PH_O), phase_tile_slots(P, PH_DOWN));
+  c->ssq_parts = std::max(phase_tiles(P, PH_O), phase_tiles(P, PH_DOWN));
   A(c->ssq, (2 * L + 1) * (size_t)c->ssq_parts * Mp * 4);
   A(c->rope, Mp * (c->D / 2) * sizeof(float2));
   A(c->q, L * Mp * c->QD * 2);
@@ -570,7 +589,7 @@ int bd_create(const bd_config* cfg, void* hip_stream, bd_ctx** out) {
   A(c->ap, L * c->ap_elems * 2);
   c->act_elems = (size_t)ceil_div(c->F, 32) * 32 * Mp;
   A(c->act, L * c->act_elems * 2);
-  c->wsD_layer_floats = (size_t)P.ph[PH_DOWN].ksplit * phase_tile_slots(P, PH_DOWN) * (Mp / 16) * 64 * 4;
+  c->wsD_layer_floats = (size_t)P.ph[PH_DOWN].ksplit * phase_tiles(P, PH_DOWN) * (Mp / 16) * 64 * 4;
   A(c->wsD, L * c->wsD_layer_floats * 4);
   {
     // attention partials of one layer: sized for the largest item count any (M, n) can produce
@@ -592,7 +611,7 @@ int bd_create(const bd_config* cfg, void* hip_stream, bd_ctx** out) {
     A(c->pO, L * c->pO_layer_floats * 4);
     A(c->pm, L * c->pml_layer_floats * 4);
     A(c->pl, L * c->pml_layer_floats * 4);
-    c->n_cntD = (int)L * phase_tile_slots(P, PH_DOWN);
+    c->n_cntD = (int)L * phase_tiles(P, PH_DOWN);
     c->n_cntA = (int)L * groups_max;
     A(c->counters, (size_t)(c->n_cntD + c->n_cntA) * 4);
   }

@@ -225,19 +225,11 @@ struct PhaseCtx {
   int* s_flags;             // LDS scratch ints
 };
 
-// Epilogue operands a caller may have fetched ahead of the product (use_pre false: the epilogue loads them itself).
-struct EpiPre {
-  float2 cs[2];   // QKV: (cos, sin) of this lane's two rotary pairs
-  f32x4 xo;       // O: the four residual values this lane adds to
-  f32x4 gn;       // O (fp8 weights): gains of the next norm for this lane's four channels
-};
-
-// DC: head dimension when the caller knows it at compile time (0: taken from the plan).
-// USE_PRE: `pre` holds this element's operands.  Either way every load of the epilogue is issued before its
-// first store: a load behind a write-through store would have to wait for that store's acknowledgement.
-template <int MT, int PH, int DC = 0, bool USE_PRE = false>
+// Every load of the epilogue is issued before its first store: a load behind a write-through store would have to wait for
+// that store's acknowledgement.
+template <int MT, int PH>
 __device__ inline void gemm_epilogue(const MegaArgs& a, const PhaseCtx& pc, const WavePhase& wp, int c, int t, int mt, f32x4 v, int lane,
-                                     float (&rmax)[MT], int (&ridx)[MT], float (&rsum)[MT], const EpiPre pre = EpiPre{}) {
+                                     float (&rmax)[MT], int (&ridx)[MT], float (&rsum)[MT]) {
   const MegaPlan& P = a.P;
   const int col = lane & 15, g = lane >> 4;
   const int token = mt * 16 + col;
@@ -247,18 +239,14 @@ __device__ inline void gemm_epilogue(const MegaArgs& a, const PhaseCtx& pc, cons
   const int nrows = min(4, wp.rows - lr);                 // ... so the last lane group may hold just 2 valid rows
   if constexpr (PH == PH_QKV) {
     if (!live) return;
-    const int D = DC ? DC : P.D, half = D >> 1;
+    const int D = P.D, half = D >> 1;
     const int rel = ((pc.n + token) >> 5) - (pc.n >> 5);    // which of the (at most three) blocks of the new rows
     const int key = ((rel == 0 ? pc.pg[0] : rel == 1 ? pc.pg[1] : pc.pg[2]) << 5) | ((pc.n + token) & 31);   // in its page
     float2 csv[2];
 #pragma unroll
     for (int pr = 0; pr < 2; ++pr) {
-      if constexpr (USE_PRE) {
-        csv[pr] = pre.cs[pr];
-      } else {
-        const int rp = r + 2 * pr;
-        csv[pr] = (2 * pr < nrows && rp < P.QD + P.KVD) ? a.rope[(size_t)token * half + ((rp % D) >> 1)] : make_float2(0.f, 0.f);
-      }
+      const int rp = r + 2 * pr;
+      csv[pr] = (2 * pr < nrows && rp < P.QD + P.KVD) ? a.rope[(size_t)token * half + ((rp % D) >> 1)] : make_float2(0.f, 0.f);
     }
 #pragma unroll
     for (int pr = 0; pr < 2; ++pr) {
@@ -294,23 +282,19 @@ __device__ inline void gemm_epilogue(const MegaArgs& a, const PhaseCtx& pc, cons
       float* xn = a.xv + ((size_t)ver * a.Mp + token) * P.H + r;
       float o[4] = {0.f, 0.f, 0.f, 0.f};
       if (nrows == 4 && (r & 3) == 0) {
-        const f32x4 ov = (USE_PRE ? pre.xo : *reinterpret_cast<const f32x4*>(xo)) + v;
+        const f32x4 ov = *reinterpret_cast<const f32x4*>(xo) + v;
         st_wt_f32x4(xn, ov);
         for (int e = 0; e < 4; ++e) o[e] = ov[e];
       } else {
         for (int e = 0; e < nrows; ++e) { o[e] = xo[e] + v[e]; st_wt_f32(xn + e, o[e]); }
       }
       ss = o[0] * o[0] + o[1] * o[1] + o[2] * o[2] + o[3] * o[3];
-      if (a.fp8) {
-        if constexpr (USE_PRE) { for (int e = 0; e < 4; ++e) o[e] *= pre.gn[e]; }
-        else { for (int e = 0; e < nrows; ++e) o[e] *= a.gains[(size_t)ver * P.H + r + e]; }
-      }
       store_xb(a.xb + (size_t)ver * a.xb_elems, token, r, nrows, o, a.MT);
     }
     ss += __shfl_xor(ss, 16);
     ss += __shfl_xor(ss, 32);
     if (g == 0)
-      st_wt_f32(a.ssq + ((size_t)ver * a.ssq_parts + (size_t)blockIdx.x * phase_tpg(P.ph[PH_O]) + 2 * c + t) * a.Mp + token, ss);
+      st_wt_f32(a.ssq + ((size_t)ver * a.ssq_parts + (wp.row0 >> 4) + 2 * c + t) * a.Mp + token, ss);
   } else if constexpr (PH == PH_GU) {
     if (!live) return;
     // rows (2f, 2f+1) = (gate f, up f)
@@ -319,15 +303,13 @@ __device__ inline void gemm_epilogue(const MegaArgs& a, const PhaseCtx& pc, cons
     for (int pr = 0; pr < 2; ++pr) {
       if (2 * pr >= nrows) break;
       const float gt = v[2 * pr], up = v[2 * pr + 1];
-      const u16 hv = f32_to_bf16_bits(gt / (1.f + __expf(-gt)) * up);
-      if (a.local_gu) base[xp_index(token, (r >> 1) + pr, a.MT)] = hv;      // read only inside this XCD: its L2 is coherent
-      else st_wt_u16(base + xp_index(token, (r >> 1) + pr, a.MT), hv);
+      st_wt_u16(base + xp_index(token, (r >> 1) + pr, a.MT), f32_to_bf16_bits(gt / (1.f + __expf(-gt)) * up));
     }
   } else if constexpr (PH == PH_DOWN) {
     // partial tile of this K group, in fragment order
     if (lr < wp.rows) {
-      const int tiles = phase_tile_slots(P, PH_DOWN);
-      const int gt = wp.ng * phase_tpg(P.ph[PH_DOWN]) + 2 * c + t;
+      const int tiles = phase_tiles(P, PH_DOWN);
+      const int gt = (wp.row0 >> 4) + 2 * c + t;
       float* dst = a.wsD + (size_t)pc.layer * a.wsD_layer_floats +
                    ((((size_t)wp.kg * tiles + gt) * a.MT + mt) * 64 + lane) * 4;
       st_wt_f32x4(dst, v);
@@ -351,9 +333,9 @@ template <int MT>
 __device__ inline bool down_finalize(const MegaArgs& a, const PhaseCtx& pc, const WavePhase& wp, int wave, int lane) {
   const MegaPlan& P = a.P;
   const int ksplit = P.ph[PH_DOWN].ksplit;
-  const int tiles = phase_tile_slots(P, PH_DOWN);
+  const int tiles = phase_tiles(P, PH_DOWN);
   const int my_tiles = (wp.rows + 15) >> 4;
-  const int gt0 = wp.ng * phase_tpg(P.ph[PH_DOWN]);
+  const int gt0 = wp.row0 >> 4;
   __syncthreads();
   if ((int)threadIdx.x < my_tiles) {
     int last = 1;
@@ -474,7 +456,7 @@ __device__ inline void gemm_phase(const MegaArgs& a, const PhaseCtx& pc, bf16x8 
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) rs[mt] = 1.f;
     if constexpr (kNorm) {
-      const int parts = ver == 0 ? 1 : phase_tile_slots(P, (ver & 1) ? PH_O : PH_DOWN);
+      const int parts = ver == 0 ? 1 : phase_tiles(P, (ver & 1) ? PH_O : PH_DOWN);
       float* s_part = reinterpret_cast<float*>(pc.red);
       float* s_rs = s_part + kWGThreads;
       row_scales_lds(s_part, s_rs, a.ssq + (size_t)ver * a.ssq_parts * a.Mp, parts, a.Mp, MT * 16, P.H, a.rms_eps);

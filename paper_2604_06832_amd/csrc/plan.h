@@ -99,11 +99,8 @@ __host__ __device__ inline int wg_of_row_group(const MegaPlan& P, int p, int ng,
 
 struct WavePhase { int rows, row0, ng, kg, w0, KW; };
 
-// 16-row tiles per row range of a phase, and (row range, tile) pairs of the whole phase
-__host__ __device__ inline int phase_tpg(const PhasePlan& ph) { return (ph.RW + 15) >> 4; }
-__host__ __device__ inline int phase_tile_slots(const MegaPlan& P, int p) {
-  return (P.nwg / P.ph[p].ksplit) * phase_tpg(P.ph[p]);
-}
+// 16-row tiles of a phase: partial sums of squares and split-K partials are kept per tile of the residual stream
+__host__ __device__ inline int phase_tiles(const MegaPlan& P, int p) { return P.ph[p].N >> 4; }
 
 template <bool CUT>
 __host__ __device__ inline WavePhase wave_phase_t(const MegaPlan& P, int p, int wg, int w) {
@@ -153,8 +150,17 @@ __host__ __device__ inline long long stream_pos(int rows, int KW, int lr, int ks
   return (long long)c * 32 * 4 * KW + (long long)ksl * (R0 + R1) * 4 + (t ? R0 * 4 : 0) + kq * R + i;
 }
 
+// The partition of one wavefront, evaluated on the host (the streaming kernel reads it instead of dividing in every phase).
+struct WaveTab {
+  int4 ph[PH_LM];           // per phase: first row; 16-row tiles + 2^16 * k-steps that exist; first k-step;
+                            // k-steps (at most 16) + 2^5 * first scale of the phase (e4m3)
+  int frags;                // 1-KiB fragments of the decoder layers' weight stream
+  int pad[3];
+};
+
 struct MegaArgs {
   MegaPlan P;
+  const WaveTab* wtab;      // [nwg][4]
   const bf16x8* wstream;
   DevState* st;
   unsigned* bar;              // barrier words (see grid_barrier)
@@ -183,7 +189,6 @@ struct MegaArgs {
                               // the bf16 copies of the residual versions that feed them
   const float* wscale;        // [L][wscale_layer] scales in phase-row order: QKV | O | gate/up | down
   int wscale_layer;
-  int wscale_off[4];
   float rms_eps;
   const float2* rope;         // [Mp][D/2]
   u16* Q;                     // [L][Mp][n_q][D]  (dims in rotary-pair order)

@@ -27,20 +27,14 @@
 namespace bd {
 
 constexpr int kFwdThreads = 512;      // 4 consumer + 4 producer wavefronts
-#ifndef BD_SLOTS
-#define BD_SLOTS 28
-#endif
-#ifndef BD_PROD_BATCH
-#define BD_PROD_BATCH 4
-#endif
-#ifndef BD_PROD_DEPTH
-#define BD_PROD_DEPTH 6
-#endif
-constexpr int kSlots = BD_SLOTS;            // 1-KiB ring slots per consumer
-constexpr int kProdBatch = BD_PROD_BATCH;   // fragments a producer issues between two publications
-constexpr int kProdDepth = BD_PROD_DEPTH;   // loads it leaves in flight when it publishes
+constexpr int kSlots = 24;                  // 1-KiB ring slots per consumer
+constexpr int kMirror = 3;                  // copies of the first slots behind the last one: any four fragments in sequence
+                                            // are contiguous in LDS, so a group is read with one address
 constexpr int kLdsSpin = 1 << 22;           // bound of every LDS wait (a timed-out wait marks the context broken)
+constexpr int kRingBytes = (kSlots + kMirror) * 1024;
 constexpr int kShareBytes = 40 * 1024;      // K-reduction buffers / attention merge buffers (one region, re-used)
+// 16-row tiles a wavefront accumulates before the K ranges are summed
+template <int MT> constexpr int round_tiles() { return MT == 1 ? 6 : 4; }
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
@@ -101,58 +95,7 @@ __device__ inline void cbar(FwdSync& sy, int lane, DevState* st) {
 // ---- producer ----------------------------------------------------------------------------------------------
 // Row ranges are whole tiles, so a consumer's stream is a plain sequence of 1-KiB fragments: fragment q of the
 // forward sits at byte q*1024 of the wavefront's stream, lane l's 16 bytes at l*16.
-template <bool CUT>
-__device__ inline unsigned stream_fragments(const MegaPlan& P, int cw) {
-  return (unsigned)((long long)P.L * wave_layer_units_t<CUT>(P, blockIdx.x, cw) / 64);
-}
-
-template <bool CUT>
-__device__ inline void producer_loop(const MegaArgs& a, int cw, char* ring, unsigned sync_base, int lane) {
-  const MegaPlan& P = a.P;
-  const unsigned total = stream_fragments<CUT>(P, cw);
-  const rsrc_t wr = make_rsrc(a.wstream + (size_t)(blockIdx.x * kWavesPerWG + cw) * P.wave_stride, total * 1024u);
-  const unsigned landed_addr = sync_base + (SY_LANDED + cw) * 4;
-  const unsigned consumed_addr = sync_base + (SY_CONSUMED + cw) * 4;
-  const unsigned dead_addr = sync_base + SY_DEAD * 4;
-  unsigned issued = 0, landed = 0, consumed = 0;
-  int slot = 0, since = 0;
-  while (issued < total) {
-    if (issued - consumed >= (unsigned)kSlots) {
-      // ring full: publish everything that is under way, then wait for the consumer
-      if (landed != issued) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        landed = issued;
-        lds_st32(landed_addr, landed);
-        since = 0;
-      }
-      int spins = 0;
-      bool ok = true;
-      while (issued - (consumed = lds_ld32(consumed_addr)) >= (unsigned)kSlots) {
-        __builtin_amdgcn_s_sleep(1);
-        if ((++spins & 31) == 0 && (lds_ld32(dead_addr) != 0u || spins > kLdsSpin)) { ok = false; break; }
-      }
-      if (!ok) break;
-    }
-    if (!a.no_weights)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_void_t*)(ring + slot * 1024), 16, (int)(issued * 1024u) + lane * 16, 0, 0,
-                                               kAuxNt);
-    ++issued;
-    slot = (slot + 1 == kSlots) ? 0 : slot + 1;
-    if (++since == kProdBatch) {
-      since = 0;
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kProdDepth) : "memory");   // all but the newest kProdDepth are in LDS
-      if (issued > (unsigned)kProdDepth && (int)(issued - kProdDepth - landed) > 0) {
-        landed = issued - kProdDepth;
-        lds_st32(landed_addr, landed);
-      }
-    }
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  lds_st32(landed_addr, issued);
-}
-
-// ---- producer with a register stash behind the ring -------------------------------------------------------------
-// The ring alone holds 28 KiB per consumer; the phases that stream almost nothing (QKV, attention, O and their
+// The ring alone holds 24 KiB per consumer; the phases that stream almost nothing (QKV, attention, O and their
 // hand-overs, a third of a layer's time) would leave HBM idle once it is full.  A producer wavefront owns as many
 // registers as a consumer and needs none, so it keeps NS further fragments there: every fragment travels
 // HBM -> stash register -> ring slot, the stash being a circular buffer of NS / 4 groups of four fragments between the
@@ -172,7 +115,7 @@ __device__ inline void producer_loop(const MegaArgs& a, int cw, char* ring, unsi
 #ifndef BD_STASH_TICKS
 #define BD_STASH_TICKS 30
 #endif
-constexpr int kStash = BD_STASH;                 // fragments a producer keeps in registers (4 registers each); 0: ring only
+constexpr int kStash = BD_STASH;                 // fragments a producer keeps in registers (4 registers each)
 constexpr int kStashGroup = 4;                   // fragments moved or requested per step
 constexpr unsigned kStashTicks = BD_STASH_TICKS; // 10-ns ticks per fragment of the background pace (1 KiB / 300 ns = 3.4 GB/s a wavefront: a layer needs 2.5)
 #ifndef BD_STASH_TICKS_FAST
@@ -200,12 +143,12 @@ __device__ inline void wait_for_loads(unsigned younger) {
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-template <bool CUT, int NS>
+template <int NS>
 __device__ inline void producer_loop_stash(const MegaArgs& a, int cw, char* ring, unsigned sync_base, int lane) {
   constexpr int NG = NS / kStashGroup;
   const MegaPlan& P = a.P;
   // (everything the inline assembly takes in scalar registers is made uniform explicitly)
-  const unsigned total = (unsigned)__builtin_amdgcn_readfirstlane((int)stream_fragments<CUT>(P, cw));
+  const unsigned total = (unsigned)__builtin_amdgcn_readfirstlane(a.wtab[blockIdx.x * kWavesPerWG + cw].frags);
   const unsigned total_up = (total + kStashGroup - 1) / kStashGroup * kStashGroup;   // (loads past the end read zeros and move no data)
   const size_t wbase = (size_t)(a.wstream + (size_t)(blockIdx.x * kWavesPerWG + cw) * P.wave_stride);
   const unsigned wlo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)wbase);
@@ -241,6 +184,10 @@ __device__ inline void producer_loop_stash(const MegaArgs& a, int cw, char* ring
           bf16x8* dst = reinterpret_cast<bf16x8*>(ring + slot * 1024 + lane * 16);
 #pragma unroll
           for (int j = 0; j < kStashGroup; ++j) dst[j * 64] = st[kStashGroup * k + j];
+          if (slot == 0) {
+#pragma unroll
+            for (int j = 0; j < kMirror; ++j) dst[(kSlots + j) * 64] = st[kStashGroup * k + j];
+          }
           asm volatile("" ::: "memory");
           moved += kStashGroup;
           lds_st32(landed_addr, min(moved, total));   // LDS executes a wavefront's operations in order
@@ -274,6 +221,21 @@ __device__ inline void producer_loop_stash(const MegaArgs& a, int cw, char* ring
   asm volatile("s_waitcnt vmcnt(0)\n\t; BD_STASH_END" ::: "memory");
 }
 
+// Reductions over the four 16-lane rows of a wavefront (the lanes that share a column of a C fragment), with the
+// row-swap instructions of gfx950: two VALU operations per step, no LDS traffic.
+__device__ inline float rows_max(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  const float m = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+__device__ inline float rows_sum(float x) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  const float m = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
 // ---- consumer side of the ring -------------------------------------------------------------------------------
 struct Ring {
   const char* base;        // this consumer's slots
@@ -283,111 +245,35 @@ struct Ring {
   int slot;
 };
 
-__device__ inline void ring_need(Ring& rg, FwdSync& sy, int nf, DevState* st) {
+// Wait until nf more fragments than were taken have landed.  (Kept small: it is there once per group of fragments.  A
+// wait that gives up marks the workgroup dead and makes every later one return at once.)
+__device__ inline void ring_need(Ring& rg, FwdSync& sy, int nf) {
   const unsigned need = rg.taken + (unsigned)nf;
-  if ((int)(rg.have - need) < 0 && !sy.dead) {
+  if ((int)(rg.have - need) < 0) {
     int spins = 0;
-    while ((int)((rg.have = lds_ld32(rg.landed_addr)) - need) < 0) {
-      if ((++spins & 63) == 0) {
-        if (lds_ld32(sy.base + SY_DEAD * 4) != 0u) { sy.dead = true; break; }
-        if (spins > kLdsSpin) { mark_dead(sy, st); break; }
-      }
+    do rg.have = lds_ld32(rg.landed_addr);
+    while ((int)(rg.have - need) < 0 && ++spins < kLdsSpin);
+    if ((int)(rg.have - need) < 0) {
+      sy.dead = true;
+      lds_st32(sy.base + SY_DEAD * 4, 1u);
+      rg.have = need + 0x40000000u;
     }
   }
   asm volatile("" ::: "memory");
 }
-__device__ inline bf16x8 ring_take(Ring& rg, int lane) {
-  const bf16x8 v = *reinterpret_cast<const bf16x8*>(rg.base + rg.slot * 1024 + lane * 16);
-  rg.slot = (rg.slot + 1 == kSlots) ? 0 : rg.slot + 1;
-  ++rg.taken;
-  return v;
+// Four fragments from slot `slot` on (contiguous: the mirror makes them so).
+__device__ inline void ring_read4(const Ring& rg, int slot, u32x4 (&f)[4], int lane) {
+  const u32x4* src = reinterpret_cast<const u32x4*>(rg.base + slot * 1024 + lane * 16);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) f[j] = src[j * 64];
 }
-__device__ inline void ring_release(Ring& rg) { lds_st32(rg.consumed_addr, rg.taken); }
-
-// One chunk (one or two 16-row tiles x KW k-steps) out of the ring, in batches of kBK k-steps, software
-// pipelined over two small register sets: the LDS reads of batch b+1 are issued (and their slots handed back to
-// the producer: LDS executes a wavefront's operations in order) before the MFMAs of batch b.
-#ifndef BD_BK
-#define BD_BK 2
-#endif
-constexpr int kBK = BD_BK;
-template <int NT>
-__device__ inline void ring_fetch(Ring& rg, FwdSync& sy, DevState* st, int nk, bf16x8 (&f)[kBK][NT], int lane) {
-  ring_need(rg, sy, nk * NT, st);
-#pragma unroll
-  for (int u = 0; u < kBK; ++u)
-    if (u < nk) {
-#pragma unroll
-      for (int t = 0; t < NT; ++t) f[u][t] = ring_take(rg, lane);
-    }
-  ring_release(rg);
-  asm volatile("" ::: "memory");                            // the reads are issued before anything that follows
-}
-// The same with the number of k-steps known at compile time: straight-line code, so the compiler's LDS wait
-// counts leave the reads of the next batch in flight during the MFMAs of this one.
-template <int MT, bool TWO, int K0, int KWC>
-__device__ inline void consume_chunk_static(Ring& rg, FwdSync& sy, DevState* st, const bf16x8 (&xk)[kMaxKW][MT],
-                                            f32x4 (&acc)[kT][MT], int lane) {
-  static_assert(KWC % kBK == 0, "whole batches");
-  constexpr int NT = TWO ? 2 : 1;
-  static_assert(KWC * NT <= kSlots, "a run must fit the ring");
-  bf16x8 f[2][kBK][NT];
-  ring_need(rg, sy, KWC * NT, st);                          // one check for the whole run
-#pragma unroll
-  for (int u = 0; u < kBK; ++u)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) f[0][u][t] = ring_take(rg, lane);
-#pragma unroll
-  for (int b = 0; b < KWC / kBK; ++b) {
-    if (b + 1 < KWC / kBK) {
-#pragma unroll
-      for (int u = 0; u < kBK; ++u)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) f[(b + 1) & 1][u][t] = ring_take(rg, lane);
-    }
-#pragma unroll
-    for (int u = 0; u < kBK; ++u)
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[b & 1][u][t], xk[K0 + b * kBK + u][mt], acc[t][mt], 0, 0, 0);
-  }
-  ring_release(rg);
-}
-
-template <int MT, bool TWO>
-__device__ inline void consume_chunk(Ring& rg, FwdSync& sy, DevState* st, const bf16x8 (&xk)[kMaxKW][MT], int KW,
-                                     f32x4 (&acc)[kT][MT], int lane) {
-  constexpr int NT = TWO ? 2 : 1;
-  if (KW == kMaxKW) {                                       // the common case: a full K range, in runs that fit the ring
-    if constexpr (TWO) {
-      consume_chunk_static<MT, TWO, 0, kMaxKW / 2>(rg, sy, st, xk, acc, lane);
-      consume_chunk_static<MT, TWO, kMaxKW / 2, kMaxKW / 2>(rg, sy, st, xk, acc, lane);
-    } else {
-      consume_chunk_static<MT, TWO, 0, kMaxKW>(rg, sy, st, xk, acc, lane);
-    }
-    return;
-  }
-  bf16x8 f[2][kBK][NT];
-  ring_fetch<NT>(rg, sy, st, min(kBK, KW), f[0], lane);
-#pragma unroll
-  for (int b = 0; b < kMaxKW / kBK; ++b) {
-    const int kb = b * kBK;
-    if (kb < KW) {
-      if (kb + kBK < KW) ring_fetch<NT>(rg, sy, st, min(kBK, KW - kb - kBK), f[(b + 1) & 1], lane);
-      const int nk = min(kBK, KW - kb);
-#pragma unroll
-      for (int u = 0; u < kBK; ++u)
-        if (u < nk) {
-#pragma unroll
-          for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-              acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[b & 1][u][t], xk[kb + u][mt], acc[t][mt], 0, 0, 0);
-        }
-    }
-  }
+// The next nf fragments have been read: hand their slots back (LDS executes a wavefront's operations in order).
+__device__ inline void ring_done(Ring& rg, int nf) {
+  asm volatile("" ::: "memory");
+  rg.taken += (unsigned)nf;
+  rg.slot += nf;
+  rg.slot -= rg.slot >= kSlots ? kSlots : 0;
+  lds_st32(rg.consumed_addr, rg.taken);
 }
 
 // e4m3 weights: one ring fragment holds a 16-row tile for TWO k-steps (lane: 8 codes of the even step, then 8 of
@@ -408,300 +294,374 @@ __device__ inline void widen_e4m3(const u32x4 raw, bf16x8& even, bf16x8& odd) {
   odd = b.v;
 }
 
-template <int MT, bool TWO>
-__device__ inline void consume_chunk_fp8(Ring& rg, FwdSync& sy, DevState* st, const bf16x8 (&xk)[kMaxKW][MT], int KW,
-                                         f32x4 (&acc)[kT][MT], int lane) {
-  constexpr int NT = TWO ? 2 : 1;
+// One chunk of the stream (one or two 16-row tiles x `steps` fragment steps of one (bf16) or two (e4m3) k-steps) out of
+// the ring, four fragments at a time through two register sets: the LDS reads of a group are issued before the MFMAs of
+// the group before it, and its slots are handed back at once.  (The last group is read whole: what lies beyond the
+// chunk's last fragment is not used.)
+template <int MT, bool TWO, bool FP8>
+__device__ inline void consume_chunk(Ring& rg, FwdSync& sy, const bf16x8 (&xk)[kMaxKW][MT], int steps, f32x4 (&acc)[kT][MT], int lane) {
+  constexpr int KF = FP8 ? 2 : 1;                           // k-steps per fragment
+  constexpr int NT = TWO ? 2 : 1, SPG = 4 / NT;             // tiles; fragment steps per group of four
+  constexpr int NG = (kMaxKW / KF + SPG - 1) / SPG;
+  u32x4 f[2][4];
+  auto take = [&](u32x4 (&dst)[4], int nf) {
+    ring_need(rg, sy, nf);
+    ring_read4(rg, rg.slot, dst, lane);
+    ring_done(rg, nf);
+    asm volatile("" ::: "memory");                          // the reads are issued before anything that follows
+  };
+  take(f[0], min(steps * NT, 4));
 #pragma unroll
-  for (int kb = 0; kb < kMaxKW; kb += 4) {                // two fragments per tile and batch
-    if (kb < KW) {
-      const int np = min(2, (KW - kb) >> 1);               // k-step pairs in this batch (KW is even)
-      ring_need(rg, sy, np * NT, st);
+  for (int b = 0; b < NG; ++b) {
+    if (b + 1 < NG) {
+      asm volatile("" : "+s"(steps));                       // (or every comparison is evaluated up front and kept in registers)
+      if ((b + 1) * SPG < steps) take(f[(b + 1) & 1], min((steps - (b + 1) * SPG) * NT, 4));
+    }
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        if (u < np) {
-          u32x4 raw[NT];
+    for (int u = 0; u < SPG; ++u) {
+      if (u > 0) {
+        asm volatile("" : "+s"(steps));
+        if (b * SPG + u >= steps) break;
+      }
 #pragma unroll
-          for (int t = 0; t < NT; ++t) raw[t] = __builtin_bit_cast(u32x4, ring_take(rg, lane));
+      for (int t = 0; t < NT; ++t) {
+        const u32x4 raw = f[b & 1][u * NT + t];
+        if constexpr (FP8) {
+          bf16x8 we, wo;
+          widen_e4m3(raw, we, wo);
 #pragma unroll
-          for (int t = 0; t < NT; ++t) {
-            bf16x8 we, wo;
-            widen_e4m3(raw[t], we, wo);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-              acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(we, xk[kb + 2 * u][mt], acc[t][mt], 0, 0, 0);
-              acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wo, xk[kb + 2 * u + 1][mt], acc[t][mt], 0, 0, 0);
-            }
+          for (int mt = 0; mt < MT; ++mt) {
+            acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(we, xk[2 * (b * SPG + u)][mt], acc[t][mt], 0, 0, 0);
+            acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wo, xk[2 * (b * SPG + u) + 1][mt], acc[t][mt], 0, 0, 0);
           }
+        } else {
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+            acc[t][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, raw), xk[b * SPG + u][mt], acc[t][mt], 0, 0, 0);
         }
       }
-      ring_release(rg);
+    }
+    if (b + 1 < NG) {
+      asm volatile("" : "+s"(steps));
+      if ((b + 1) * SPG >= steps) break;
     }
   }
 }
 
+// What a consumer needs to know of a phase, read from LDS (filled from MegaArgs::wtab when the kernel starts).
 struct FwdCtx {
-  PhaseCtx pc;            // layer, n, red (LDS), s_flags
-  f32x4* red2;            // second K-reduction buffer (chunks alternate)
-  float* s_part;          // LDS [4][64] partial sums of squares per consumer
-  char* share;            // LDS region shared by the K-reduction and the attention merge
+  int layer, n;             // layer index, committed context length
+  int pg[3];                // pages of the blocks that hold positions n .. n+63 (the new rows' keys and values)
+  f32x4* red;               // LDS [4][kRound * MT][64]: partial tiles of the four K ranges
+  float* s_part;            // LDS [4][64] partial sums of squares per consumer
+  char* share;              // LDS region shared by the K-reduction and the attention merge
+  int* s_flags;             // LDS scratch ints
+  const int4* s_plan;       // LDS [4 phases][4 consumers]: WaveTab::ph
 };
 
+// ---- epilogues -------------------------------------------------------------------------------------------------
+// v: rows r .. r+3 of one token (lane: column = token, row quad).  Every load of an epilogue precedes its first store: a
+// load behind a write-through store would have to wait for that store's acknowledgement.
+template <int D>
+__device__ inline void epilogue_qkv(const MegaArgs& a, const FwdCtx& fc, int token, int r, f32x4 v, f32x4 cs) {
+  const MegaPlan& P = a.P;
+  const int rel = ((fc.n + token) >> 5) - (fc.n >> 5);      // which of the (at most three) blocks of the new rows
+  const int key = ((rel == 0 ? fc.pg[0] : rel == 1 ? fc.pg[1] : fc.pg[2]) << 5) | ((fc.n + token) & 31);   // in its page
+  if (r < P.QD + P.KVD) {
+    // rotary pairs: phase rows (2i, 2i+1) of a head hold dims (i, i + D/2)
+    const uint32_t p0 = (uint32_t)f32_to_bf16_bits(v[0] * cs[0] - v[1] * cs[1]) |
+                        ((uint32_t)f32_to_bf16_bits(v[1] * cs[0] + v[0] * cs[1]) << 16);
+    const uint32_t p1 = (uint32_t)f32_to_bf16_bits(v[2] * cs[2] - v[3] * cs[3]) |
+                        ((uint32_t)f32_to_bf16_bits(v[3] * cs[2] + v[2] * cs[3]) << 16);
+    u16* dst;
+    if (r < P.QD) {
+      dst = a.Q + ((size_t)fc.layer * a.Mp + token) * P.QD + r;
+    } else {
+      const int rk = r - P.QD;
+      dst = a.Kc + (size_t)fc.layer * a.kv_layer_elems + (size_t)(rk / D) * a.max_kb * 32 * D + kp_index(key, rk % D, D / 32);
+    }
+    st_wt_u64(dst, (uint64_t)p0 | ((uint64_t)p1 << 32));
+  } else {
+    const int rv = r - P.QD - P.KVD;
+    u16* vc = a.Vc + (size_t)fc.layer * a.kv_layer_elems + (size_t)(rv / D) * a.max_kb * 32 * D + vp_index(key, rv % D, D / 16);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) st_wt_u16(vc + e * 8, f32_to_bf16_bits(v[e]));   // (four consecutive dims of one 16-dim tile)
+  }
+}
+
+// x_new = x_old + v into residual version `ver`: fp32, bf16 copy (times the next norm's gain with e4m3 weights), sum of
+// squares of this tile's 16 channels.
+template <bool FP8>
+__device__ inline void epilogue_residual(const MegaArgs& a, int ver, int token, int r, f32x4 v, f32x4 xo, f32x4 gn, int g) {
+  float ss = 0.f;
+  if (token < a.M) {
+    const f32x4 o = xo + v;
+    st_wt_f32x4(a.xv + ((size_t)ver * a.Mp + token) * a.P.H + r, o);
+    ss = o[0] * o[0] + o[1] * o[1] + o[2] * o[2] + o[3] * o[3];
+    const f32x4 w = FP8 ? o * gn : o;
+    const uint32_t lo = (uint32_t)f32_to_bf16_bits(w[0]) | ((uint32_t)f32_to_bf16_bits(w[1]) << 16);
+    const uint32_t hi = (uint32_t)f32_to_bf16_bits(w[2]) | ((uint32_t)f32_to_bf16_bits(w[3]) << 16);
+    st_wt_u64(a.xb + (size_t)ver * a.xb_elems + xp_index(token, r, a.MT), (uint64_t)lo | ((uint64_t)hi << 32));
+  }
+  ss = rows_sum(ss);
+  if (g == 0) st_wt_f32(a.ssq + ((size_t)ver * a.ssq_parts + (r >> 4)) * a.Mp + token, ss);
+}
+
 // ---- one GEMM phase (consumer wavefronts) ------------------------------------------------------------------------
-template <int MT, int PH, int D, bool FP8>
-__device__ inline void stream_gemm_phase(const MegaArgs& a, FwdCtx& fc, Ring& rg, FwdSync& sy, int wave, int lane_in) {
+// The four phases run the same code with the phase as a runtime value: the loads of the activations, the walk over the
+// ring and the reduction are there once.  What that is for is the instruction cache (64 KiB for two compute units): every
+// hand-over is a chain in which a miss is not hidden by anything.  With a copy per phase, and the partition of the
+// rows evaluated in each (64-bit divisions, a fifth of all instructions), the kernel was 156 KB and missed its cache about
+// 180 times per layer; now 70 KB and 6 times.  The K ranges are summed once per round of 6 (one token tile) or 4 (two:
+// more accumulators spill) row tiles instead of once per pair.  One forward, 3B shape, 1024 keys: 1 row 2116 -> 1995 us,
+// 32 rows 2422 -> 2211 us (two token tiles: rounds of 6 tiles 2442, of 2 tiles 2243).
+template <int MT, int D, bool FP8>
+__device__ inline void stream_gemm_phase(const MegaArgs& a, FwdCtx& fc, Ring& rg, FwdSync& sy, int ph, int wave, int lane_in) {
+  constexpr int kRound = round_tiles<MT>();
   int lane = lane_in;
   asm volatile("" : "+v"(lane));
   const MegaPlan& P = a.P;
-  PhaseCtx& pc = fc.pc;
-  const WavePhase wp = wave_phase_t<FP8>(P, PH, blockIdx.x, wave);
-  const int n_tiles = (wp.rows + 15) >> 4;
-  const int n_chunks = (n_tiles + 1) >> 1;
-  float rmax[MT], rsum[MT];
-  int ridx[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) { rmax[mt] = -INFINITY; ridx[mt] = 0x7FFFFFFF; rsum[mt] = 0.f; }
+  const int col = lane & 15, g = lane >> 4;
+  int row0, n_tiles, w0, KW, KX, ws_off;                     // (KX: k-steps of KW that exist; e4m3 ranges may reach past the end)
+  {
+    const int4 d = fc.s_plan[ph * kWavesPerWG + wave];
+    row0 = __builtin_amdgcn_readfirstlane(d.x);
+    const int y = __builtin_amdgcn_readfirstlane(d.y);
+    n_tiles = y & 0xFFFF;
+    KX = y >> 16;
+    w0 = __builtin_amdgcn_readfirstlane(d.z);
+    const int w = __builtin_amdgcn_readfirstlane(d.w);
+    KW = w & 31;
+    ws_off = w >> 5;
+  }
 
 #define BD_SUBTS2(k)                                                                                  \
   do {                                                                                                \
-    if (a.trace2 != nullptr && pc.layer == 1 && threadIdx.x == 0 && PH < PH_LM)                        \
-      a.trace2[(size_t)blockIdx.x * 64 + PH * 12 + (k)] = wall_clock64();                              \
+    if (a.trace2 != nullptr && fc.layer == 1 && threadIdx.x == 0) a.trace2[(size_t)blockIdx.x * 64 + ph * 12 + (k)] = wall_clock64(); \
   } while (0)
   BD_SUBTS2(0);
-  if (n_chunks > 0) {
-    constexpr bool kNorm = (PH == PH_QKV || PH == PH_GU || PH == PH_LM);
-    const int ver = (PH == PH_QKV) ? 2 * pc.layer : (PH == PH_GU) ? 2 * pc.layer + 1 : 2 * P.L;
-    const rsrc_t xr = kNorm ? make_rsrc(a.xb + (size_t)ver * a.xb_elems, (unsigned)(a.xb_elems * 2))
-                            : (PH == PH_O ? make_rsrc(a.ap + (size_t)pc.layer * a.ap_elems, (unsigned)(a.ap_elems * 2))
-                                          : make_rsrc(a.act + (size_t)pc.layer * a.act_elems, (unsigned)(a.act_elems * 2)));
+  if (n_tiles > 0) {
+    const bool norm = ph == PH_QKV || ph == PH_GU;
+    const int ver = 2 * fc.layer + (ph == PH_GU ? 1 : 0);
+    const u16* src = norm ? a.xb + (size_t)ver * a.xb_elems
+                          : (ph == PH_O ? a.ap + (size_t)fc.layer * a.ap_elems : a.act + (size_t)fc.layer * a.act_elems);
+    const rsrc_t xr = make_rsrc(src + (size_t)w0 * MT * 512, (unsigned)(KX * MT * 1024));   // (k-steps beyond KX read as zero)
+    // this wavefront's share (parts = wave*4 + lane group mod 16) of the sums of squares of every row, ahead of the
+    // activations: they are summed while those arrive
+    float sv[MT][8];
+    if (norm) {
+      const int parts = ver == 0 ? 1 : P.H >> 4;
+      const rsrc_t sr = make_rsrc(a.ssq + (size_t)ver * a.ssq_parts * a.Mp, (unsigned)(parts * a.Mp * 4));
+      const int so = ((wave * 4 + g) * a.Mp + col) * 4;
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          sv[mt][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, so + mt * 64, u * 16 * a.Mp * 4, 0));
+      asm volatile("" ::: "memory");
+    }
     // activation fragments of this wavefront's k-steps: one round trip, straight into registers
     bf16x8 xk[kMaxKW][MT];
 #pragma unroll
     for (int ksl = 0; ksl < kMaxKW; ++ksl)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        xk[ksl][mt] = buf_load_b(xr, ksl < wp.KW ? (((wp.w0 + ksl) * MT + mt) * 64 + lane) * 16 : kOob);
-    if constexpr (kNorm) {
-      // this wavefront's share (parts = wave*4 + lane group mod 16) of the sums of squares of every row
-      const int parts = ver == 0 ? 1 : phase_tile_slots(P, (ver & 1) ? PH_O : PH_DOWN);
-      const rsrc_t sr = make_rsrc(a.ssq + (size_t)ver * a.ssq_parts * a.Mp, (unsigned)((size_t)parts * a.Mp * 4));
-      const int col = lane & 15, g = lane >> 4;
-      float sv[MT][16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int p = wave * 4 + g + 16 * u;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          sv[mt][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                    sr, p < parts ? (p * a.Mp + mt * 16 + col) * 4 : kOob, 0, 0));
-      }
+      for (int mt = 0; mt < MT; ++mt) xk[ksl][mt] = buf_load_b(xr, (ksl * MT + mt) * 1024 + lane * 16);
+    asm volatile("" ::: "memory");
+    if (norm) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         float s = 0.f;
 #pragma unroll
-        for (int u = 0; u < 16; ++u) s += sv[mt][u];
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
+        for (int u = 0; u < 8; ++u) s += sv[mt][u];
+        s = rows_sum(s);
         if (g == 0) fc.s_part[wave * 64 + mt * 16 + col] = s;
       }
     }
-    float rs[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) rs[mt] = 1.f;
     BD_SUBTS2(1);
-
-    for (int c = 0; c < n_chunks; ++c) {
-      const bool two = 2 * c + 1 < n_tiles;
-      // operands of this wavefront's epilogue element of the chunk (idx == wave), fetched while the product runs
-      EpiPre pre;
-      pre.cs[0] = pre.cs[1] = make_float2(0.f, 0.f);
-      pre.xo = f32x4{0.f, 0.f, 0.f, 0.f};
-      pre.gn = f32x4{1.f, 1.f, 1.f, 1.f};
-      f32x4 wsc = f32x4{1.f, 1.f, 1.f, 1.f};                 // fp8: scales of this lane's four output rows
+    const int mt_e = MT == 1 ? 0 : wave % MT;                // token tile of this wavefront's epilogue elements (4 % MT == 0)
+    const int token = mt_e * 16 + col;
+    for (int t0 = 0; t0 < n_tiles; t0 += kRound) {
+      const int nt = min(kRound, n_tiles - t0);
+      const int n_el = nt * MT;                              // (tile, token tile) elements, dealt to the wavefronts
+      // operands of the first element's epilogue, fetched while the product runs (rotary factors, old residual values)
+      f32x4 pre = f32x4{0.f, 0.f, 0.f, 0.f}, gn = f32x4{1.f, 1.f, 1.f, 1.f};
+      f32x4 wsc[3];
+      const int r0 = row0 + (t0 + wave / MT) * 16 + 4 * g;   // first row of this lane in element i: r0 + i * (64 / MT)
+      if (wave < n_el) {
+        if (ph == PH_QKV) {
+          if (token < a.M) pre = *reinterpret_cast<const f32x4*>(a.rope + (size_t)token * (D >> 1) + ((r0 % D) >> 1));
+        } else if (ph == PH_O) {
+          if (token < a.M) pre = *reinterpret_cast<const f32x4*>(a.xv + ((size_t)(2 * fc.layer) * a.Mp + token) * P.H + r0);
+          if constexpr (FP8) gn = *reinterpret_cast<const f32x4*>(a.gains + (size_t)(2 * fc.layer + 1) * P.H + r0);
+        }
+      }
       if constexpr (FP8) {
-        static_assert(kT * MT <= kWavesPerWG, "one epilogue element per consumer");
-        if (wave < kT * MT) {
-          const int lr = (2 * c + wave / MT) * 16 + 4 * (lane >> 4);
-          if (lr < wp.rows)
-            wsc = *reinterpret_cast<const f32x4*>(a.wscale + (size_t)pc.layer * a.wscale_layer + a.wscale_off[PH] + wp.row0 + lr);
-        }
-      }
-      if constexpr (PH == PH_QKV || PH == PH_O) {
-        static_assert(kT * MT <= kWavesPerWG, "one epilogue element per consumer");
-        if (wave < kT * MT) {
-          const int t = wave / MT, mt = wave % MT;
-          const int token = mt * 16 + (lane & 15);
-          const int lr = (2 * c + t) * 16 + 4 * (lane >> 4);
-          const int r = wp.row0 + lr;
-          if (token < a.M && lr < wp.rows) {
-            if constexpr (PH == PH_QKV) {
+        const float* ws = a.wscale + (size_t)fc.layer * a.wscale_layer + ws_off;
 #pragma unroll
-              for (int pr = 0; pr < 2; ++pr) {
-                const int rp = r + 2 * pr;
-                if (2 * pr < min(4, wp.rows - lr) && rp < P.QD + P.KVD)
-                  pre.cs[pr] = a.rope[(size_t)token * (D >> 1) + ((rp % D) >> 1)];
-              }
-            } else {
-              if (min(4, wp.rows - lr) == 4 && (r & 3) == 0) {
-                pre.xo = *reinterpret_cast<const f32x4*>(a.xv + ((size_t)(2 * pc.layer) * a.Mp + token) * P.H + r);
-                if constexpr (FP8) pre.gn = *reinterpret_cast<const f32x4*>(a.gains + (size_t)(2 * pc.layer + 1) * P.H + r);
-              }
-            }
-          }
-        }
+        for (int i = 0; i < 3; ++i)
+          wsc[i] = wave + 4 * i < n_el ? *reinterpret_cast<const f32x4*>(ws + r0 + i * (64 / MT)) : f32x4{1.f, 1.f, 1.f, 1.f};
       }
-      f32x4 acc[kT][MT];
+      f32x4 acc[kRound / kT][kT][MT];
 #pragma unroll
-      for (int t = 0; t < kT; ++t)
+      for (int c = 0; c < kRound / kT; ++c)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[t][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if constexpr (PH == PH_QKV) {
-        if (c == 0) {
-          // (trace) the activations have arrived when the first MFMA could start
-          unsigned x = __builtin_bit_cast(u32x4, xk[kMaxKW - 1][MT - 1])[0] | __builtin_bit_cast(u32x4, xk[0][0])[0];
-          asm volatile("" ::"v"(x));
-          BD_SUBTS2(6);
+        for (int t = 0; t < kT; ++t)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) acc[c][t][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (KW > 0) {
+        const int steps = FP8 ? KW >> 1 : KW;
+#pragma unroll
+        for (int c = 0; c < kRound / kT; ++c) {
+          if (kT * c + 1 < nt) consume_chunk<MT, true, FP8>(rg, sy, xk, steps, acc[c], lane);
+          else if (kT * c < nt) consume_chunk<MT, false, FP8>(rg, sy, xk, steps, acc[c], lane);
         }
       }
-      if (wp.KW > 0) {
-        if constexpr (FP8) {
-          if (two) consume_chunk_fp8<MT, true>(rg, sy, a.st, xk, wp.KW, acc, lane);
-          else consume_chunk_fp8<MT, false>(rg, sy, a.st, xk, wp.KW, acc, lane);
-        } else {
-          if (two) consume_chunk<MT, true>(rg, sy, a.st, xk, wp.KW, acc, lane);
-          else consume_chunk<MT, false>(rg, sy, a.st, xk, wp.KW, acc, lane);
-        }
-      }
-      if (c < 3) BD_SUBTS2(3 + 2 * c);
+      BD_SUBTS2(3);
       // The operands fetched for the epilogue are taken here, before its first store: the vector-memory counter is
       // in order, so a wait for them placed behind a write-through store would also wait for that store's
       // acknowledgement (and after a branch that may have stored, the compiler can only wait for everything).
-      asm volatile("" ::"v"(pre.cs[0].x), "v"(pre.cs[0].y), "v"(pre.cs[1].x), "v"(pre.cs[1].y), "v"(pre.xo), "v"(pre.gn), "v"(wsc));
+      asm volatile("" ::"v"(pre), "v"(gn));
+      if constexpr (FP8) asm volatile("" ::"v"(wsc[0]), "v"(wsc[1]), "v"(wsc[2]));
       // the four consumers hold disjoint K ranges: sum them through LDS in fixed order
-      f32x4* red = (c & 1) ? fc.red2 : pc.red;
+      if (t0 > 0) cbar(sy, lane, a.st);                      // (the round before has been read)
 #pragma unroll
-      for (int t = 0; t < kT; ++t)
+      for (int c = 0; c < kRound / kT; ++c)
+        if (kT * c < nt) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) red[(wave * (kT * MT) + t * MT + mt) * 64 + lane] = acc[t][mt];
+          for (int t = 0; t < kT; ++t)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) fc.red[(wave * (kRound * MT) + (c * kT + t) * MT + mt) * 64 + lane] = acc[c][t][mt];
+        }
       cbar(sy, lane, a.st);
-      if (c == 0) BD_SUBTS2(2);
-      if constexpr (kNorm) {
-        if (c == 0) {
+      BD_SUBTS2(2);
+      float rs = 1.f;
+      if (norm) {
+        const float t = fc.s_part[token] + fc.s_part[64 + token] + fc.s_part[128 + token] + fc.s_part[192 + token];
+        rs = rsqrtf(t / (float)P.H + a.rms_eps);
+      }
+      f32x4 v[3];
+      {
+        const f32x4* rd = fc.red + wave * 64 + lane;         // (elements that are not there are read and not used)
+        f32x4 p[3][kWavesPerWG];
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            const int r = mt * 16 + (lane & 15);
-            const float t = fc.s_part[r] + fc.s_part[64 + r] + fc.s_part[128 + r] + fc.s_part[192 + r];
-            rs[mt] = rsqrtf(t / (float)P.H + a.rms_eps);
-          }
+        for (int i = 0; i < (kRound * MT + 3) / 4; ++i)
+#pragma unroll
+          for (int w = 0; w < kWavesPerWG; ++w) p[i][w] = rd[(w * kRound * MT + 4 * i) * 64];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < (kRound * MT + 3) / 4; ++i) {
+          v[i] = (p[i][0] + p[i][1] + p[i][2] + p[i][3]) * rs;
+          if constexpr (FP8) v[i] *= wsc[i];
         }
       }
+      if (ph == PH_GU) {
+        // rows (2f, 2f+1) = (gate f, up f): features f, f + 1 of this lane sit side by side
+        if (token < a.M) {
+          u16* dst = a.act + (size_t)fc.layer * a.act_elems + xp_index(token, r0 >> 1, a.MT);
 #pragma unroll
-      for (int idx = 0; idx < kT * MT; ++idx) {
-        if ((idx & 3) != wave) continue;
-        const int t = idx / MT, mt = idx % MT;
-        if (t == 1 && !two) continue;
-        f32x4 v = red[(0 * (kT * MT) + idx) * 64 + lane];
-        v += red[(1 * (kT * MT) + idx) * 64 + lane];
-        v += red[(2 * (kT * MT) + idx) * 64 + lane];
-        v += red[(3 * (kT * MT) + idx) * 64 + lane];
-        if constexpr (kNorm) v *= rs[mt];
-        if constexpr (FP8) v *= wsc;
-        if constexpr (PH == PH_QKV) { if (c == 0) BD_SUBTS2(5); }
-        gemm_epilogue<MT, PH, D, (PH == PH_QKV || PH == PH_O)>(a, pc, wp, c, t, mt, v, lane, rmax, ridx, rsum, pre);
+          for (int i = 0; i < 3; ++i) {
+            if (wave + 4 * i >= n_el) break;
+            const uint32_t h0 = f32_to_bf16_bits(v[i][0] / (1.f + __expf(-v[i][0])) * v[i][1]);
+            const uint32_t h1 = f32_to_bf16_bits(v[i][2] / (1.f + __expf(-v[i][2])) * v[i][3]);
+            u16* d = i == 0 ? dst : a.act + (size_t)fc.layer * a.act_elems + xp_index(token, (r0 + i * (64 / MT)) >> 1, a.MT);
+            if (a.local_gu) *reinterpret_cast<uint32_t*>(d) = h0 | (h1 << 16);   // read only inside this XCD: its L2 is coherent
+            else st_wt_u32(d, h0 | (h1 << 16));
+          }
+        }
+      } else if (ph == PH_DOWN) {
+        // partial tiles of this K group, in fragment order
+        const int kg = blockIdx.x % P.ph[PH_DOWN].ksplit;
+        float* dst = a.wsD + (size_t)fc.layer * a.wsD_layer_floats +
+                     ((((size_t)kg * (P.H >> 4) + (r0 >> 4)) * MT + mt_e) * 64 + lane) * 4;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+          if (wave + 4 * i < n_el) st_wt_f32x4(dst + (size_t)i * 4 * 256, v[i]);   // (element el + 4: 4 / MT tiles on)
+      } else if (ph == PH_QKV) {
+        if (wave < n_el && token < a.M) epilogue_qkv<D>(a, fc, token, r0, v[0], pre);
+#pragma unroll 1
+        for (int i = 1; wave + 4 * i < n_el; ++i) {          // (plans with more than one element per wavefront)
+          v[0] = v[1];
+          v[1] = v[2];
+          const int r = r0 + i * (64 / MT);
+          if (token < a.M)
+            epilogue_qkv<D>(a, fc, token, r, v[0], *reinterpret_cast<const f32x4*>(a.rope + (size_t)token * (D >> 1) + ((r % D) >> 1)));
+        }
+      } else {
+        if (wave < n_el) epilogue_residual<FP8>(a, 2 * fc.layer + 1, token, r0, v[0], pre, gn, g);
+#pragma unroll 1
+        for (int i = 1; wave + 4 * i < n_el; ++i) {
+          v[0] = v[1];
+          v[1] = v[2];
+          const int r = r0 + i * (64 / MT);
+          if (token < a.M) pre = *reinterpret_cast<const f32x4*>(a.xv + ((size_t)(2 * fc.layer) * a.Mp + token) * P.H + r);
+          if constexpr (FP8) gn = *reinterpret_cast<const f32x4*>(a.gains + (size_t)(2 * fc.layer + 1) * P.H + r);
+          epilogue_residual<FP8>(a, 2 * fc.layer + 1, token, r, v[0], pre, gn, g);
+        }
       }
-      if (c < 3) BD_SUBTS2(4 + 2 * c);
+      BD_SUBTS2(4);
     }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this wavefront's stores have been acknowledged
   BD_SUBTS2(9);
 
-  if constexpr (PH == PH_DOWN) {
+  if (ph == PH_DOWN && n_tiles > 0) {
     // the last of the ksplit workgroups to finish a tile sums all partials, adds the residual, stores the new
     // residual version and its sum of squares
     const int ksplit = P.ph[PH_DOWN].ksplit;
-    const int tiles = phase_tile_slots(P, PH_DOWN);
-    const int my_tiles = (wp.rows + 15) >> 4;
-    const int gt0 = wp.ng * phase_tpg(P.ph[PH_DOWN]);
-    const int col = lane & 15, g = lane >> 4;
-    const int ver = 2 * pc.layer + 2;
-    const int n_idx = my_tiles * MT;                          // (tile, row tile of tokens) pairs of this row range
+    const int tiles = P.H >> 4, gt0 = row0 >> 4;
+    const int ver = 2 * fc.layer + 2;
+    const int n_idx = n_tiles * MT;                           // (tile, row tile of tokens) pairs of this row range
     cbar(sy, lane, a.st);                                    // every consumer's partials are out
-    if (wave == 0 && lane < my_tiles) {
+    if (wave == 0 && lane < n_tiles) {
       int last = 1;
       if (ksplit > 1) {
-        const unsigned old = __hip_atomic_fetch_add(a.cntD + (size_t)pc.layer * tiles + gt0 + lane, 1u, __ATOMIC_RELAXED,
+        const unsigned old = __hip_atomic_fetch_add(a.cntD + (size_t)fc.layer * tiles + gt0 + lane, 1u, __ATOMIC_RELAXED,
                                                     __HIP_MEMORY_SCOPE_AGENT);
         last = old == (unsigned)ksplit - 1u;
       }
-      pc.s_flags[8 + lane] = last;
+      fc.s_flags[8 + lane] = last;
     }
     cbar(sy, lane, a.st);
-    const float* src = a.wsD + (size_t)pc.layer * a.wsD_layer_floats;
+    const float* src = a.wsD + (size_t)fc.layer * a.wsD_layer_floats;
     for (int idx0 = wave; idx0 < n_idx; idx0 += 2 * kWavesPerWG) {
       // two pairs per round, every load of the round in flight at once
       f32x4 pv[2][8], xov[2], gnv[2];
-      bool on[2], vec[2];
-      int tok[2], rr[2], nr[2], gtt[2];
+      bool on[2];
+      int tok[2], rr[2];
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const int idx = idx0 + j * kWavesPerWG;
         const int tl = idx / MT, mt = idx % MT;
-        on[j] = idx < n_idx && pc.s_flags[8 + min(tl, my_tiles - 1)];
-        gtt[j] = gt0 + tl;
+        on[j] = idx < n_idx && fc.s_flags[8 + min(tl, n_tiles - 1)];
         tok[j] = mt * 16 + col;
-        const int lr = tl * 16 + 4 * g;
-        rr[j] = wp.row0 + lr;
-        nr[j] = min(4, wp.rows - lr);
-        vec[j] = nr[j] == 4 && (rr[j] & 3) == 0;
+        rr[j] = row0 + tl * 16 + 4 * g;
         xov[j] = f32x4{0.f, 0.f, 0.f, 0.f};
         gnv[j] = f32x4{1.f, 1.f, 1.f, 1.f};
         if constexpr (FP8) {
-          if (on[j] && vec[j] && ver < 2 * P.L) gnv[j] = *reinterpret_cast<const f32x4*>(a.gains + (size_t)ver * P.H + rr[j]);
+          if (on[j] && ver < 2 * P.L) gnv[j] = *reinterpret_cast<const f32x4*>(a.gains + (size_t)ver * P.H + rr[j]);
         }
         if (on[j]) {
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
             const int kg = min(u, ksplit - 1);
-            pv[j][u] = *reinterpret_cast<const f32x4*>(src + ((((size_t)kg * tiles + gtt[j]) * a.MT + mt) * 64 + lane) * 4);
+            pv[j][u] = *reinterpret_cast<const f32x4*>(src + ((((size_t)kg * tiles + gt0 + tl) * MT + mt) * 64 + lane) * 4);
           }
-          if (tok[j] < a.M && vec[j])
-            xov[j] = *reinterpret_cast<const f32x4*>(a.xv + ((size_t)(ver - 1) * a.Mp + tok[j]) * P.H + rr[j]);
+          if (tok[j] < a.M) xov[j] = *reinterpret_cast<const f32x4*>(a.xv + ((size_t)(ver - 1) * a.Mp + tok[j]) * P.H + rr[j]);
         }
       }
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         if (!on[j]) continue;
         const int idx = idx0 + j * kWavesPerWG;
-        const int mt = idx % MT;
+        const int tl = idx / MT, mt = idx % MT;
         f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < 8; ++u)
           if (u < ksplit) v += pv[j][u];
         for (int kg = 8; kg < ksplit; ++kg)
-          v += *reinterpret_cast<const f32x4*>(src + ((((size_t)kg * tiles + gtt[j]) * a.MT + mt) * 64 + lane) * 4);
-        const int token = tok[j], r = rr[j], nrows = nr[j];
-        float ss = 0.f;
-        if (token < a.M && nrows > 0) {
-          const float* xo = a.xv + ((size_t)(ver - 1) * a.Mp + token) * P.H + r;
-          float* xn = a.xv + ((size_t)ver * a.Mp + token) * P.H + r;
-          float o[4] = {0.f, 0.f, 0.f, 0.f};
-          if (vec[j]) {
-            const f32x4 ov = xov[j] + v;
-            st_wt_f32x4(xn, ov);
-            for (int e = 0; e < 4; ++e) o[e] = ov[e];
-          } else {
-            for (int e = 0; e < nrows; ++e) { o[e] = xo[e] + v[e]; st_wt_f32(xn + e, o[e]); }
-          }
-          ss = o[0] * o[0] + o[1] * o[1] + o[2] * o[2] + o[3] * o[3];
-          if constexpr (FP8) {
-            if (ver < 2 * P.L)
-              for (int e = 0; e < nrows; ++e) o[e] *= gnv[j][e];
-          }
-          store_xb(a.xb + (size_t)ver * a.xb_elems, token, r, nrows, o, a.MT);
-        }
-        ss += __shfl_xor(ss, 16);
-        ss += __shfl_xor(ss, 32);
-        if (g == 0) st_wt_f32(a.ssq + ((size_t)ver * a.ssq_parts + gtt[j]) * a.Mp + token, ss);
+          v += *reinterpret_cast<const f32x4*>(src + ((((size_t)kg * tiles + gt0 + tl) * MT + mt) * 64 + lane) * 4);
+        epilogue_residual<FP8>(a, ver, tok[j], rr[j], v, xov[j], gnv[j], g);
       }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -721,21 +681,6 @@ __device__ inline void stream_attn_chunks(int n_keys, int max_chunks, int& n_kb,
   if (want > max_chunks) want = max_chunks;
   chunk_len = ((n_kb + want - 1) / want + 3) & ~3;
   n_chunks = (n_kb + chunk_len - 1) / chunk_len;
-}
-
-// Reductions over the four 16-lane rows of a wavefront (the lanes that share a column of a C fragment), with the
-// row-swap instructions of gfx950: two VALU operations per step, no LDS traffic.
-__device__ inline float rows_max(float x) {
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const float m = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ inline float rows_sum(float x) {
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const float m = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 template <int D>
@@ -815,7 +760,6 @@ __device__ inline void stream_attention_phase(const MegaArgs& a, FwdCtx& fc, Fwd
   int lane = lane_in;
   asm volatile("" : "+v"(lane));
   const MegaPlan& P = a.P;
-  const PhaseCtx& pc = fc.pc;
   f32x4* sO = reinterpret_cast<f32x4*>(fc.share);                        // [4][DT][64]
   float* sm = reinterpret_cast<float*>(fc.share + kWavesPerWG * DT * 1024);   // [4][16]
   float* sl = sm + kWavesPerWG * 16;                                     // [4][16]
@@ -823,7 +767,7 @@ __device__ inline void stream_attention_phase(const MegaArgs& a, FwdCtx& fc, Fwd
   float* s_inv = wgt + 64 * 16;                                          // [16]
 
   const int col = lane & 15, g = lane >> 4;
-  const int n = pc.n;
+  const int n = fc.n;
   const int G = P.n_q / P.n_kv;
   const int Mp = a.MT * 16;
   const int n_ct = G * a.MT;                                             // column tiles per kv head
@@ -832,24 +776,24 @@ __device__ inline void stream_attention_phase(const MegaArgs& a, FwdCtx& fc, Fwd
   stream_attn_chunks(n + a.M, a.attn_max_chunks, n_kb, chunk_len, n_chunks);
   const int n_items = n_groups * n_chunks;
   const size_t kv_block = (size_t)32 * D / 8;
-  const u16* Qb = a.Q + (size_t)pc.layer * a.Mp * P.n_q * D;
-  float* pO = a.pO + (size_t)pc.layer * a.pO_layer_floats;
-  float* pm = a.pm + (size_t)pc.layer * a.pml_layer_floats;
-  float* pl = a.pl + (size_t)pc.layer * a.pml_layer_floats;
-  u16* out = a.ap + (size_t)pc.layer * a.ap_elems;
+  const u16* Qb = a.Q + (size_t)fc.layer * a.Mp * P.n_q * D;
+  float* pO = a.pO + (size_t)fc.layer * a.pO_layer_floats;
+  float* pm = a.pm + (size_t)fc.layer * a.pml_layer_floats;
+  float* pl = a.pl + (size_t)fc.layer * a.pml_layer_floats;
+  u16* out = a.ap + (size_t)fc.layer * a.ap_elems;
   const float c = a.scale_log2e;
 
 #define BD_ATS(k)                                                                                     \
   do {                                                                                                \
-    if (a.trace2 != nullptr && pc.layer == 1 && threadIdx.x == 0) a.trace2[(size_t)blockIdx.x * 64 + 48 + (k)] = wall_clock64(); \
+    if (a.trace2 != nullptr && fc.layer == 1 && threadIdx.x == 0) a.trace2[(size_t)blockIdx.x * 64 + 48 + (k)] = wall_clock64(); \
   } while (0)
   BD_ATS(0);
   for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
     const int chunk = item % n_chunks;
     const int grp = item / n_chunks;
     const int ct = grp % n_ct, kvh = grp / n_ct;
-    const bf16x8* Kh = reinterpret_cast<const bf16x8*>(a.Kc + (size_t)pc.layer * a.kv_layer_elems) + (size_t)kvh * a.max_kb * kv_block;
-    const bf16x8* Vh = reinterpret_cast<const bf16x8*>(a.Vc + (size_t)pc.layer * a.kv_layer_elems) + (size_t)kvh * a.max_kb * kv_block;
+    const bf16x8* Kh = reinterpret_cast<const bf16x8*>(a.Kc + (size_t)fc.layer * a.kv_layer_elems) + (size_t)kvh * a.max_kb * kv_block;
+    const bf16x8* Vh = reinterpret_cast<const bf16x8*>(a.Vc + (size_t)fc.layer * a.kv_layer_elems) + (size_t)kvh * a.max_kb * kv_block;
     const int cidx = ct * 16 + col;
     const int hq = cidx / Mp, row = cidx - hq * Mp;
     bf16x8 qf[DS];
@@ -933,12 +877,12 @@ __device__ inline void stream_attention_phase(const MegaArgs& a, FwdCtx& fc, Fwd
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     cbar(sy, lane, a.st);
     if (wave == 0 && lane == 0) {
-      const unsigned old = __hip_atomic_fetch_add(a.cntA + (size_t)pc.layer * n_groups + grp, 1u, __ATOMIC_RELAXED,
+      const unsigned old = __hip_atomic_fetch_add(a.cntA + (size_t)fc.layer * n_groups + grp, 1u, __ATOMIC_RELAXED,
                                                   __HIP_MEMORY_SCOPE_AGENT);
-      fc.pc.s_flags[4] = old == (unsigned)n_chunks - 1u;
+      fc.s_flags[4] = old == (unsigned)n_chunks - 1u;
     }
     cbar(sy, lane, a.st);
-    if (fc.pc.s_flags[4]) {
+    if (fc.s_flags[4]) {
       // last arriver of this (kv head, column tile): merge all chunks in fixed order
       const size_t item0 = (size_t)grp * n_chunks;
       if (wave == 0) {
@@ -1018,7 +962,6 @@ __device__ inline bool stream_attention_local(const MegaArgs& a, FwdCtx& fc, Fwd
   int lane = lane_in;
   asm volatile("" : "+v"(lane));
   const MegaPlan& P = a.P;
-  const PhaseCtx& pc = fc.pc;
   f32x4* sO = reinterpret_cast<f32x4*>(fc.share);                        // [4][DT][64]
   float* sm = reinterpret_cast<float*>(fc.share + kWavesPerWG * DT * 1024);   // [4][16]
   float* sl = sm + kWavesPerWG * 16;                                     // [4][16]
@@ -1026,7 +969,7 @@ __device__ inline bool stream_attention_local(const MegaArgs& a, FwdCtx& fc, Fwd
   float* s_inv = wgt + 64 * 16;                                          // [16]
 
   const int col = lane & 15, g = lane >> 4;
-  const int n = pc.n;
+  const int n = fc.n;
   const int G = P.n_q / P.n_kv;
   const int Mp = a.MT * 16;
   const int n_ct = G * a.MT;                                             // column tiles per kv head
@@ -1035,24 +978,24 @@ __device__ inline bool stream_attention_local(const MegaArgs& a, FwdCtx& fc, Fwd
   const int x = blockIdx.x % a.n_xcd, w = blockIdx.x / a.n_xcd;          // XCD, workgroup inside it
   const int n_kb = (n + a.M + 31) >> 5;
   const size_t kv_block = (size_t)32 * D / 8;
-  const u16* Qb = a.Q + (size_t)pc.layer * a.Mp * P.n_q * D;
-  float* pO = a.pO + (size_t)pc.layer * a.pO_layer_floats;
-  float* pm = a.pm + (size_t)pc.layer * a.pml_layer_floats;
-  float* pl = a.pl + (size_t)pc.layer * a.pml_layer_floats;
-  u16* out = a.ap + (size_t)pc.layer * a.ap_elems;
+  const u16* Qb = a.Q + (size_t)fc.layer * a.Mp * P.n_q * D;
+  float* pO = a.pO + (size_t)fc.layer * a.pO_layer_floats;
+  float* pm = a.pm + (size_t)fc.layer * a.pml_layer_floats;
+  float* pl = a.pl + (size_t)fc.layer * a.pml_layer_floats;
+  u16* out = a.ap + (size_t)fc.layer * a.ap_elems;
   const float c = a.scale_log2e;
 
 #define BD_ATS(k)                                                                                     \
   do {                                                                                                \
-    if (a.trace2 != nullptr && pc.layer == 1 && threadIdx.x == 0) a.trace2[(size_t)blockIdx.x * 64 + 48 + (k)] = wall_clock64(); \
+    if (a.trace2 != nullptr && fc.layer == 1 && threadIdx.x == 0) a.trace2[(size_t)blockIdx.x * 64 + 48 + (k)] = wall_clock64(); \
   } while (0)
   BD_ATS(0);
   {
     const int ctl = w % lp.CT, chunk = w / lp.CT;
     const int ct = x * lp.CT + ctl;                                      // column tile of this workgroup
     const int kvh = ct / n_ct, ctk = ct - kvh * n_ct;
-    const bf16x8* Kh = reinterpret_cast<const bf16x8*>(a.Kc + (size_t)pc.layer * a.kv_layer_elems) + (size_t)kvh * a.max_kb * kv_block;
-    const bf16x8* Vh = reinterpret_cast<const bf16x8*>(a.Vc + (size_t)pc.layer * a.kv_layer_elems) + (size_t)kvh * a.max_kb * kv_block;
+    const bf16x8* Kh = reinterpret_cast<const bf16x8*>(a.Kc + (size_t)fc.layer * a.kv_layer_elems) + (size_t)kvh * a.max_kb * kv_block;
+    const bf16x8* Vh = reinterpret_cast<const bf16x8*>(a.Vc + (size_t)fc.layer * a.kv_layer_elems) + (size_t)kvh * a.max_kb * kv_block;
     const int cidx = ctk * 16 + col;
     const int hq = cidx / Mp, row = cidx - hq * Mp;
     bf16x8 qf[DS];
@@ -1264,19 +1207,24 @@ __device__ inline bool stream_xcd_barrier(const MegaArgs& a, FwdSync& sy, unsign
 }
 
 // ---- the kernel ------------------------------------------------------------------------------------------------
-template <int MT> constexpr int stream_lds_bytes() { return kWavesPerWG * kSlots * 1024 + kShareBytes; }
+template <int MT> constexpr int stream_lds_bytes() { return kWavesPerWG * kRingBytes + kShareBytes; }
 
 template <int MT, int D, bool FP8, bool QUAD = false>
 __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) {
-  static_assert(2 * kWavesPerWG * kT * MT * 1024 <= kShareBytes, "K-reduction buffers exceed the shared region");
+  constexpr int kRound = round_tiles<MT>();
+  static_assert(kWavesPerWG * kRound * MT * 1024 <= kShareBytes, "K-reduction buffers exceed the shared region");
+  static_assert(kRound * MT <= 3 * kWavesPerWG && kWavesPerWG % MT == 0, "at most three epilogue elements per consumer and round");
   static_assert(kWavesPerWG * (D / 16) * 1024 + (8 * 16 + 64 * 16 + 16) * 4 <= kShareBytes, "attention merge buffers exceed the shared region");
   extern __shared__ __attribute__((aligned(16))) char lds[];
   __shared__ unsigned s_sync[SY_WORDS];
   __shared__ int s_flags[16];
   __shared__ float s_part[kWavesPerWG * 64];
+  __shared__ int4 s_plan[PH_LM * kWavesPerWG];
   const MegaPlan& P = a.P;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (threadIdx.x < SY_WORDS) s_sync[threadIdx.x] = 0u;
+  if (threadIdx.x < PH_LM * kWavesPerWG)
+    s_plan[threadIdx.x] = a.wtab[blockIdx.x * kWavesPerWG + threadIdx.x % kWavesPerWG].ph[threadIdx.x / kWavesPerWG];
   if (threadIdx.x == 0) {
     int go = (a.st->error == 0);
     if (go && a.skippable && a.st->skip) {
@@ -1295,27 +1243,25 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
 
   if (wave >= kWavesPerWG) {
     const int cw = wave - kWavesPerWG;
-    if constexpr (kStash > 0) producer_loop_stash<FP8, kStash>(a, cw, lds + cw * kSlots * 1024, sync_base, lane);
-    else producer_loop<FP8>(a, cw, lds + cw * kSlots * 1024, sync_base, lane);
+    producer_loop_stash<kStash>(a, cw, lds + cw * kRingBytes, sync_base, lane);
     return;
   }
 
   FwdSync sy;
   sy.base = sync_base; sy.cbar_target = 0u; sy.arrive_target = 0u; sy.dead = false;
   Ring rg;
-  rg.base = lds + wave * kSlots * 1024;
+  rg.base = lds + wave * kRingBytes;
   rg.landed_addr = sync_base + (SY_LANDED + wave) * 4;
   rg.consumed_addr = sync_base + (SY_CONSUMED + wave) * 4;
   rg.have = 0u; rg.taken = 0u; rg.slot = 0;
   FwdCtx fc;
-  fc.share = lds + kWavesPerWG * kSlots * 1024;
-  fc.pc.n = a.st->n;
-  for (int i = 0; i < 3; ++i) fc.pc.pg[i] = page_of_block(a.kv_pages, min((fc.pc.n >> 5) + i, a.max_kb - 1));
-  fc.pc.xstage = nullptr;
-  fc.pc.red = reinterpret_cast<f32x4*>(fc.share);
-  fc.red2 = fc.pc.red + kWavesPerWG * kT * MT * 64;
-  fc.pc.s_flags = s_flags;
+  fc.share = lds + kWavesPerWG * kRingBytes;
+  fc.n = a.st->n;
+  for (int i = 0; i < 3; ++i) fc.pg[i] = page_of_block(a.kv_pages, min((fc.n >> 5) + i, a.max_kb - 1));
+  fc.red = reinterpret_cast<f32x4*>(fc.share);
+  fc.s_flags = s_flags;
   fc.s_part = s_part;
+  fc.s_plan = s_plan;
   unsigned epoch = a.bar_epoch, xepoch = a.xbar_epoch;
 
   int tsi = 0;
@@ -1327,39 +1273,31 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
   BD_TS2();
   bool alive = true;
   for (int l = 0; l < P.L && alive; ++l) {
-    fc.pc.layer = l;
-    stream_gemm_phase<MT, PH_QKV, D, FP8>(a, fc, rg, sy, wave, lane);
-    BD_TS2();
-    alive = stream_grid_barrier(a, sy, ++epoch, wave, lane);
-    BD_TS2();
-    if (!alive) break;
-    if (a.attn_local) {
-      alive = stream_attention_local<D, QUAD>(a, fc, sy, ++xepoch, wave, lane);
+    fc.layer = l;
+    // the five phases of a layer (QKV, attention, O, gate/up, down), each ended by a barrier: `step` stays a runtime value
+    // so that the phases share one copy of the code
+#pragma unroll 1
+    for (int step = 0; step < 5; ++step) {
+      asm volatile("" : "+s"(step));
+      if (step == 1) {
+        if (a.attn_local) {
+          alive = stream_attention_local<D, QUAD>(a, fc, sy, ++xepoch, wave, lane);
+          if (!alive) break;
+        } else {
+          stream_attention_phase<D, QUAD>(a, fc, sy, wave, lane);
+        }
+      } else {
+        stream_gemm_phase<MT, D, FP8>(a, fc, rg, sy, step == 0 ? (int)PH_QKV : step - 1, wave, lane);
+      }
+      BD_TS2();
+      if (step == 3 && a.local_gu) alive = stream_xcd_barrier(a, sy, ++xepoch, wave, lane);
+      else alive = stream_grid_barrier(a, sy, ++epoch, wave, lane);
+      BD_TS2();
       if (!alive) break;
-    } else {
-      stream_attention_phase<D, QUAD>(a, fc, sy, wave, lane);
     }
-    BD_TS2();
-    alive = stream_grid_barrier(a, sy, ++epoch, wave, lane);
-    BD_TS2();
-    if (!alive) break;
-    stream_gemm_phase<MT, PH_O, D, FP8>(a, fc, rg, sy, wave, lane);
-    BD_TS2();
-    alive = stream_grid_barrier(a, sy, ++epoch, wave, lane);
-    BD_TS2();
-    if (!alive) break;
-    stream_gemm_phase<MT, PH_GU, D, FP8>(a, fc, rg, sy, wave, lane);
-    BD_TS2();
-    if (a.local_gu) alive = stream_xcd_barrier(a, sy, ++xepoch, wave, lane);
-    else alive = stream_grid_barrier(a, sy, ++epoch, wave, lane);
-    BD_TS2();
-    if (!alive) break;
-    stream_gemm_phase<MT, PH_DOWN, D, FP8>(a, fc, rg, sy, wave, lane);
-    BD_TS2();
-    alive = stream_grid_barrier(a, sy, ++epoch, wave, lane);
-    BD_TS2();
   }
   if (!alive && lane == 0) lds_st32(sync_base + SY_DEAD * 4, 1u);   // let the producers go
+  if (sy.dead && lane == 0) __hip_atomic_store(&a.st->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #undef BD_TS2
 }
 
