@@ -8,9 +8,8 @@
 namespace bd {
 namespace {
 
-// Tile shapes per phase (rows per workgroup = 32*WN, k-steps per stage BKS, tokens per workgroup = 32*TW), picked by
-// measurement at 1024 rows: gate/up 128 rows x 128 tokens x 2 k-steps, down and O 64 x 64 x 4, QKV 64 x 64 x 2 (the
-// phases with 2048-2560 output rows need the smaller token tile to put two workgroups on every CU).
+// The register-staged kernel (32*WN rows x 32*TW tokens per workgroup, BKS k-steps per stage): K of any length, and the
+// path of BD_FLAG_PREFILL_STAGED.
 template <int PH, int WN, int BKS, int TW>
 int launch_pf_gemm(hipStream_t s, PfGemmArgs a, int n_rows) {
   static bool attr_set = false;
@@ -27,28 +26,95 @@ int launch_pf_gemm(hipStream_t s, PfGemmArgs a, int n_rows) {
   return check_launch();
 }
 
-template <int PH, int WN, int BKS, int TW, int NST, int OCC>
-int launch_pf_gemm_direct(hipStream_t s, PfGemmArgs a, int n_rows) {
+template <int PH, int WN, int TW, int BKS, int NST>
+int launch_pf_gemm_pipe(hipStream_t s, PfGemmArgs a) {
   static bool attr_set = false;
-  constexpr int lds = pf_gemm_direct_lds<WN, BKS, TW, NST>();
+  constexpr int lds = pf_gemm_pipe_lds<WN, TW, BKS, NST>();
+  static_assert(lds <= 160 * 1024, "LDS of one CU");
   if (!attr_set) {
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_direct_kernel<PH, WN, BKS, TW, NST, OCC>),
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_pipe_kernel<PH, WN, TW, BKS, NST>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     attr_set = true;
   }
-  static_assert(OCC * lds <= 160 * 1024, "workgroups per CU bounded by LDS");
-  if (a.KS % BKS != 0) return BD_E_ARG;
-  a.NT = n_rows / 16;
+  static_assert(BKS <= 2, "turns of two k-steps");
+  if (a.SK < 1 || a.KS % (2 * a.SK) != 0) return BD_E_ARG;        // whole turns of the K loop per split
   a.RG = ceil_div(a.NT, 2 * WN);
   a.TG = ceil_div(a.MTc, 2 * TW);
-  if (a.SK < 1 || (a.KS / BKS) % a.SK != 0) return BD_E_ARG;
   const int grid = ceil_div(a.RG, 8) * 8 * a.TG * a.SK;
-  hipLaunchKernelGGL((pf_gemm_direct_kernel<PH, WN, BKS, TW, NST, OCC>), dim3(grid), dim3(kPfThreads), lds, s, a);
+  hipLaunchKernelGGL((pf_gemm_pipe_kernel<PH, WN, TW, BKS, NST>), dim3(grid), dim3(kPfThreads), lds, s, a);
   return check_launch();
 }
 
+// Tile shapes of the pipelined GEMM: 32*WN rows x 32*TW tokens per workgroup, one workgroup per CU.  A shape's cost is the
+// number of rounds of the chip (32 CUs per XCD; a row group and its K splits stay on one XCD) times the time of one
+// round, measured on the phase's 3B shape (launches back to back, weights from HBM); the cheapest shape is taken.
+struct PfTile { int wn, tw; float us; };
+template <int N>
+int pick_tile(const PfTile (&t)[N], int NT, int MTc, int SK) {
+  int best = 0;
+  float cost = 0.f;
+  for (int i = 0; i < N; ++i) {
+    const int per_xcd = ceil_div(ceil_div(NT, 2 * t[i].wn), 8) * ceil_div(MTc, 2 * t[i].tw) * SK;
+    const float c = (float)ceil_div(per_xcd, 32) * t[i].us;
+    if (i == 0 || c < cost) { best = i; cost = c; }
+  }
+  return best;
+}
+
+int launch_qkv(hipStream_t s, const PfGemmArgs& a) {
+  static constexpr PfTile t[] = {{1, 1, 8.3f}, {1, 2, 9.9f}, {3, 2, 13.8f}, {5, 2, 20.f}, {5, 4, 28.f}};
+  switch (pick_tile(t, a.NT, a.MTc, 1)) {
+    case 0: return launch_pf_gemm_pipe<PH_QKV, 1, 1, 2, 12>(s, a);
+    case 1: return launch_pf_gemm_pipe<PH_QKV, 1, 2, 2, 12>(s, a);
+    case 2: return launch_pf_gemm_pipe<PH_QKV, 3, 2, 2, 6>(s, a);
+    case 3: return launch_pf_gemm_pipe<PH_QKV, 5, 2, 2, 5>(s, a);
+    default: return launch_pf_gemm_pipe<PH_QKV, 5, 4, 2, 4>(s, a);
+  }
+}
+int launch_o(hipStream_t s, const PfGemmArgs& a) {
+  if (a.SK > 1) {
+    static constexpr PfTile t[] = {{1, 2, 5.8f}, {1, 4, 6.5f}, {2, 4, 8.f}};
+    switch (pick_tile(t, a.NT, a.MTc, a.SK)) {
+      case 0: return launch_pf_gemm_pipe<PH_O, 1, 2, 2, 12>(s, a);
+      case 1: return launch_pf_gemm_pipe<PH_O, 1, 4, 2, 7>(s, a);
+      default: return launch_pf_gemm_pipe<PH_O, 2, 4, 2, 6>(s, a);
+    }
+  }
+  static constexpr PfTile t[] = {{4, 1, 12.f}, {4, 2, 16.7f}, {4, 4, 23.f}};
+  switch (pick_tile(t, a.NT, a.MTc, 1)) {
+    case 0: return launch_pf_gemm_pipe<PH_O, 4, 1, 2, 6>(s, a);
+    case 1: return launch_pf_gemm_pipe<PH_O, 4, 2, 2, 6>(s, a);
+    default: return launch_pf_gemm_pipe<PH_O, 4, 4, 2, 4>(s, a);
+  }
+}
+int launch_gu(hipStream_t s, const PfGemmArgs& a) {
+  static constexpr PfTile t[] = {{3, 2, 20.5f}, {3, 3, 22.f}, {3, 4, 24.f}, {6, 4, 31.f}, {6, 6, 39.f}, {11, 4, 49.f}, {11, 6, 62.f}, {11, 8, 81.f}};
+  switch (pick_tile(t, a.NT, a.MTc, 1)) {
+    case 0: return launch_pf_gemm_pipe<PH_GU, 3, 2, 2, 7>(s, a);
+    case 1: return launch_pf_gemm_pipe<PH_GU, 3, 3, 2, 6>(s, a);
+    case 2: return launch_pf_gemm_pipe<PH_GU, 3, 4, 2, 5>(s, a);
+    case 3: return launch_pf_gemm_pipe<PH_GU, 6, 4, 1, 6>(s, a);
+    case 4: return launch_pf_gemm_pipe<PH_GU, 6, 6, 1, 5>(s, a);
+    case 5: return launch_pf_gemm_pipe<PH_GU, 11, 4, 1, 5>(s, a);
+    case 6: return launch_pf_gemm_pipe<PH_GU, 11, 6, 1, 4>(s, a);
+    default: return launch_pf_gemm_pipe<PH_GU, 11, 8, 1, 4>(s, a);
+  }
+}
+int launch_down(hipStream_t s, const PfGemmArgs& a) {
+  static constexpr PfTile t[] = {{1, 2, 12.4f}, {1, 3, 13.9f}, {1, 4, 15.5f}, {4, 2, 19.5f}, {8, 2, 30.f}, {8, 3, 38.5f}, {8, 4, 47.f}};
+  switch (pick_tile(t, a.NT, a.MTc, a.SK)) {
+    case 0: return launch_pf_gemm_pipe<PH_DOWN, 1, 2, 2, 12>(s, a);
+    case 1: return launch_pf_gemm_pipe<PH_DOWN, 1, 3, 2, 9>(s, a);
+    case 2: return launch_pf_gemm_pipe<PH_DOWN, 1, 4, 2, 7>(s, a);
+    case 3: return launch_pf_gemm_pipe<PH_DOWN, 4, 2, 2, 6>(s, a);
+    case 4: return launch_pf_gemm_pipe<PH_DOWN, 8, 2, 1, 6>(s, a);
+    case 5: return launch_pf_gemm_pipe<PH_DOWN, 8, 3, 1, 6>(s, a);
+    default: return launch_pf_gemm_pipe<PH_DOWN, 8, 4, 1, 5>(s, a);
+  }
+}
+
 // K splits (at most kPfSplit) that divide n_it pipeline iterations evenly.
-int skinny_split(int n_it) {
+int k_split(int n_it) {
   for (int sk = kPfSplit; sk > 1; --sk)
     if (n_it % sk == 0) return sk;
   return 1;
@@ -78,10 +144,7 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
   }
   hipLaunchKernelGGL(rope_table_kernel, dim3(mc), dim3(64), 0, s, c.rope, c.st, c.D / 2, c.rope_theta, c.quad_W);
   BD_TRY(check_launch());
-  // Up to 128 rows: the products are bound by how fast the weights arrive, not by the matrix cores.  Tiles of 32 rows x
-  // 64 tokens put 2.5 to 8 times as many workgroups on the chip as the tiles above, each with a deep direct-to-LDS
-  // pipeline (84 to 132 KiB in flight per CU), and the two projections with few output rows split K over workgroups.
-  // (65 to 128 rows: two token groups per row group, the second of which finds the weights in its XCD's L2.)
+  // Up to 128 rows: one workgroup per row in the norm, and (up to 64) the keys dealt to workgroups in the attention.
   const bool skinny = MTc <= 8 && !c.staged;
   PfGemmArgs g{};
   g.MTc = MTc; g.Mvalid = rows; g.rs = c.rs; g.rope = c.rope; g.x = c.x; g.q = c.q; g.max_kb = c.max_kb; g.n0 = c.n0;
@@ -105,9 +168,9 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
     g.w = reinterpret_cast<const bf16x8*>(wl + c.w_off[0]); g.KS = ceil_div(c.H, 32);
     g.xin = reinterpret_cast<const bf16x8*>(c.xb);
     g.wscale = ws ? ws + c.wscale_off[0] : nullptr;
-    // (every phase: the direct-to-LDS kernel when K is a whole number of stages, else the register-staged one)
-    if (skinny && g.KS % 4 == 0) BD_TRY((launch_pf_gemm_direct<PH_QKV, 1, 4, 2, 6, 1>(s, g, c.NQKV)));
-    else if (!c.staged && g.KS % 2 == 0) BD_TRY((launch_pf_gemm_direct<PH_QKV, 2, 2, 2, 2, 4>(s, g, c.NQKV)));
+    // (every phase: the pipelined kernel when K is a whole number of its turns, else the register-staged one)
+    g.NT = c.NQKV / 16;
+    if (!c.staged && g.KS % 2 == 0) BD_TRY(launch_qkv(s, g));
     else BD_TRY((launch_pf_gemm<PH_QKV, 2, 2, 2>(s, g, c.NQKV)));
     {
       PfAttnArgs t{};
@@ -139,15 +202,16 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
     g.w = reinterpret_cast<const bf16x8*>(wl + c.w_off[1]); g.KS = ceil_div(c.QD, 32);
     g.xin = reinterpret_cast<const bf16x8*>(c.ap);
     g.wscale = ws ? ws + c.wscale_off[1] : nullptr;
+    g.NT = c.H / 16;
     int o_parts = 0;
-    if (skinny && g.KS % 2 == 0) {
-      // K split over workgroups like the down projection below; the norm that follows adds the splits
-      g.SK = skinny_split(g.KS / 2); g.part = g.SK > 1 ? c.part : nullptr;
-      BD_TRY((launch_pf_gemm_direct<PH_O, 1, 2, 2, 12, 1>(s, g, c.H)));
+    if (!c.staged && g.KS % 2 == 0) {
+      // up to 256 rows K is split over workgroups like in the down projection below, and the norm that follows adds the
+      // splits (beyond, the norm would lose what the product gains)
+      g.SK = MTc <= 16 ? k_split(g.KS / 2) : 1;
+      g.part = g.SK > 1 ? c.part : nullptr;
+      BD_TRY(launch_o(s, g));
       o_parts = g.SK > 1 ? g.SK : 0;
       g.SK = 1; g.part = nullptr;
-    } else if (!c.staged && g.KS % 4 == 0) {
-      BD_TRY((launch_pf_gemm_direct<PH_O, 2, 4, 2, 2, 2>(s, g, c.H)));
     } else {
       BD_TRY((launch_pf_gemm<PH_O, 2, 4, 2>(s, g, c.H)));
     }
@@ -155,25 +219,19 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
     g.w = reinterpret_cast<const bf16x8*>(wl + c.w_off[2]); g.KS = ceil_div(c.H, 32);
     g.xin = reinterpret_cast<const bf16x8*>(c.xb);
     g.wscale = ws ? ws + c.wscale_off[2] : nullptr;
-    // gate/up: 256 rows x 128 tokens per workgroup (a 128 x 64 tile per wavefront), one k-step per stage: 97 us for the
-    // 3B shape against 110 us with 128 x 128 tiles and 136 us with the register-staged kernel
-    if (skinny && g.KS % 2 == 0) BD_TRY((launch_pf_gemm_direct<PH_GU, 3, 2, 2, 7, 1>(s, g, 2 * c.F)));
-    else if (!c.staged) BD_TRY((launch_pf_gemm_direct<PH_GU, 8, 1, 4, 2, 2>(s, g, 2 * c.F)));
+    g.NT = 2 * c.F / 16;
+    if (!c.staged && g.KS % 2 == 0) BD_TRY(launch_gu(s, g));
     else BD_TRY((launch_pf_gemm<PH_GU, 4, 2, 4>(s, g, 2 * c.F)));
     g.w = reinterpret_cast<const bf16x8*>(wl + c.w_off[3]); g.KS = ceil_div(c.F, 32);
     g.xin = reinterpret_cast<const bf16x8*>(c.act);
     g.wscale = ws ? ws + c.wscale_off[3] : nullptr;
-    // down: K split four ways over workgroups with 128 x 128 tiles when K divides; the next norm adds the splits
-    if (skinny && g.KS % 2 == 0) {
-      g.SK = skinny_split(g.KS / 2); g.part = g.SK > 1 ? c.part : nullptr;
-      BD_TRY((launch_pf_gemm_direct<PH_DOWN, 1, 2, 2, 12, 1>(s, g, c.H)));
+    g.NT = c.H / 16;
+    // down: K split over workgroups (2048 output rows are too few tiles for the chip); the next norm adds the splits
+    if (!c.staged && g.KS % 2 == 0) {
+      g.SK = k_split(g.KS / 2); g.part = g.SK > 1 ? c.part : nullptr;
+      BD_TRY(launch_down(s, g));
       parts = g.SK > 1 ? g.SK : 0;
       g.SK = 1; g.part = nullptr;
-    } else if (!c.staged && g.KS % (2 * kPfSplit) == 0) {
-      g.SK = kPfSplit; g.part = c.part;
-      BD_TRY((launch_pf_gemm_direct<PH_DOWN, 4, 2, 4, 2, 2>(s, g, c.H)));
-      g.SK = 1; g.part = nullptr;
-      parts = kPfSplit;
     } else {
       BD_TRY((launch_pf_gemm<PH_DOWN, 2, 4, 2>(s, g, c.H)));
     }

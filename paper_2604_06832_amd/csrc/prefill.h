@@ -12,74 +12,130 @@
 // ((T*KS + ks)*64 + lane) 16-byte units, rows in the decode path's phase-row order (rotary pairs of q/k adjacent,
 // (gate f, up f) adjacent, norm gains folded into the columns).  Activations: the packed order of xp_index().
 #pragma once
+#include <type_traits>
+
 #include "prefill_args.h"
 #include "prefill_attn.h"
 #include "stream_fwd.h"
 
 namespace bd {
 
+// Epilogue operands of a workgroup tile, read from LDS (their own counter): a load behind a store waits for that store's
+// acknowledgement, because vector memory operations are counted in order, and with the row scales and token factors loaded
+// tile by tile between the stores the gate/up epilogue of a 352 x 256 tile took about 40 us, as long as its products.
+// [AT * 16] scales of the rows (e4m3 weights), then [BT * 16] token factors 1/rms (QKV, gate/up).
+template <int AT, int BT> constexpr int pf_ep_bytes() { return (AT + BT) * 16 * 4; }
+template <int PH, int AT, int BT>
+__device__ inline void pf_ep_fetch(const PfGemmArgs& a, float* ep, int T0, int mt0) {
+  constexpr bool kNorm = PH == PH_QKV || PH == PH_GU;
+  for (int i = threadIdx.x; i < AT * 16; i += kPfThreads) ep[i] = a.wscale != nullptr ? a.wscale[min(T0 * 16 + i, a.NT * 16 - 1)] : 1.f;
+  if constexpr (kNorm)
+    for (int i = threadIdx.x; i < BT * 16; i += kPfThreads) ep[AT * 16 + i] = a.rs[min(mt0 * 16 + i, a.MTc * 16 - 1)];
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // (published by the first barrier of the K loop)
+}
+
+__device__ inline uint32_t pack_bf16(float lo, float hi) {
+  return (uint32_t)f32_to_bf16_bits(lo) | ((uint32_t)f32_to_bf16_bits(hi) << 16);
+}
+
 // Epilogue of both GEMM kernels: lane (token column col, row quad g) of a 16 x 16 accumulator tile holds rows
-// r .. r+3 of one token.
+// r .. r+3 of one token.  The loads that remain (rotary factors, old residual values) precede the stores they go with.
 template <int PH, int WN, int TW>
-__device__ inline void pf_epilogue(const PfGemmArgs& a, const f32x4 (&acc)[WN][TW], int T0, int mt0, int wn, int wm, int lane,
+__device__ inline void pf_epilogue(const PfGemmArgs& a, f32x4 (&acc)[WN][TW], const float* ep, int T0, int mt0, int wn, int wm, int lane,
                                    int kz = 0) {
   const int col = lane & 15, g = lane >> 4;
-#pragma unroll
-  for (int i = 0; i < WN; ++i) {
-    const int T = T0 + wn * WN + i;
-    if (T >= a.NT) continue;
-    const int r = T * 16 + 4 * g;
+  const int Tw = T0 + wn * WN, mtw = mt0 + wm * TW;            // this wavefront's first row tile, first token tile
+  const float* ep_rs = ep + 2 * WN * 16 + wm * TW * 16 + col;
+  auto scale = [&](int i) { return *reinterpret_cast<const f32x4*>(ep + (wn * WN + i) * 16 + 4 * g); };   // of rows r .. r+3 of tile i
+  if constexpr (PH == PH_QKV) {
+    const int D = a.D, half = D >> 1;
+    int key[TW];
+    f32x4 cs[WN][TW];                                          // (cos, sin) of the two rotary pairs
 #pragma unroll
     for (int j = 0; j < TW; ++j) {
-      if (mt0 + wm * TW + j >= a.MTc) continue;
-      const int token = (mt0 + wm * TW + j) * 16 + col;
-      f32x4 v = acc[i][j];
-      if (a.wscale != nullptr) v *= *reinterpret_cast<const f32x4*>(a.wscale + r);
-      if constexpr (PH == PH_QKV) {
+      const int tok = min((mtw + j) * 16 + col, a.Mvalid - 1);
+      key[j] = paged_key(a.pages, a.n0 + tok);
+#pragma unroll
+      for (int i = 0; i < WN; ++i)
+        cs[i][j] = *reinterpret_cast<const f32x4*>(a.rope + (size_t)tok * half + ((((Tw + i) * 16 + 4 * g) % D) >> 1));
+    }
+#pragma unroll
+    for (int j = 0; j < TW; ++j) {
+      asm volatile("" ::"v"(key[j]));
+#pragma unroll
+      for (int i = 0; i < WN; ++i) asm volatile("" ::"v"(cs[i][j]));
+    }
+#pragma unroll
+    for (int i = 0; i < WN; ++i) {
+      const int r = (Tw + i) * 16 + 4 * g;
+      if (Tw + i >= a.NT) continue;
+#pragma unroll
+      for (int j = 0; j < TW; ++j) {
+        const int token = (mtw + j) * 16 + col;
         if (token >= a.Mvalid) continue;
-        const int D = a.D, half = D >> 1;
-        v *= a.rs[token];
-        const int key = paged_key(a.pages, a.n0 + token);
-#pragma unroll
-        for (int pr = 0; pr < 2; ++pr) {
-          const int rp = r + 2 * pr;
-          if (rp < a.QD + a.KVD) {
-            // rotary pair: phase rows (2i, 2i+1) of a head hold dims (i, i + D/2)
-            const int dp = rp % D;
-            const float2 cs = a.rope[(size_t)token * half + (dp >> 1)];
-            const float lo = v[2 * pr] * cs.x - v[2 * pr + 1] * cs.y;
-            const float hi = v[2 * pr + 1] * cs.x + v[2 * pr] * cs.y;
-            const uint32_t pk = (uint32_t)f32_to_bf16_bits(lo) | ((uint32_t)f32_to_bf16_bits(hi) << 16);
-            u16* dst;
-            if (rp < a.QD) {
-              dst = a.q + ((size_t)token * a.n_q + rp / D) * D + dp;
-            } else {
-              const int rk = rp - a.QD;
-              dst = a.Kc + (size_t)(rk / D) * a.max_kb * 32 * D + kp_index(key, dp, D / 32);
-            }
-            *reinterpret_cast<uint32_t*>(dst) = pk;
+        const f32x4 v = acc[i][j] * scale(i) * ep_rs[j * 16], c = cs[i][j];
+        if (r < a.QD + a.KVD) {
+          // rotary pairs: phase rows (2i, 2i+1) of a head hold dims (i, i + D/2)
+          const uint32_t p0 = pack_bf16(v[0] * c[0] - v[1] * c[1], v[1] * c[0] + v[0] * c[1]);
+          const uint32_t p1 = pack_bf16(v[2] * c[2] - v[3] * c[3], v[3] * c[2] + v[2] * c[3]);
+          u16* dst;
+          if (r < a.QD) {
+            dst = a.q + (size_t)token * a.n_q * D + r;
           } else {
-            const int rv = rp - a.QD - a.KVD;
-            u16* vc = a.Vc + (size_t)(rv / D) * a.max_kb * 32 * D;
-            vc[vp_index(key, rv % D, D / 16)] = f32_to_bf16_bits(v[2 * pr]);
-            vc[vp_index(key, (rv + 1) % D, D / 16)] = f32_to_bf16_bits(v[2 * pr + 1]);
+            const int rk = r - a.QD;
+            dst = a.Kc + (size_t)(rk / D) * a.max_kb * 32 * D + kp_index(key[j], rk % D, D / 32);
           }
-        }
-      } else if constexpr (PH == PH_O || PH == PH_DOWN) {
-        if (a.part != nullptr) {
-          *reinterpret_cast<f32x4*>(a.part + ((size_t)kz * a.MTc * 16 + token) * a.H + r) = v;
+          *reinterpret_cast<uint64_t*>(dst) = (uint64_t)p0 | ((uint64_t)p1 << 32);
         } else {
-          f32x4* xp = reinterpret_cast<f32x4*>(a.x + (size_t)token * a.H + r);
-          *xp = *xp + v;
-        }
-      } else {
-        v *= a.rs[token];
+          const int rv = r - a.QD - a.KVD;
+          u16* vc = a.Vc + (size_t)(rv / D) * a.max_kb * 32 * D + vp_index(key[j], rv % D, D / 16);
 #pragma unroll
-        for (int pr = 0; pr < 2; ++pr) {
-          const float gt = v[2 * pr], up = v[2 * pr + 1];
-          a.act[xp_index(token, (r >> 1) + pr, a.MTc)] = f32_to_bf16_bits(gt / (1.f + __expf(-gt)) * up);
+          for (int e = 0; e < 4; ++e) vc[e * 8] = f32_to_bf16_bits(v[e]);    // (four consecutive dims of one 16-dim tile)
         }
       }
+    }
+  } else if constexpr (PH == PH_GU) {
+    float rs[TW];
+#pragma unroll
+    for (int j = 0; j < TW; ++j) rs[j] = ep_rs[j * 16];
+    // No branches between the tiles: a branch per tile keeps the chains (exponential, division) of different tiles from
+    // overlapping.  Tiles past the end store beyond the buffer's range, which drops them.
+    const rsrc_t ar = make_rsrc(a.act, (unsigned)((a.NT * 8 + 31) / 32 * a.MTc * 1024));
+#pragma unroll
+    for (int i = 0; i < WN; ++i) {
+      const f32x4 ws = scale(i);
+      // rows (2f, 2f+1) = (gate f, up f): a tile's eight features are one 16-byte unit per token, a quarter of it in this lane
+      const int off = (((Tw + i) >> 2) * a.MTc + mtw) * 1024 + ((((Tw + i) & 3) * 16 + col) << 4) + 4 * g;
+#pragma unroll
+      for (int j = 0; j < TW; ++j) {
+        const f32x4 v = acc[i][j] * ws * rs[j];
+        const uint32_t h = pack_bf16(v[0] / (1.f + __expf(-v[0])) * v[1], v[2] / (1.f + __expf(-v[2])) * v[3]);
+        __builtin_amdgcn_raw_buffer_store_b32(h, ar, Tw + i < a.NT && mtw + j < a.MTc ? off + j * 1024 : kOob, 0, 0);
+      }
+    }
+  } else if (a.part != nullptr) {
+#pragma unroll
+    for (int i = 0; i < WN; ++i) {
+      if (Tw + i >= a.NT) continue;
+#pragma unroll
+      for (int j = 0; j < TW; ++j) {
+        if (mtw + j >= a.MTc) continue;
+        *reinterpret_cast<f32x4*>(a.part + ((size_t)kz * a.MTc * 16 + (mtw + j) * 16 + col) * a.H + (Tw + i) * 16 + 4 * g) = acc[i][j] * scale(i);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < TW; ++j) {
+      if (mtw + j >= a.MTc) continue;
+      float* xp = a.x + (size_t)((mtw + j) * 16 + col) * a.H;
+      f32x4 xo[WN];
+#pragma unroll
+      for (int i = 0; i < WN; ++i) xo[i] = *reinterpret_cast<const f32x4*>(xp + min((Tw + i) * 16, a.NT * 16 - 16) + 4 * g);
+#pragma unroll
+      for (int i = 0; i < WN; ++i) asm volatile("" ::"v"(xo[i]));
+#pragma unroll
+      for (int i = 0; i < WN; ++i)
+        if (Tw + i < a.NT) *reinterpret_cast<f32x4*>(xp + (Tw + i) * 16 + 4 * g) = xo[i] + acc[i][j] * scale(i);
     }
   }
 }
@@ -90,7 +146,7 @@ __device__ inline void pf_epilogue(const PfGemmArgs& a, const f32x4 (&acc)[WN][T
 // being issued before the MFMAs of stage i.  (A second register set, two stages ahead, costs more in registers than
 // it hides in latency: measured slower for every shape here.)
 template <int PH, int WN, int BKS, int TW>
-__global__ __launch_bounds__(kPfThreads, (2 * (2 * WN * BKS * 64 + 2 * TW * BKS * 64) * 16 <= 80 * 1024) ? 2 : 1) void pf_gemm_kernel(PfGemmArgs a) {
+__global__ __launch_bounds__(kPfThreads, (2 * (2 * WN * BKS * 64 + 2 * TW * BKS * 64) * 16 <= 72 * 1024) ? 2 : 1) void pf_gemm_kernel(PfGemmArgs a) {
   constexpr int AT = 2 * WN;                                        // row tiles per workgroup
   constexpr int BT = 2 * TW;                                        // token tiles per workgroup
   constexpr int A_UNITS = AT * BKS * 64, B_UNITS = BT * BKS * 64;   // 16-byte units per stage
@@ -167,6 +223,8 @@ __global__ __launch_bounds__(kPfThreads, (2 * (2 * WN * BKS * 64 + 2 * TW * BKS 
   };
 
   const int n_it = (a.KS + BKS - 1) / BKS;
+  float* ep = reinterpret_cast<float*>(lds + 2 * STAGE * 16);
+  pf_ep_fetch<PH, AT, BT>(a, ep, T0, mt0);
   Regs R0;
   gload(R0, 0);
   lstore(R0, 0);
@@ -178,57 +236,92 @@ __global__ __launch_bounds__(kPfThreads, (2 * (2 * WN * BKS * 64 + 2 * TW * BKS 
     __syncthreads();
   }
 
-  pf_epilogue<PH, WN, TW>(a, acc, T0, mt0, wn, wm, lane);
+  pf_epilogue<PH, WN, TW>(a, acc, ep, T0, mt0, wn, wm, lane);
 }
 
-// The same product with the operands loaded straight into LDS (no registers in between) through NST stages: the loads
-// of iteration i + NST - 1 are issued, one 1-KiB fragment per instruction and wavefront, before the MFMAs of
-// iteration i, and one barrier per iteration both publishes the stage that has landed and frees the one just read.
-// (Measured on the gate/up shape: two stages with two workgroups per CU beat deeper pipelines with one.)  Needs KS to
-// be a multiple of BKS (no K tail); tiles past the end of the rows or tokens re-read the last valid tile and are
-// dropped by the epilogue.  With SK > 1 the workgroups of an output tile split K among them and each leaves its
-// product in its own slice of `part` (O and down phases: a 128 x 128 tile then fetches half the operand bytes per
-// MFMA of the 64 x 64 tile that the same number of workgroups would otherwise need).
-template <int PH, int WN, int BKS, int TW, int NST, int OCC>
-__global__ __launch_bounds__(kPfThreads, OCC) void pf_gemm_direct_kernel(PfGemmArgs a) {
+// ---- the same product, pipelined: every phase whose K is a whole number of turns of its loop -----------------------------
+// Products and accumulators are named in inline assembly so that the sums are updated in place: from the builtin the compiler
+// makes the form with separate source and destination registers, and copies or spills accumulators at the ends of the loop.
+// The first 64 tiles of a wavefront sit in accumulation registers, the rest in vector registers.
+template <bool ACC>
+__device__ inline void mfma_in_place(f32x4& c, const bf16x8& a, const bf16x8& b) {
+  if constexpr (ACC) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+template <bool ACC>
+__device__ inline void pin_acc(f32x4& c) {
+  if constexpr (ACC) asm volatile("" : "+a"(c));
+  else asm volatile("" : "+v"(c));
+}
+// f(integral constant i) for i = 0 .. N-1, unrolled by construction
+template <int N, int I = 0, typename F>
+__device__ inline void unrolled(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    unrolled<N, I + 1>(f);
+  }
+}
+
+// One workgroup per CU with a tile as large as its registers allow (a wavefront owns up to 512 of them), NST stages of BKS
+// k-steps in LDS filled by direct loads, and the LDS reads of the next k-step issued between the products of the current one:
+// the fragment of row tile i is read again as soon as the products of row i are issued, those of the tokens go into a
+// second register set.  So neither LDS nor barrier is waited for while the matrix cores have work: the K loop of the
+// 352 x 256 tile takes 0.94 us per k-step (1.54 PFLOP/s over the chip on random data, 2.1 with zeros in LDS and no loads:
+// the clock follows the power), and more stages in flight change nothing.  What is left on top is fixed: launch, first loads and epilogue
+// take 18.6 us (gate/up, 352 x 256), 11.9 (down, 256 x 128 x four K splits), 7.9 (QKV, 160 x 64), 6.0 (O, 128 x 64).  Measured on
+// the 3B shape (launches back to back) against kernels without the overlap of LDS reads and products (1024 rows: two stages, two
+// to four workgroups per CU; 72 rows: two token groups of 64): 1024 rows gate/up 82 us / 98, down 47 / 52, QKV 19.9 / 22.9,
+// O 16.8 / 16.7; 72 rows gate/up 21.7 / 33.4, down 14.0 / 25.1, QKV 9.8 / 10.2, O 6.3 / 9.0.
+// Needs whole turns of the loop per K split (no K tail).  With SK > 1 the workgroups of an output tile split K among them and
+// each leaves its product in its own slice of `part` (O and down phases), which the norm that follows adds.
+template <int PH, int WN, int TW, int BKS, int NST>
+__global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs a) {
   constexpr int AT = 2 * WN, BT = 2 * TW;
-  constexpr int AF = AT * BKS, BF = BT * BKS;                       // fragments per stage
-  constexpr int PER = (AF + BF) / 4;                                // loads per wavefront and stage
-  static_assert(AF % 4 == 0 && BF % 4 == 0, "fragments are dealt to four wavefronts");
+  constexpr int AF = AT * BKS, TF = AF + BT * BKS;                  // weight fragments, all fragments of a stage
+  constexpr int PER = (TF + 3) / 4;                                 // loads per wavefront and stage
+  constexpr int U = BKS > 2 ? BKS : 2;                              // k-steps per turn of the loop
+  static_assert(U % BKS == 0 && U % 2 == 0 && NST >= 3, "");
   static_assert((NST - 2) * PER <= 63, "outstanding loads must fit the counter");
   extern __shared__ __attribute__((aligned(16))) char lds[];
   if (a.skippable && a.st->skip) return;
-  const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
-  const int per = a.TG * a.SK;                                      // workgroups of a row group: token groups x K splits
-  const int rg = (slot / per) * 8 + xcd, tg = (slot % per) / a.SK, kz = slot % a.SK;
+  const int xcd = blockIdx.x % 8, slot0 = blockIdx.x / 8;
+  const int per = a.TG * a.SK;
+  const int rg = (slot0 / per) * 8 + xcd, tg = (slot0 % per) / a.SK, kz = slot0 % a.SK;
   if (rg >= a.RG) return;
   const int T0 = rg * AT, mt0 = tg * BT;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wn = wave >> 1, wm = wave & 1;
   const rsrc_t wr = make_rsrc(a.w, (unsigned)((size_t)a.NT * a.KS * 1024));
   const rsrc_t xr = make_rsrc(a.xin, (unsigned)((size_t)a.KS * a.MTc * 1024));
+  const int n_it = a.KS / BKS / a.SK, it0 = kz * n_it;
+  // Row groups that run at the same time start a few k-steps apart: their weight tiles lie a multiple of 4 KiB apart (the
+  // same few channels of the L2 for the same k-step), while the activations they share stay in the L2 between them.
+  const int rot = (rg >> 3) % 4 % n_it;
 
-  const int n_it = a.KS / BKS / a.SK, it0 = kz * n_it;             // this workgroup's share of K
-  // Every row group walks its K range from another starting point (fixed by its number: same sums on every run), so that
-  // the workgroups running at the same time do not all ask the same L2 channels for the same activation fragment.
-  const int rot = (rg * 5) % n_it;
-  auto issue = [&](int it) {
-    char* base = lds + (it % NST) * ((AF + BF) * 1024);
-    int itr = it + rot;
-    if (itr >= n_it) itr -= n_it;
-    const int ks0 = (it0 + itr) * BKS;
+  // Fragment f of a stage: weights (k-step f / AT, row tile f mod AT), then activations (k-step, token tile).  Tiles past
+  // the end re-read the last valid one and are dropped by the epilogue; with a fragment count that does not divide by
+  // four the last one is loaded more than once (the same bytes to the same place).
+  unsigned fo[PER];                                                 // byte offset of this wavefront's fragments at k-step 0
 #pragma unroll
-    for (int i = 0; i < AF / 4; ++i) {
-      const int f = i * 4 + wave, tile = f / BKS, ksl = f % BKS;
-      const int off = ((min(T0 + tile, a.NT - 1) * a.KS) + ks0 + ksl) * 1024 + lane * 16;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_void_t*)(base + f * 1024), 16, off, 0, 0, 0);
-    }
+  for (int i = 0; i < PER; ++i) {
+    const int f = min(i * 4 + wave, TF - 1);
+    if (f < AF) fo[i] = ((unsigned)min(T0 + f % AT, a.NT - 1) * a.KS + f / AT) * 1024u;
+    else fo[i] = ((unsigned)((f - AF) / BT) * a.MTc + min(mt0 + (f - AF) % BT, a.MTc - 1)) * 1024u;
+  }
+  int s_issue = 0, itr = rot;                                       // slot and (rotated) iteration of the next stage to issue
+  auto issue = [&]() {
+    char* base = lds + s_issue * (TF * 1024);
+    const unsigned ka = (unsigned)(it0 + itr) * (BKS * 1024u), kb = ka * (unsigned)a.MTc;
 #pragma unroll
-    for (int i = 0; i < BF / 4; ++i) {
-      const int f = i * 4 + wave, ksl = f / BT, tile = f % BT;
-      const int off = ((ks0 + ksl) * a.MTc + min(mt0 + tile, a.MTc - 1)) * 1024 + lane * 16;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void_t*)(base + (AF + f) * 1024), 16, off, 0, 0, 0);
+    for (int i = 0; i < PER; ++i) {
+      const int f = min(i * 4 + wave, TF - 1);
+      if (i * 4 + 3 < AF || (i * 4 < AF && f < AF))
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_void_t*)(base + f * 1024), 16, lane * 16, (int)(fo[i] + ka), 0, 0);
+      else
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void_t*)(base + f * 1024), 16, lane * 16, (int)(fo[i] + kb), 0, 0);
     }
+    s_issue = s_issue + 1 == NST ? 0 : s_issue + 1;
+    itr = itr + 1 == n_it ? 0 : itr + 1;
   };
 
   f32x4 acc[WN][TW];
@@ -236,41 +329,59 @@ __global__ __launch_bounds__(kPfThreads, OCC) void pf_gemm_direct_kernel(PfGemmA
   for (int i = 0; i < WN; ++i)
 #pragma unroll
     for (int j = 0; j < TW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](int stage) {
-    const bf16x8* A = reinterpret_cast<const bf16x8*>(lds + stage * ((AF + BF) * 1024));
-    const bf16x8* Bm = A + AF * 64;
+  unrolled<WN>([&](auto i) { unrolled<TW>([&](auto j) { pin_acc<(i * TW + j < 64)>(acc[i][j]); }); });
+  bf16x8 af[WN], bf[2][TW];
+  const char* fa = lds + (wn * WN) * 1024 + lane * 16;              // this wavefront's first row / token fragment of slot 0
+  const char* fb = lds + (AF + wm * TW) * 1024 + lane * 16;
+
+  float* ep = reinterpret_cast<float*>(lds + NST * TF * 1024);
+  pf_ep_fetch<PH, AT, BT>(a, ep, T0, mt0);
+  for (int it = 0; it < NST - 1 && it < n_it; ++it) issue();
+  if (n_it >= NST - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 2) * PER) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
 #pragma unroll
-    for (int ksl = 0; ksl < BKS; ++ksl) {
-      bf16x8 af[WN], bfr[TW];
+  for (int i = 0; i < WN; ++i) af[i] = *reinterpret_cast<const bf16x8*>(fa + i * 1024);
 #pragma unroll
-      for (int i = 0; i < WN; ++i) af[i] = A[((wn * WN + i) * BKS + ksl) * 64 + lane];
+  for (int j = 0; j < TW; ++j) bf[0][j] = *reinterpret_cast<const bf16x8*>(fb + j * 1024);
+
+  int it = 0, s_read = 0;                                           // stage of the current k-step, slot of the next one
+  const int ksteps = n_it * BKS;
+  for (int k = 0; k < ksteps; k += U) {
 #pragma unroll
-      for (int j = 0; j < TW; ++j) bfr[j] = Bm[(ksl * BT + wm * TW + j) * 64 + lane];
+    for (int u = 0; u < U; ++u) {
+      const int ksn = (u + 1) % BKS;                                // the next k-step inside its stage
+      if (ksn == 0) {
+        // the next k-step opens stage it + 1: its loads are this wavefront's oldest, NST - 3 later stages may stay in flight
+        if (it + NST - 1 <= n_it) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 3) * PER) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        // (a bare barrier: __syncthreads() is also a fence, which waits for every load in flight and so would empty the
+        // pipeline; what a wavefront read from slot it - 1 it has waited for before the products that used it)
+        __builtin_amdgcn_s_barrier();
+        if (it + NST - 1 < n_it) issue();
+        ++it;
+        s_read = s_read + 1 == NST ? 0 : s_read + 1;
+      }
+      const char* na = fa + s_read * (TF * 1024) + ksn * (AT * 1024);   // (behind the last k-step: read and not used)
+      const char* nb = fb + s_read * (TF * 1024) + ksn * (BT * 1024);
+      __builtin_amdgcn_sched_barrier(0);
+      unrolled<WN>([&](auto i) {
 #pragma unroll
-      for (int i = 0; i < WN; ++i)
-#pragma unroll
-        for (int j = 0; j < TW; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < TW; ++j)
+          if (j * WN / TW == i) bf[(u + 1) & 1][j] = *reinterpret_cast<const bf16x8*>(nb + j * 1024);
+        unrolled<TW>([&](auto j) { mfma_in_place<(i * TW + j < 64)>(acc[i][j], af[i], bf[u & 1][j]); });
+        af[i] = *reinterpret_cast<const bf16x8*>(na + i * 1024);
+        __builtin_amdgcn_sched_barrier(0);
+      });
     }
-  };
-
-  for (int it = 0; it < NST - 1 && it < n_it; ++it) issue(it);
-  for (int it = 0; it < n_it; ++it) {
-    // the loads of iteration `it` are this wavefront's oldest: in the steady state NST - 2 later stages may stay in flight
-    if (it + NST - 2 < n_it) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 2) * PER) : "memory");
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    // (the bare barrier: __syncthreads() is also a fence, which waits for every load in flight and so would empty
-    // the pipeline at every iteration; the waits that matter are the explicit one above and the LDS reads of the last
-    // iteration, which the MFMAs that used them have already waited for)
-    __builtin_amdgcn_s_barrier();
-    if (it + NST - 1 < n_it) issue(it + NST - 1);
-    compute(it % NST);
   }
-  pf_epilogue<PH, WN, TW>(a, acc, T0, mt0, wn, wm, lane, kz);
+  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  unrolled<WN>([&](auto i) { unrolled<TW>([&](auto j) { pin_acc<(i * TW + j < 64)>(acc[i][j]); }); });
+  pf_epilogue<PH, WN, TW>(a, acc, ep, T0, mt0, wn, wm, lane, kz);
 }
+template <int WN, int TW, int BKS, int NST> constexpr int pf_gemm_pipe_lds() { return NST * (2 * WN + 2 * TW) * BKS * 1024 + pf_ep_bytes<2 * WN, 2 * TW>(); }
 
-template <int WN, int BKS, int TW, int NST> constexpr int pf_gemm_direct_lds() { return NST * (2 * WN * BKS + 2 * TW * BKS) * 1024; }
-
-template <int WN, int BKS, int TW> constexpr int pf_gemm_lds() { return 2 * (2 * WN * BKS * 64 + 2 * TW * BKS * 64) * 16; }
+template <int WN, int BKS, int TW> constexpr int pf_gemm_lds() { return 2 * (2 * WN * BKS * 64 + 2 * TW * BKS * 64) * 16 + pf_ep_bytes<2 * WN, 2 * TW>(); }
 
 // ---- block assembly: embedding gather into the fp32 residual stream ---------------------------------
 // Row r takes embeds[off + r] while off + r < n_embed, else table[id] with id = ids[off + r - n_embed];

@@ -19,7 +19,7 @@ struct PfGemmArgs {
   const float* wscale;    // e4m3 weights: one scale per phase row, applied to the accumulators; else nullptr
   const float2* rope;     // [Mc][D/2] (QKV)
   float* x;               // [Mc][H] residual stream, updated in place (O, down)
-  int SK;                 // K split over workgroups (direct kernel; 1 = none)
+  int SK;                 // K split over workgroups (pipelined kernel; 1 = none)
   float* part;            // SK > 1: [SK][Mc][H] partial products of the splits, added to x by the next norm kernel
   u16* q;                 // [Mc][n_q][D] (QKV)
   u16* Kc; u16* Vc;       // this layer's packed cache (QKV)
