@@ -113,6 +113,19 @@ int launch_down(hipStream_t s, const PfGemmArgs& a) {
   }
 }
 
+template <int D, int JT>
+int launch_attn_wide(hipStream_t s, const PfAttnArgs& t) {
+  static bool attr_set = false;
+  constexpr int lds = pf_attn_wide_lds<D, JT>();
+  static_assert(lds <= 160 * 1024, "LDS of one CU");
+  if (!attr_set) {
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_attn_wide_kernel<D, JT>), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    attr_set = true;
+  }
+  hipLaunchKernelGGL((pf_attn_wide_kernel<D, JT>), dim3(t.n_q * ceil_div(t.Mc / 16, JT)), dim3(256), lds, s, t);
+  return check_launch();
+}
+
 // K splits (at most kPfSplit) that divide n_it pipeline iterations evenly.
 int k_split(int n_it) {
   for (int sk = kPfSplit; sk > 1; --sk)
@@ -182,6 +195,10 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
       // (few rows: query tiles of a head share a workgroup, the keys are dealt to kPfAttnChunks workgroups, a second
       // kernel sums the chunks)
       const bool split = skinny && MTc <= 4 && c.apart != nullptr;
+      // Two query tiles per workgroup where that leaves enough of them and enough keys to share: (tiles of 16 rows, keys before
+      // the chunk) -> us for one and for two tiles, 16 heads: (64, 0) 21.3 / 18.1, (64, 1024) 41 / 29, (64, 7168) 155 / 93, (33, 0)
+      // 10.1 / 10.5, (33, 1024) 23.4 / 20.7, (21, 0) 7.9 / 8.3, (21, 1024) 16.0 / 14.3, (12, 1024) 9.8 / 12.4, (12, 7168) 42 / 43.
+      const bool wide = !split && !quad && items >= 320 && c.n0 + rows >= 1024;
       if (split) {
         t.n_chunks = kPfAttnChunks;
         t.part = c.apart;
@@ -193,6 +210,9 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
         BD_TRY(check_launch());
         if (c.D == 128) hipLaunchKernelGGL((pf_attn_merge_kernel<128, kPfAttnChunks>), dim3(items * 2), dim3(256), 0, s, t);
         else hipLaunchKernelGGL((pf_attn_merge_kernel<64, kPfAttnChunks>), dim3(items), dim3(256), 0, s, t);
+      } else if (wide) {
+        if (c.D == 128) BD_TRY((launch_attn_wide<128, 2>(s, t)));
+        else BD_TRY((launch_attn_wide<64, 2>(s, t)));
       } else if (c.D == 128 && quad) hipLaunchKernelGGL((pf_attn_kernel<128, 4, true>), dim3(items), dim3(256), 0, s, t);
       else if (c.D == 128) hipLaunchKernelGGL((pf_attn_kernel<128, 4>), dim3(items), dim3(256), 0, s, t);
       else if (quad) hipLaunchKernelGGL((pf_attn_kernel<64, 4, true>), dim3(items), dim3(256), 0, s, t);

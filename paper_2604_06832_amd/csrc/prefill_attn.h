@@ -110,6 +110,176 @@ __global__ __launch_bounds__(64 * (NW > 4 ? NW : 4), NW > 4 ? 1 : 2) void pf_att
   }
 }
 
+// ---- chunks whose query tiles fill the chip several at a time ------------------------------------------------------------
+// One block of 32 keys against JT tiles of 16 query columns of one head: the products and exponentials of the tiles are
+// independent and interleave.  The weights' sums stay per lane until the end, and the running maximum follows the scores
+// only when some score exceeds it by more than 2^8 (weights up to 256 lose nothing in bf16 or fp32, and sums and outputs are
+// rescaled a few times per chunk instead of once per block).
+template <int D, int JT, bool MASKED, typename FK, typename FV>
+__device__ inline void attn_block_wide(KvBlock<D>& b, FK next_k, FV next_v, const bf16x8 (&qf)[JT][D / 32], f32x4 (&O)[JT][D / 16], float (&mrun)[JT],
+                                       float (&lrun)[JT], int kb, int n, int M, int mode, int row0, int g, float c) {
+  constexpr int DS = D / 32, DT = D / 16;
+  f32x4 s[JT][2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt) s[jt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds)
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) s[jt][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.k[t][ds], qf[jt][ds], s[jt][t], 0, 0, 0);
+  }
+  next_k(b);
+  asm volatile("" ::: "memory");
+  float cm[JT];
+  bool move = false;
+#pragma unroll
+  for (int jt = 0; jt < JT; ++jt) {
+    float m = kNegBig;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float v = s[jt][e >> 2][e & 3];
+      if constexpr (MASKED) {
+        const int jb = kb * 32 + 8 * g + e - n;
+        const bool vis = jb < 0 || (jb < M && block_key_visible<false>(mode, row0 + jt * 16, jb));
+        v = vis ? v : -INFINITY;
+        s[jt][e >> 2][e & 3] = v;
+      }
+      m = fmaxf(m, v);
+    }
+    cm[jt] = rows_max(m) * c;
+    move |= cm[jt] > mrun[jt] + 8.f;
+  }
+  if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt) {
+      const float mnew = fmaxf(mrun[jt], cm[jt]);
+      const float alpha = __builtin_amdgcn_exp2f(mrun[jt] - mnew);
+      mrun[jt] = mnew;
+      lrun[jt] *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) O[jt][dt] *= alpha;
+    }
+  }
+  bf16x8 p8[JT];
+#pragma unroll
+  for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float p = __builtin_amdgcn_exp2f(fmaf(s[jt][e >> 2][e & 3], c, -mrun[jt]));   // (a masked score gives 0)
+      lrun[jt] += p;
+      p8[jt][e] = (__bf16)p;
+    }
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt) O[jt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b.v[dt], p8[jt], O[jt][dt], 0, 0, 0);
+  next_v(b);
+  asm volatile("" ::: "memory");
+}
+
+// pf_attn_kernel with JT query tiles of a head per workgroup: its four wavefronts share out the key blocks, and each block is
+// loaded once for JT tiles.  What bounds the kernel above on long contexts is that traffic: 16 KiB per block, tile and
+// wavefront, 29 TB/s out of the L2s at 1024 rows against 8192 keys, where it takes 151 us and this one 91 (JT = 2, two workgroups
+// per CU; JT = 4 with one 106; two register buffers, one block ahead, 120).  Wavefront w merges tiles w, w + 4, ...  The workgroups
+// of a kv head run on the same XCDs where the number of kv heads divides theirs, so that its keys and values stay in those L2s.
+template <int D, int JT> constexpr int pf_attn_wide_lds() { return 4 * JT * ((D / 16) * 1024 + 2 * 64); }
+template <int D, int JT>
+__global__ __launch_bounds__(256, JT > 2 ? 1 : 2) void pf_attn_wide_kernel(PfAttnArgs a) {
+  constexpr int DS = D / 32, DT = D / 16, NW = 4;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  f32x4* sO = reinterpret_cast<f32x4*>(lds);                   // [NW][JT][DT][64]
+  float* sm = reinterpret_cast<float*>(lds + NW * JT * DT * 1024);   // [NW][JT][16]
+  float* sl = sm + NW * JT * 16;
+  if (a.skippable && a.st->skip) return;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int col = lane & 15, g = lane >> 4;
+  const int G = a.n_q / a.n_kv, QT = a.Mc >> 4, TG = (QT + JT - 1) / JT;
+  int kvh, idx;
+  if (8 % a.n_kv == 0) {
+    kvh = blockIdx.x % a.n_kv;
+    idx = blockIdx.x / a.n_kv;
+  } else {
+    kvh = blockIdx.x / (G * TG);
+    idx = blockIdx.x % (G * TG);
+  }
+  const int head = kvh * G + idx % G, qt0 = (idx / G) * JT;    // (tiles past the last one repeat it and store nothing)
+  const size_t kv_block = (size_t)32 * D / 8;
+  const bf16x8* Kh = reinterpret_cast<const bf16x8*>(a.Kc) + (size_t)kvh * a.max_kb * kv_block;
+  const bf16x8* Vh = reinterpret_cast<const bf16x8*>(a.Vc) + (size_t)kvh * a.max_kb * kv_block;
+  bf16x8 qf[JT][DS];
+  f32x4 O[JT][DT];
+  float mrun[JT], lrun[JT];
+#pragma unroll
+  for (int jt = 0; jt < JT; ++jt) {
+    const u16* qp = a.q + ((size_t)(min(qt0 + jt, QT - 1) * 16 + col) * a.n_q + head) * D + 8 * g;
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds) qf[jt][ds] = *reinterpret_cast<const bf16x8*>(qp + ds * 32);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) O[jt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    mrun[jt] = kNegBig;
+    lrun[jt] = 0.f;
+  }
+  {
+    // blocks holding a key some row of the group may see: up to its last row (causal), else all of the chunk
+    const int last_row = min(min(qt0 + JT, QT) * 16 - 1, a.Mvalid - 1);
+    const int kb_end = (a.n0 + (a.mode == 1 ? last_row : a.Mvalid - 1)) / 32 + 1;
+    const float c = a.scale_log2e;
+    const int row0 = qt0 * 16 + col;
+    // The keys of the next block are loaded over this block's as soon as their products are issued, its values likewise: one
+    // register buffer, and each load has the other half of the block to arrive.  (The look-ahead is unconditional, at the
+    // end of the last block again: behind a load that may not have been issued the compiler can only wait for everything.)
+    if (wave < kb_end) {
+      KvBlock<D> b;
+      kv_load<D>(b, Kh, Vh, wave, lane, a.pages);
+      asm volatile("" ::: "memory");
+      for (int kb = wave; kb < kb_end; kb += NW) {
+        const int nb = page_of_block(a.pages, __builtin_amdgcn_readfirstlane(min(kb + NW, kb_end - 1)));
+        auto next_k = [&](KvBlock<D>& o) { kv_load_k<D>(o, Kh, nb, lane); };
+        auto next_v = [&](KvBlock<D>& o) { kv_load_v<D>(o, Vh, nb, lane); };
+        if (kb * 32 + 31 >= a.n0)
+          attn_block_wide<D, JT, true>(b, next_k, next_v, qf, O, mrun, lrun, kb, a.n0, a.Mvalid, a.mode, row0, g, c);
+        else
+          attn_block_wide<D, JT, false>(b, next_k, next_v, qf, O, mrun, lrun, kb, a.n0, a.Mvalid, a.mode, row0, g, c);
+      }
+    }
+  }
+#pragma unroll
+  for (int jt = 0; jt < JT; ++jt) {
+    const float l = rows_sum(lrun[jt]);
+    if (g == 0) {
+      sm[(wave * JT + jt) * 16 + col] = mrun[jt];
+      sl[(wave * JT + jt) * 16 + col] = l;
+    }
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) sO[((wave * JT + jt) * DT + dt) * 64 + lane] = O[jt][dt];
+  }
+  __syncthreads();
+  for (int jt = wave; jt < JT && qt0 + jt < QT; jt += NW) {
+    float m = kNegBig, f[NW], l = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) m = fmaxf(m, sm[(w * JT + jt) * 16 + col]);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      f[w] = __builtin_amdgcn_exp2f(sm[(w * JT + jt) * 16 + col] - m);
+      l += sl[(w * JT + jt) * 16 + col] * f[w];
+    }
+    const float inv = 1.f / l;
+    const int row = (qt0 + jt) * 16 + col;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < NW; ++w) o += sO[((w * JT + jt) * DT + dt) * 64 + lane] * f[w];
+      o *= inv;
+      const int fo = head * D + dt * 16 + 4 * g;
+      const uint32_t lo = (uint32_t)f32_to_bf16_bits(o[0]) | ((uint32_t)f32_to_bf16_bits(o[1]) << 16);
+      const uint32_t hi = (uint32_t)f32_to_bf16_bits(o[2]) | ((uint32_t)f32_to_bf16_bits(o[3]) << 16);
+      *reinterpret_cast<uint64_t*>(a.out + xp_index(row, fo, a.MTc)) = (uint64_t)lo | ((uint64_t)hi << 32);
+    }
+  }
+}
+
 // The same for forwards of at most 64 rows, where few items would leave most CUs idle and every item would walk all keys
 // of its kv head at one CU's load rate: a workgroup takes JT query tiles of one head (they share every key/value block
 // it loads) and one of n_chunks key chunks (block kb belongs to chunk kb mod n_chunks, and inside the workgroup to

@@ -691,15 +691,24 @@ struct KvBlock {
 
 // Block kb of a kv head (the keys of positions 32 kb .. 32 kb + 31) out of the page that holds it.
 template <int D>
-__device__ inline void kv_load(KvBlock<D>& b, const bf16x8* Kh, const bf16x8* Vh, int kb_logical, int lane, const int* pages) {
-  constexpr int DS = D / 32, DT = D / 16;
-  const int kb = page_of_block(pages, __builtin_amdgcn_readfirstlane(kb_logical));
+__device__ inline void kv_load_k(KvBlock<D>& b, const bf16x8* Kh, int page, int lane) {
+  constexpr int DS = D / 32;
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int ds = 0; ds < DS; ++ds) b.k[t][ds] = Kh[(((size_t)kb * 2 + t) * DS + ds) * 64 + lane];
+    for (int ds = 0; ds < DS; ++ds) b.k[t][ds] = Kh[(((size_t)page * 2 + t) * DS + ds) * 64 + lane];
+}
+template <int D>
+__device__ inline void kv_load_v(KvBlock<D>& b, const bf16x8* Vh, int page, int lane) {
+  constexpr int DT = D / 16;
 #pragma unroll
-  for (int dt = 0; dt < DT; ++dt) b.v[dt] = Vh[((size_t)kb * DT + dt) * 64 + lane];
+  for (int dt = 0; dt < DT; ++dt) b.v[dt] = Vh[((size_t)page * DT + dt) * 64 + lane];
+}
+template <int D>
+__device__ inline void kv_load(KvBlock<D>& b, const bf16x8* Kh, const bf16x8* Vh, int kb_logical, int lane, const int* pages) {
+  const int kb = page_of_block(pages, __builtin_amdgcn_readfirstlane(kb_logical));
+  kv_load_k<D>(b, Kh, kb, lane);
+  kv_load_v<D>(b, Vh, kb, lane);
 }
 
 // One block of 32 keys against one tile of 16 query columns.  Scores stay unscaled until the exponent:

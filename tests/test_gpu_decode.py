@@ -1200,3 +1200,36 @@ def test_large_m_prefill_agrees_with_the_chunked_one():
     for a, b in ((k0, k2), (v0, v2)):
         assert float((a - b).abs().max()) <= 1e-2 * float(b.abs().max())
     assert c0[0] == c2[0] and abs(c0[1] - c2[1]) <= 0.02 * c2[1]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+def test_large_m_tiles_over_chunk_sizes(dtype):
+    """Prompts whose chunks take every tile shape of the pipelined GEMMs and both attention kernels (edges of the token tiles,
+    ragged last tiles, a second chunk of few and of many rows) against the decode kernels, 32 or 64 rows at a time: keys and
+    values of the second layer, which depend on every phase of the first.  Bar: both sides round the same eight hand-overs per
+    layer to bf16 (2^-9 each) around sums of another order, 2 layers: rms 2^-9 sqrt(2 * 16) < 0.012 of the result; largest of
+    about 10^6 values, 8 rms, relative to the largest value (4 to 5 rms of the values): 2e-2 as in the test above."""
+    shape = _wide(2, vocab=8192)
+    w = inputs.make_weights(shape, 4 if dtype == "bf16" else 2, dtype, threads=8)
+    kw = dict(max_seq=2176, max_block=64 if dtype == "bf16" else 32,
+              weight_dtype=binding.BD_FP8_E4M3 if dtype == "fp8" else binding.BD_BF16)
+    emb, ids = inputs.make_prompt(shape, 900, 1250, seed=12)
+    ctxs = []
+    for flags in (0, binding.BD_FLAG_PREFILL_DECODE):
+        ctx = binding.Context(shape, flags=flags, **kw)
+        ctx.load_model(w, as_bf16_bits=True) if dtype == "bf16" else ctx.load_model(w)
+        ctxs.append(ctx)
+    for rows in (129, 193, 257, 333, 386, 513, 770, 1000, 1024, 1153, 2149):
+        _say(f"large-M tiles {dtype}: {rows} rows")
+        e, i = torch.from_numpy(emb[:min(rows, 900)]).cuda(), torch.from_numpy(ids[:max(0, rows - 900)]).cuda()
+        res = []
+        for ctx in ctxs:
+            ctx.bd_prefill(e, i)
+            k, v = ctx.bd_read_kv(1, 0, rows)
+            res.append((k.clone(), v.clone()))
+            ctx.bd_status()
+        for a, b in zip(*res):
+            assert float((a - b).abs().max()) <= 2e-2 * float(b.abs().max()), rows
+            assert float((a - b).norm()) <= 1.2e-2 * float(b.norm()), rows
+    for ctx in ctxs:
+        ctx.close()
