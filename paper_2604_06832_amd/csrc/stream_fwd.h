@@ -711,6 +711,23 @@ __device__ inline void kv_load(KvBlock<D>& b, const bf16x8* Kh, const bf16x8* Vh
   kv_load_v<D>(b, Vh, kb, lane);
 }
 
+// The same through buffer descriptors of the kv head's keys and values, for loops that look ahead: `ok` false requests nothing (an
+// offset past the end), but the loads are issued either way, so the compiler knows how many are younger than those it waits
+// for.  (Behind a look-ahead that may not have been issued it waits for everything, the look-ahead included: 32 rows, 8192 keys, eight
+// blocks per wavefront, one forward 2471 us; in this form 2413.)
+template <int D>
+__device__ inline void kv_load_ahead(KvBlock<D>& b, const rsrc_t& kr, const rsrc_t& vr, int kb_logical, bool ok, int lane, const int* pages) {
+  constexpr int DS = D / 32, DT = D / 16;
+  const int kb = ok ? page_of_block(pages, __builtin_amdgcn_readfirstlane(kb_logical)) : 0;
+  const int off = ok ? kb * (64 * D) + lane * 16 : 0x7FFF0000;
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds) b.k[t][ds] = buf_load_b(kr, off + (t * DS + ds) * 1024);
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) b.v[dt] = buf_load_b(vr, off + dt * 1024);
+}
+
 // One block of 32 keys against one tile of 16 query columns.  Scores stay unscaled until the exponent:
 // p = 2^(s*c - m) with c = log2(e)/sqrt(d) folded into one fused multiply-add per score.
 template <int D, bool MASKED, bool QUAD = false>
@@ -1019,17 +1036,18 @@ __device__ inline bool stream_attention_local(const MegaArgs& a, FwdCtx& fc, Fwd
     float mrun = kNegBig, lrun = 0.f;
     const int stride = kWavesPerWG * lp.NCH;
     const int kb0 = chunk + lp.NCH * wave;
+    const rsrc_t kr = make_rsrc(Kh, (unsigned)(a.max_kb * 64 * D)), vr = make_rsrc(Vh, (unsigned)(a.max_kb * 64 * D));
     KvBlock<D> b0, b1;
-    if (kb0 < n_kb) kv_load<D>(b0, Kh, Vh, kb0, lane, a.kv_pages);
+    kv_load_ahead<D>(b0, kr, vr, kb0, kb0 < n_kb, lane, a.kv_pages);
     asm volatile("" ::: "memory");
     for (int kb = kb0; kb < n_kb; kb += 2 * stride) {
       const int kb1 = kb + stride, kb2 = kb + 2 * stride;
-      if (kb1 < n_kb) kv_load<D>(b1, Kh, Vh, kb1, lane, a.kv_pages);
+      kv_load_ahead<D>(b1, kr, vr, kb1, kb1 < n_kb, lane, a.kv_pages);
       asm volatile("" ::: "memory");
       if (kb * 32 + 31 >= n) attn_block<D, true, QUAD>(b0, qf, O, mrun, lrun, kb, n, a.M, a.mode, row, g, c);
       else attn_block<D, false>(b0, qf, O, mrun, lrun, kb, n, a.M, a.mode, row, g, c);
       if (kb1 < n_kb) {
-        if (kb2 < n_kb) kv_load<D>(b0, Kh, Vh, kb2, lane, a.kv_pages);
+        kv_load_ahead<D>(b0, kr, vr, kb2, kb2 < n_kb, lane, a.kv_pages);
         asm volatile("" ::: "memory");
         if (kb1 * 32 + 31 >= n) attn_block<D, true, QUAD>(b1, qf, O, mrun, lrun, kb1, n, a.M, a.mode, row, g, c);
         else attn_block<D, false>(b1, qf, O, mrun, lrun, kb1, n, a.M, a.mode, row, g, c);
