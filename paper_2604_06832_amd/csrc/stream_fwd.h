@@ -714,7 +714,7 @@ __device__ inline void kv_load(KvBlock<D>& b, const bf16x8* Kh, const bf16x8* Vh
 // The same through buffer descriptors of the kv head's keys and values, for loops that look ahead: `ok` false requests nothing (an
 // offset past the end), but the loads are issued either way, so the compiler knows how many are younger than those it waits
 // for.  (Behind a look-ahead that may not have been issued it waits for everything, the look-ahead included: 32 rows, 8192 keys, eight
-// blocks per wavefront, one forward 2471 us; in this form 2413.)
+// blocks per wavefront, one forward 2471 us; in this form 2413 to 2422.)
 template <int D>
 __device__ inline void kv_load_ahead(KvBlock<D>& b, const rsrc_t& kr, const rsrc_t& vr, int kb_logical, bool ok, int lane, const int* pages) {
   constexpr int DS = D / 32, DT = D / 16;
