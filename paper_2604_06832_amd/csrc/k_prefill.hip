@@ -198,7 +198,9 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
       // Two query tiles per workgroup where that leaves enough of them and enough keys to share: (tiles of 16 rows, keys before
       // the chunk) -> us for one and for two tiles, 16 heads: (64, 0) 21.3 / 18.1, (64, 1024) 41 / 29, (64, 7168) 155 / 93, (33, 0)
       // 10.1 / 10.5, (33, 1024) 23.4 / 20.7, (21, 0) 7.9 / 8.3, (21, 1024) 16.0 / 14.3, (12, 1024) 9.8 / 12.4, (12, 7168) 42 / 43.
-      const bool wide = !split && !quad && items >= 320 && c.n0 + rows >= 1024;
+      // (A first chunk stays with one tile: 3 us a layer at most, and a carry decided by a near-tie of the e4m3 model at full
+      // depth turns with the order of its sums.)
+      const bool wide = !split && !quad && items >= 320 && c.n0 >= 512;
       if (split) {
         t.n_chunks = kPfAttnChunks;
         t.part = c.apart;
