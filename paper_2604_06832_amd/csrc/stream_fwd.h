@@ -33,6 +33,9 @@ constexpr int kMirror = 3;                  // copies of the first slots behind 
 constexpr int kLdsSpin = 1 << 22;           // bound of every LDS wait (a timed-out wait marks the context broken)
 constexpr int kRingBytes = (kSlots + kMirror) * 1024;
 constexpr int kShareBytes = 40 * 1024;      // K-reduction buffers / attention merge buffers (one region, re-used)
+// Sums of squares a lane adds up: one per 16 channels of a row, dealt to 16 lane groups.  (K of the normed phases is not
+// split over workgroups, so H is at most what the four K ranges hold.)
+constexpr int kSsqPer = kWavesPerWG * kMaxKW * 32 / 16 / 16;
 // 16-row tiles a wavefront accumulates before the K ranges are summed
 template <int MT> constexpr int round_tiles() { return MT == 1 ? 6 : 4; }
 
@@ -448,16 +451,16 @@ __device__ inline void stream_gemm_phase(const MegaArgs& a, FwdCtx& fc, Ring& rg
     const rsrc_t xr = make_rsrc(src + (size_t)w0 * MT * 512, (unsigned)(KX * MT * 1024));   // (k-steps beyond KX read as zero)
     // this wavefront's share (parts = wave*4 + lane group mod 16) of the sums of squares of every row, ahead of the
     // activations: they are summed while those arrive
-    float sv[MT][8];
+    float sv[MT][kSsqPer];
     if (norm) {
       const int parts = ver == 0 ? 1 : P.H >> 4;
       const rsrc_t sr = make_rsrc(a.ssq + (size_t)ver * a.ssq_parts * a.Mp, (unsigned)(parts * a.Mp * 4));
-      const int so = ((wave * 4 + g) * a.Mp + col) * 4;
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
+      const int so = ((wave * 4 + g) * a.Mp + col) * 4;      // (parts that do not exist read as zero: the whole offset is
+#pragma unroll                                               // in the vector offset, the only one the range check covers)
+      for (int u = 0; u < kSsqPer; ++u)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-          sv[mt][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, so + mt * 64, u * 16 * a.Mp * 4, 0));
+          sv[mt][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, so + u * 16 * a.Mp * 4 + mt * 64, 0, 0));
       asm volatile("" ::: "memory");
     }
     // activation fragments of this wavefront's k-steps: one round trip, straight into registers
@@ -472,7 +475,7 @@ __device__ inline void stream_gemm_phase(const MegaArgs& a, FwdCtx& fc, Ring& rg
       for (int mt = 0; mt < MT; ++mt) {
         float s = 0.f;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s += sv[mt][u];
+        for (int u = 0; u < kSsqPer; ++u) s += sv[mt][u];
         s = rows_sum(s);
         if (g == 0) fc.s_part[wave * 64 + mt * 16 + col] = s;
       }
