@@ -994,9 +994,11 @@ def test_headline_config_first_block_full_depth():
     _say("generating 3B-shaped bf16 weights (seed 0)")
     w = inputs.make_weights(shape, 0, "bf16", threads=16)
     emb, ids = inputs.make_prompt(shape, 768, 256, seed=101)
+    ids[-1] = 48     # the carry seeds the block: a last id after which the oracle decides it by 0.68 (id margin 0.48)
     _say("uploading + oracle prefill of 1024 tokens")
     p = Pair(shape, w, max_seq=1024 + 256 + 32, oracle_dtype=np.float32)
     p.prefill(emb, ids, oracle_chunk=256)
+    assert p.carry_is_robust()
     # the last prompt row's logits (row 0 of the LM-head pass that ends a large-M prefill) against the oracle's, to the
     # bars of every other logits row
     glog = p.ctx.bd_read_logits(1).cpu().numpy()[0]
@@ -1029,11 +1031,14 @@ def test_fp8_config_first_block_full_depth():
     _say("generating 3B-shaped e4m3 weights (seed 2)")
     w = inputs.make_weights(shape, 2, "fp8", threads=16)
     emb, ids = inputs.make_prompt(shape, 768, 256, seed=104)
+    ids[-1] = 32     # the carry seeds the block: a last id after which the oracle decides it by 0.73 (id margin 0.48)
     _say("uploading + oracle prefill of 1024 tokens")
     p = Pair(shape, w, max_seq=1024 + 64, oracle_dtype=np.float32, predecode=True)
     p.prefill(emb, ids, oracle_chunk=256)
+    assert p.carry_is_robust()
     glog = p.ctx.bd_read_logits(1).cpu().numpy()[0]
     assert_logits_close(glog, p.o.carry, FP8_LOGIT_TOL, what="carry logits", n_layers=shape.n_layers)
+    p.check_carry()
     tok, msk = fresh_block(shape, 32)
     fwd = 0
     while msk.any():
