@@ -26,22 +26,22 @@ int launch_pf_gemm(hipStream_t s, PfGemmArgs a, int n_rows) {
   return check_launch();
 }
 
-template <int PH, int WN, int TW, int BKS, int NST>
+template <int PH, int WN, int TW, int BKS, int NST, bool ODD = false>
 int launch_pf_gemm_pipe(hipStream_t s, PfGemmArgs a) {
   static bool attr_set = false;
   constexpr int lds = pf_gemm_pipe_lds<WN, TW, BKS, NST>();
   static_assert(lds <= 160 * 1024, "LDS of one CU");
   if (!attr_set) {
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_pipe_kernel<PH, WN, TW, BKS, NST>),
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_pipe_kernel<PH, WN, TW, BKS, NST, ODD>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     attr_set = true;
   }
   static_assert(BKS <= 2, "turns of two k-steps");
-  if (a.SK < 1 || a.KS % (2 * a.SK) != 0) return BD_E_ARG;        // whole turns of the K loop per split
+  if (ODD ? a.SK != 1 || a.KS % 2 != 1 : a.SK < 1 || a.KS % (2 * a.SK) != 0) return BD_E_ARG;   // whole turns of the K loop per split
   a.RG = ceil_div(a.NT, 2 * WN);
   a.TG = ceil_div(a.MTc, 2 * TW);
   const int grid = ceil_div(a.RG, 8) * 8 * a.TG * a.SK;
-  hipLaunchKernelGGL((pf_gemm_pipe_kernel<PH, WN, TW, BKS, NST>), dim3(grid), dim3(kPfThreads), lds, s, a);
+  hipLaunchKernelGGL((pf_gemm_pipe_kernel<PH, WN, TW, BKS, NST, ODD>), dim3(grid), dim3(kPfThreads), lds, s, a);
   return check_launch();
 }
 
@@ -88,6 +88,16 @@ int launch_o(hipStream_t s, const PfGemmArgs& a) {
   }
 }
 int launch_gu(hipStream_t s, const PfGemmArgs& a) {
+  if (a.KS % 2 != 0) {
+    // (hidden an odd multiple of 32; a round's times as below: a stage of one k-step instead of two changes them by under a tenth)
+    static constexpr PfTile t[] = {{3, 4, 24.f}, {6, 4, 31.f}, {11, 4, 49.f}, {11, 8, 81.f}};
+    switch (pick_tile(t, a.NT, a.MTc, 1)) {
+      case 0: return launch_pf_gemm_pipe<PH_GU, 3, 4, 1, 9, true>(s, a);
+      case 1: return launch_pf_gemm_pipe<PH_GU, 6, 4, 1, 6, true>(s, a);
+      case 2: return launch_pf_gemm_pipe<PH_GU, 11, 4, 1, 5, true>(s, a);
+      default: return launch_pf_gemm_pipe<PH_GU, 11, 8, 1, 4, true>(s, a);
+    }
+  }
   static constexpr PfTile t[] = {{3, 2, 20.5f}, {3, 3, 22.f}, {3, 4, 24.f}, {6, 4, 31.f}, {6, 6, 39.f}, {11, 4, 49.f}, {11, 6, 62.f}, {11, 8, 81.f}};
   switch (pick_tile(t, a.NT, a.MTc, 1)) {
     case 0: return launch_pf_gemm_pipe<PH_GU, 3, 2, 2, 7>(s, a);
@@ -181,7 +191,8 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
     g.w = reinterpret_cast<const bf16x8*>(wl + c.w_off[0]); g.KS = ceil_div(c.H, 32);
     g.xin = reinterpret_cast<const bf16x8*>(c.xb);
     g.wscale = ws ? ws + c.wscale_off[0] : nullptr;
-    // (every phase: the pipelined kernel when K is a whole number of its turns, else the register-staged one)
+    // (every phase: the pipelined kernel when K is a whole number of its turns, else the register-staged one; gate/up, half
+    // of a layer's products, at any K)
     g.NT = c.NQKV / 16;
     if (!c.staged && g.KS % 2 == 0) BD_TRY(launch_qkv(s, g));
     else BD_TRY((launch_pf_gemm<PH_QKV, 2, 2, 2>(s, g, c.NQKV)));
@@ -242,7 +253,7 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
     g.xin = reinterpret_cast<const bf16x8*>(c.xb);
     g.wscale = ws ? ws + c.wscale_off[2] : nullptr;
     g.NT = 2 * c.F / 16;
-    if (!c.staged && g.KS % 2 == 0) BD_TRY(launch_gu(s, g));
+    if (!c.staged) BD_TRY(launch_gu(s, g));
     else BD_TRY((launch_pf_gemm<PH_GU, 4, 2, 4>(s, g, 2 * c.F)));
     g.w = reinterpret_cast<const bf16x8*>(wl + c.w_off[3]); g.KS = ceil_div(c.F, 32);
     g.xin = reinterpret_cast<const bf16x8*>(c.act);

@@ -272,15 +272,15 @@ __device__ inline void unrolled(F&& f) {
 // the 3B shape (launches back to back) against kernels without the overlap of LDS reads and products (1024 rows: two stages, two
 // to four workgroups per CU; 72 rows: two token groups of 64): 1024 rows gate/up 82 us / 98, down 47 / 52, QKV 19.9 / 22.9,
 // O 16.8 / 16.7; 72 rows gate/up 21.7 / 33.4, down 14.0 / 25.1, QKV 9.8 / 10.2, O 6.3 / 9.0.
-// Needs whole turns of the loop per K split (no K tail).  With SK > 1 the workgroups of an output tile split K among them and
+// Needs whole turns of the loop per K split (ODD: one k-step more, with stages of one and no split).  With SK > 1 the workgroups of an output tile split K among them and
 // each leaves its product in its own slice of `part` (O and down phases), which the norm that follows adds.
-template <int PH, int WN, int TW, int BKS, int NST>
+template <int PH, int WN, int TW, int BKS, int NST, bool ODD = false>
 __global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs a) {
   constexpr int AT = 2 * WN, BT = 2 * TW;
   constexpr int AF = AT * BKS, TF = AF + BT * BKS;                  // weight fragments, all fragments of a stage
   constexpr int PER = (TF + 3) / 4;                                 // loads per wavefront and stage
   constexpr int U = BKS > 2 ? BKS : 2;                              // k-steps per turn of the loop
-  static_assert(U % BKS == 0 && U % 2 == 0 && NST >= 3, "");
+  static_assert(U % BKS == 0 && U % 2 == 0 && NST >= 3 && (!ODD || BKS == 1), "");
   static_assert((NST - 2) * PER <= 63, "outstanding loads must fit the counter");
   extern __shared__ __attribute__((aligned(16))) char lds[];
   if (a.skippable && a.st->skip) return;
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs 
   for (int j = 0; j < TW; ++j) bf[0][j] = *reinterpret_cast<const bf16x8*>(fb + j * 1024);
 
   int it = 0, s_read = 0;                                           // stage of the current k-step, slot of the next one
-  const int ksteps = n_it * BKS;
+  const int ksteps = n_it * BKS - (ODD ? 1 : 0);
   for (int k = 0; k < ksteps; k += U) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -375,6 +375,8 @@ __global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs 
       });
     }
   }
+  if constexpr (ODD)                                                // the last k-step: its fragments are in registers by now
+    unrolled<WN>([&](auto i) { unrolled<TW>([&](auto j) { mfma_in_place<(i * TW + j < 64)>(acc[i][j], af[i], bf[0][j]); }); });
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
   unrolled<WN>([&](auto i) { unrolled<TW>([&](auto j) { pin_acc<(i * TW + j < 64)>(acc[i][j]); }); });
   pf_epilogue<PH, WN, TW>(a, acc, ep, T0, mt0, wn, wm, lane, kz);

@@ -1179,6 +1179,43 @@ def test_prefill_with_the_k_split_down_projection(n_embed, n_ids):
     p.close()
 
 
+def _kernels_of(call):
+    """Names of the device kernels that `call` launches."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return {e.name for e in prof.events()}
+
+
+def _instances(names, kernel):
+    """Template arguments of the instantiations of `kernel` among the names."""
+    import re
+    return {tuple(a.strip() for a in m.group(1).split(",")) for n in names for m in [re.search(kernel + r"<([^>]*)>", n)] if m}
+
+
+def test_gate_up_of_a_hidden_size_with_an_odd_number_of_k_steps():
+    """Hidden 224 is seven k-steps of 32: the pipelined gate/up product ends with half a turn of its loop.  Chunks of 48 (a
+    committed block), 200, 512 and 600 rows take its four tile shapes (96 and 192 rows x 128 tokens, 352 x 128, 352 x 256);
+    cache, carry and logits against the oracle."""
+    shape = inputs.ModelShape(n_layers=2, hidden=224, n_q_heads=4, n_kv_heads=2, head_dim=64, ffn=11008, vocab=1024)
+    w = inputs.make_weights(shape, 3, "bf16", threads=8)
+    p = Pair(shape, w, max_seq=704)
+    taken = set()
+    for n_embed, n_ids, block in ((20, 20, 48), (130, 70, 0), (312, 200, 33), (400, 200, 64)):
+        _say(f"odd k-steps: {n_embed + n_ids} rows, block of {block}")
+        emb, ids = inputs.make_prompt(shape, n_embed, n_ids, seed=9)
+        names = _kernels_of(lambda: p.prefill(emb, ids))
+        p.check_carry()
+        if block:
+            names |= _kernels_of(lambda: p.commit(np.arange(3, 3 + block, dtype=np.int32)))
+        p.check_kv(0, n_embed + n_ids + block)
+        taken |= {a[1:3] for a in _instances(names, "pf_gemm_pipe_kernel") if a[0] == "2" and a[-1] == "true"}
+    assert taken == {("3", "4"), ("6", "4"), ("11", "4"), ("11", "8")}, taken
+    p.close()
+
+
 def test_large_m_prefill_agrees_with_the_chunked_one():
     """The same prompt through the large-M kernels and through 64-row decode forwards: same cache and carry up to
     bf16 rounding of a different summation order (each path is also held against the oracle elsewhere)."""
