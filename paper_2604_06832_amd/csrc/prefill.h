@@ -345,6 +345,9 @@ __global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs 
 #pragma unroll
   for (int j = 0; j < TW; ++j) bf[0][j] = *reinterpret_cast<const bf16x8*>(fb + j * 1024);
 
+  // (The compiler's hazard handling does not look into inline assembly: the build checks that between the two markers
+  // nothing but the products touches an accumulator, and nothing but LDS reads writes their operands.)
+  asm volatile("; BD_ACC_BEGIN" ::: "memory");
   int it = 0, s_read = 0;                                           // stage of the current k-step, slot of the next one
   const int ksteps = n_it * BKS - (ODD ? 1 : 0);
   for (int k = 0; k < ksteps; k += U) {
@@ -377,7 +380,7 @@ __global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs 
   }
   if constexpr (ODD)                                                // the last k-step: its fragments are in registers by now
     unrolled<WN>([&](auto i) { unrolled<TW>([&](auto j) { mfma_in_place<(i * TW + j < 64)>(acc[i][j], af[i], bf[0][j]); }); });
-  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  asm volatile("s_nop 15\n\ts_nop 15\n\t; BD_ACC_END" ::: "memory");
   unrolled<WN>([&](auto i) { unrolled<TW>([&](auto j) { pin_acc<(i * TW + j < 64)>(acc[i][j]); }); });
   pf_epilogue<PH, WN, TW>(a, acc, ep, T0, mt0, wn, wm, lane, kz);
 }
