@@ -294,9 +294,11 @@ __global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs 
   const rsrc_t wr = make_rsrc(a.w, (unsigned)((size_t)a.NT * a.KS * 1024));
   const rsrc_t xr = make_rsrc(a.xin, (unsigned)((size_t)a.KS * a.MTc * 1024));
   const int n_it = a.KS / BKS / a.SK, it0 = kz * n_it;
-  // Row groups that run at the same time start a few k-steps apart: their weight tiles lie a multiple of 4 KiB apart (the
-  // same few channels of the L2 for the same k-step), while the activations they share stay in the L2 between them.
-  const int rot = (rg >> 3) % 4 % n_it;
+  // With one token group every workgroup has weights of its own and they all share the activations: the row groups start at
+  // different k-steps, so that they do not ask the same channels of the L2 for the same fragment at once (3B gate/up, 96 rows per
+  // workgroup, 64 tokens: 18.9 us, all from the first k-step 19.7; 48 tokens 18.5 / 19.2; 128 tokens, 96 x 128 tiles, 23.3 / 24.3).  With several,
+  // the workgroups that share weights keep in step (1024 rows, 352 x 256: 81.4 us, from different k-steps 84.6).
+  const int rot = a.TG == 1 ? rg * 5 % n_it : 0;
 
   // Fragment f of a stage: weights (k-step f / AT, row tile f mod AT), then activations (k-step, token tile).  Tiles past
   // the end re-read the last valid one and are dropped by the epilogue; with a fragment count that does not divide by
