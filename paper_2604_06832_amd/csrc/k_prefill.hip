@@ -48,14 +48,15 @@ int launch_pf_gemm_pipe(hipStream_t s, PfGemmArgs a) {
 // Tile shapes of the pipelined GEMM: 32*WN rows x 32*TW tokens per workgroup, one workgroup per CU.  A shape's cost is the
 // number of rounds of the chip (32 CUs per XCD; a row group and its K splits stay on one XCD) times the time of one
 // round, measured on the phase's 3B shape (launches back to back, weights from HBM); the cheapest shape is taken.
+constexpr int kXcds = 8, kXcdCUs = 32, kCUs = kXcds * kXcdCUs;     // (an MI355X in one piece)
 struct PfTile { int wn, tw; float us; };
 template <int N>
 int pick_tile(const PfTile (&t)[N], int NT, int MTc, int SK) {
   int best = 0;
   float cost = 0.f;
   for (int i = 0; i < N; ++i) {
-    const int per_xcd = ceil_div(ceil_div(NT, 2 * t[i].wn), 8) * ceil_div(MTc, 2 * t[i].tw) * SK;
-    const float c = (float)ceil_div(per_xcd, 32) * t[i].us;
+    const int per_xcd = ceil_div(ceil_div(NT, 2 * t[i].wn), kXcds) * ceil_div(MTc, 2 * t[i].tw) * SK;
+    const float c = (float)ceil_div(per_xcd, kXcdCUs) * t[i].us;
     if (i == 0 || c < cost) { best = i; cost = c; }
   }
   return best;
@@ -206,12 +207,14 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
       // (few rows: query tiles of a head share a workgroup, the keys are dealt to kPfAttnChunks workgroups, a second
       // kernel sums the chunks)
       const bool split = skinny && MTc <= 4 && c.apart != nullptr;
-      // Two query tiles per workgroup where that leaves enough of them and enough keys to share: (tiles of 16 rows, keys before
-      // the chunk) -> us for one and for two tiles, 16 heads: (64, 0) 21.3 / 18.1, (64, 1024) 41 / 29, (64, 7168) 155 / 93, (33, 0)
-      // 10.1 / 10.5, (33, 1024) 23.4 / 20.7, (21, 0) 7.9 / 8.3, (21, 1024) 16.0 / 14.3, (12, 1024) 9.8 / 12.4, (12, 7168) 42 / 43.
-      // (A first chunk stays with one tile: 3 us a layer at most, and a carry decided by a near-tie of the e4m3 model at full
-      // depth turns with the order of its sums.)
-      const bool wide = !split && !quad && items >= 320 && c.n0 >= 512;
+      // Two query tiles per workgroup halve what comes out of the L2s, and the number of workgroups.  (Tiles of 16 rows, keys before
+      // the chunk) -> us for one and for two tiles, 16 heads.  They are faster once the one-tile kernel, of which three workgroups of
+      // D = 128 fit a CU, needs another round of the chip: D = 128 (48, 0) 14.1 / 14.2, (56, 0) 18.1 / 16.0, (64, 0) 21.1 / 17.9; D = 64 (48, 0)
+      // 10.1 / 10.2, (56, 0) 13.2 / 11.4.  With fewer workgroups they are where the loads bound it, D = 128 from 512 keys on: (16, 512)
+      // 8.3 / 10.2, (20, 512) 11.5 / 11.0, (33, 128) 11.9 / 12.8, (33, 512) 17.3 / 16.4, (64, 7168) 151 / 92; D = 64, half the bytes per
+      // block: (33, 1024) 14.1 / 14.9, (40, 1024) 15.7 / 15.4, (20, 4096) 25.3 / 22.9, (33, 4096) 31.3 / 31.9.
+      const bool loads = c.D == 128 ? c.n0 >= 512 : c.n0 >= 4096 || (c.n0 >= 512 && MTc >= 40);
+      const bool wide = !split && !quad && (items > 3 * kCUs || (items >= 320 && loads));
       if (split) {
         t.n_chunks = kPfAttnChunks;
         t.part = c.apart;

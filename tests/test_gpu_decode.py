@@ -1275,3 +1275,41 @@ def test_large_m_tiles_over_chunk_sizes(dtype):
             assert float((a - b).norm()) <= 1.2e-2 * float(b.norm()), rows
     for ctx in ctxs:
         ctx.close()
+
+
+@pytest.mark.parametrize("heads,n_kv,dim,rows,first", [
+    (16, 2, 128, 1000, True),          # one chunk: 63 tiles, the last of 8 rows
+    (16, 2, 128, 1353, True),          # 1024 + 329 rows: 21 tiles, the last of 9 rows
+    (12, 2, 128, 1465, False),         # 1024 + 441 rows: 28 tiles, 7 rows short; 12 heads keep one tile in the first chunk
+    (8, 2, 64, 1929, False),           # 1024 + 905 rows: 57 tiles; so do 8 heads
+    (18, 3, 64, 1929, True)])          # kv heads that do not divide the XCDs
+def test_attention_of_two_query_tiles_per_workgroup(heads, n_kv, dim, rows, first):
+    """Chunks whose attention takes two query tiles per workgroup (the names of the launched kernels must show it), with odd
+    numbers of tiles and ragged last ones: keys and values of the second layer against the decode kernels, 64 rows at a time
+    (bars as above), and bit for bit against a cache whose pages are scattered."""
+    shape = inputs.ModelShape(n_layers=2, hidden=256, n_q_heads=heads, n_kv_heads=n_kv, head_dim=dim, ffn=768, vocab=1024)
+    w = inputs.make_weights(shape, 5, "bf16", threads=8)
+    emb, ids = inputs.make_prompt(shape, rows - 400, 400, seed=14)
+    e, i = torch.from_numpy(emb).cuda(), torch.from_numpy(ids).cuda()
+    res = []
+    for flags, scattered in ((0, False), (0, True), (binding.BD_FLAG_PREFILL_DECODE, False)):
+        ctx = binding.Context(shape, max_seq=2176, max_block=64, flags=flags)
+        ctx.load_model(w, as_bf16_bits=True)
+        if scattered:
+            ctx.bd_kv_page_order(np.random.default_rng(6).permutation(2176 // 32).astype(np.int32))
+        names = _kernels_of(lambda: ctx.bd_prefill(e, i))
+        wide = {a[0] for a in _instances(names, "pf_attn_wide_kernel")}
+        one = {a[0] for a in _instances(names, "pf_attn_kernel")}
+        if flags == 0:
+            assert wide == {str(dim)} and one == (set() if first else {str(dim)}), (wide, one)
+        else:
+            assert not wide and not one
+        k, v = ctx.bd_read_kv(1, 0, rows)
+        res.append((k.clone(), v.clone(), ctx.bd_read_carry()))
+        ctx.bd_status()
+        ctx.close()
+    (k0, v0, c0), (k1, v1, c1), (k2, v2, c2) = res
+    assert torch.equal(k0, k1) and torch.equal(v0, v1) and c0 == c1
+    for a, b in ((k0, k2), (v0, v2)):
+        assert float((a - b).abs().max()) <= 2e-2 * float(b.abs().max())
+        assert float((a - b).norm()) <= 1.2e-2 * float(b.norm())
