@@ -146,10 +146,7 @@ int make_plan(bd_ctx* c) {
       if (!may_split || P.nwg % (ph.ksplit * 2) != 0) return false;
       ph.ksplit *= 2;
     }
-    const int groups = P.nwg / ph.ksplit;
-    if (N % 16 != 0) return false;
-    ph.RW = 16 * ceil_div(N / 16, groups);
-    return true;
+    return N % 16 == 0;
   };
   if (!set(PH_QKV, c->NQKV, c->H, false) || !set(PH_O, c->H, c->QD, false) || !set(PH_GU, 2 * c->F, c->H, false) ||
       !set(PH_DOWN, c->H, c->F, true) || !set(PH_LM, c->V, c->H, false))
@@ -157,7 +154,7 @@ int make_plan(bd_ctx* c) {
   // QKV and O: at most one tile per workgroup -> tile j on workgroup j / nwg-1-j (see MegaPlan::single)
   P.single = 0;
   for (int p : {PH_QKV, PH_O})
-    if (P.ph[p].ksplit == 1 && P.ph[p].N / 16 <= P.nwg) { P.single |= 1 << p; P.ph[p].RW = 16; }
+    if (P.ph[p].ksplit == 1 && P.ph[p].N / 16 <= P.nwg) P.single |= 1 << p;
   // Gate/up rows dealt out per XCD so that the SwiGLU output never leaves the XCD that produced it: needs the K slices
   // of the down projection to coincide with XCDs (workgroup b holds K slice b mod ksplit and runs on XCD b mod xcds).
   P.xcd_gu = 0;
@@ -169,9 +166,6 @@ int make_plan(bd_ctx* c) {
       P.ph[PH_DOWN].KS / P.ph[PH_DOWN].kgran >= c->xcds && (fp8 || P.ph[PH_DOWN].KS % c->xcds == 0)) {
     P.xcd_gu = c->xcds;
     P.gu_cut = fp8 ? 1 : 0;
-    int most = 0;
-    for (int g = 0; g < P.nwg; ++g) most = std::max(most, phase_tile0(P, PH_GU, g + 1) - phase_tile0(P, PH_GU, g));
-    P.ph[PH_GU].RW = 16 * most;
   }
   long long mx = 0;
   for (int wg = 0; wg < P.nwg; ++wg)
@@ -330,7 +324,7 @@ int forward(bd_ctx* c, int M, int mode, bool want_lm, const float* embeds, int n
             bool lm_only = false, int row0 = 0);
 
 // Rows of the large-M kernels' residual stream [0, M) to the final norm + LM head of the decode kernels (all of them,
-// or only the last one as row 0), and the clean-up afterwards.
+// or only the last one as row 0).
 int lm_head_of_rows(bd_ctx* c, const float* xrows, int M, int mode, bool skippable, int quad_B) {
   hipStream_t s = c->stream;
   const int ver = 2 * c->L, parts = phase_tiles(c->plan, PH_DOWN);
@@ -343,8 +337,6 @@ int lm_head_of_rows(bd_ctx* c, const float* xrows, int M, int mode, bool skippab
                        c->xb + (size_t)ver * c->xb_elems, ssq, parts, c->Mp_max, skip);
     BD_TRY(check_launch());
     BD_TRY(forward(c, rows, mode, true, nullptr, 0, nullptr, 0, nullptr, nullptr, nullptr, skippable, quad_B, true, r0));
-    hipLaunchKernelGGL(pf_clear_ssq_kernel, dim3(4), dim3(256), 0, s, ssq, parts, c->Mp_max, MT * 16, skip);
-    BD_TRY(check_launch());
   }
   c->last_rows = M;
   return BD_OK;

@@ -36,7 +36,6 @@ int launch_pf_gemm_pipe(hipStream_t s, PfGemmArgs a) {
                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     attr_set = true;
   }
-  static_assert(BKS <= 2, "turns of two k-steps");
   if (ODD ? a.SK != 1 || a.KS % 2 != 1 : a.SK < 1 || a.KS % (2 * a.SK) != 0) return BD_E_ARG;   // whole turns of the K loop per split
   a.RG = ceil_div(a.NT, 2 * WN);
   a.TG = ceil_div(a.MTc, 2 * TW);

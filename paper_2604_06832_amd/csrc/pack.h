@@ -216,14 +216,6 @@ __global__ __launch_bounds__(kPfThreads) void pf_rows_to_lm_kernel(const float* 
   for (int p = threadIdx.x; p < parts; p += kPfThreads) ssq[(size_t)p * Mp + m] = p == 0 ? (m < M ? t : 1.f) : 0.f;
 }
 
-// The decode kernels rely on the slots of the partial sums that no tile owns staying zero: clear what the hand-over
-// wrote once the LM head has read it.
-__global__ void pf_clear_ssq_kernel(float* __restrict__ ssq, int parts, int Mp, int rows, const DevState* st) {
-  if (st != nullptr && st->skip) return;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < parts * rows; i += gridDim.x * blockDim.x)
-    ssq[(size_t)(i / rows) * Mp + i % rows] = 0.f;
-}
-
 // One matrix into the tile-major fragment order of the prefill GEMMs (same row maps and column gains as the
 // weight stream of the decode kernels).  One-byte sources are e4m3 codes: every code is a bf16 value, so the copy is
 // exact; its row scales and the norm gains stay outside (accumulator epilogue, activation copy).

@@ -19,7 +19,6 @@ struct PhasePlan {
   int N;        // output rows of the phase (after fusing / interleaving); a multiple of 16
   int KS;       // k-steps
   int ksplit;   // workgroups that share an output row range and split K
-  int RW;       // rows of the largest row range (a multiple of 16)
   int kgran;    // k-steps per unit of the K split: 1 (bf16 weights) or 2 (fp8 weights: a 1-KiB fragment of 16 rows
                 // x 64 k holds two k-steps, so wavefront ranges start and end on even k-steps)
   int wbytes;   // bytes per streamed weight element: 2 (bf16) or 1 (e4m3)
@@ -172,8 +171,7 @@ struct MegaArgs {
                               // the norm-on-load GEMM phases read
   size_t xb_elems;
   float* ssq;                 // [2L+1][parts][Mp] partial sums of squares of each version
-  int ssq_parts;              // stride (parts) per version; version 0 has one part, odd versions one per
-                              // tile slot of the O phase, even versions one per tile slot of the DOWN phase
+  int ssq_parts;              // stride (parts) per version; version 0 has one part, the others one per 16-row tile (H / 16)
   int Mp;
   const float* gains;         // [2L+1][H]: attn_norm l, ffn_norm l, ..., final_norm
   int skippable;              // this launch belongs to a step that does nothing once the block is complete (DevState::skip)

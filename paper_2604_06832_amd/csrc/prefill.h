@@ -279,8 +279,8 @@ __global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs 
   constexpr int AT = 2 * WN, BT = 2 * TW;
   constexpr int AF = AT * BKS, TF = AF + BT * BKS;                  // weight fragments, all fragments of a stage
   constexpr int PER = (TF + 3) / 4;                                 // loads per wavefront and stage
-  constexpr int U = BKS > 2 ? BKS : 2;                              // k-steps per turn of the loop
-  static_assert(U % BKS == 0 && U % 2 == 0 && NST >= 3 && (!ODD || BKS == 1), "");
+  constexpr int U = 2;                                              // k-steps per turn of the loop
+  static_assert(U % BKS == 0 && NST >= 3 && (!ODD || BKS == 1), "");
   static_assert((NST - 2) * PER <= 63, "outstanding loads must fit the counter");
   extern __shared__ __attribute__((aligned(16))) char lds[];
   if (a.skippable && a.st->skip) return;

@@ -5,7 +5,7 @@
 // which a compute wavefront cannot also keep HBM busy.  So every workgroup (one per compute unit) runs
 // two kinds of wavefronts:
 //   * four PRODUCERS, one per consumer, that do nothing but copy their consumer's weight stream from HBM
-//     into a ring of 1-KiB slots in LDS with direct-to-LDS buffer loads (no registers involved).  The
+//     into a ring of 1-KiB slots in LDS, by way of registers that hold a further stretch of it.  The
 //     stream is the sequence of 16-row x 32-k MFMA A-operand fragments in exactly the order the consumer
 //     will multiply them, across all phases and layers, so the producer needs no knowledge of the
 //     computation: it runs ahead whenever a slot is free, through barriers and attention phases alike;
@@ -994,8 +994,6 @@ __device__ inline bool stream_attention_local(const MegaArgs& a, FwdCtx& fc, Fwd
   f32x4* sO = reinterpret_cast<f32x4*>(fc.share);                        // [4][DT][64]
   float* sm = reinterpret_cast<float*>(fc.share + kWavesPerWG * DT * 1024);   // [4][16]
   float* sl = sm + kWavesPerWG * 16;                                     // [4][16]
-  float* wgt = sl + kWavesPerWG * 16;                                    // [64 chunks][16]
-  float* s_inv = wgt + 64 * 16;                                          // [16]
 
   const int col = lane & 15, g = lane >> 4;
   const int n = fc.n;
@@ -1148,7 +1146,6 @@ __device__ inline bool stream_attention_local(const MegaArgs& a, FwdCtx& fc, Fwd
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   BD_ATS(5);
 #undef BD_ATS
-  (void)wgt; (void)s_inv;
   return true;
 }
 
