@@ -1246,8 +1246,8 @@ def test_large_m_prefill_agrees_with_the_chunked_one():
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 def test_large_m_tiles_over_chunk_sizes(dtype):
-    """Prompts whose chunks take every tile shape of the pipelined GEMMs and both attention kernels (edges of the token tiles,
-    ragged last tiles, a second chunk of few and of many rows) against the decode kernels, 32 or 64 rows at a time: keys and
+    """Prompts whose chunks take the tile shapes of chunks of 129 to 1024 rows (edges of the token tiles, ragged last
+    tiles, a second chunk of few and of many rows; all shapes: test_every_tile_shape_of_the_pipelined_gemms) against the decode kernels, 32 or 64 rows at a time: keys and
     values of the second layer, which depend on every phase of the first.  Bar: both sides round the same eight hand-overs per
     layer to bf16 (2^-9 each) around sums of another order, 2 layers: rms 2^-9 sqrt(2 * 16) < 0.012 of the result; largest of
     about 10^6 values, 8 rms, relative to the largest value (4 to 5 rms of the values): 2e-2 as in the test above."""
@@ -1274,6 +1274,48 @@ def test_large_m_tiles_over_chunk_sizes(dtype):
             assert float((a - b).abs().max()) <= 2e-2 * float(b.abs().max()), rows
             assert float((a - b).norm()) <= 1.2e-2 * float(b.norm()), rows
     for ctx in ctxs:
+        ctx.close()
+
+
+def test_every_tile_shape_of_the_pipelined_gemms():
+    """Quadratic steps of 56 to 1056 rows on the 3B-shaped layers take every tile shape of the pipelined GEMMs (K even: the
+    odd ones are held above), which the names of the launched kernels must show: logits of all rows against the register-staged
+    GEMMs, one tile shape per phase and no K splits.  Bar as in the test above: both sides round the same hand-overs around
+    sums of another order."""
+    shape = _wide(2, vocab=8192)
+    w = inputs.make_weights(shape, 4, "bf16", threads=8)
+    emb, ids = inputs.make_prompt(shape, 150, 60, seed=13)
+    ctxs = []
+    for flags in (0, binding.BD_FLAG_PREFILL_STAGED):
+        ctx = binding.Context(shape, max_seq=210 + 1056, max_block=64, flags=flags)
+        ctx.load_model(w, as_bf16_bits=True)
+        ctx.bd_debug_logits(True)
+        ctx.bd_prefill(torch.from_numpy(emb).cuda(), torch.from_numpy(ids).cuda())
+        ctxs.append(ctx)
+    taken = set()
+    for B in (7, 8, 10, 11, 14, 18, 21, 25, 30, 32):
+        rows = B * (B + 1)
+        _say(f"tile shapes: {rows} rows")
+        draft = torch.arange(40, 40 + B, dtype=torch.int32, device="cuda")
+        nxt = torch.zeros(B, dtype=torch.int32, device="cuda")
+        logits = []
+        for ctx in ctxs:
+            names = _kernels_of(lambda: ctx.bd_quad_step(B, draft, nxt))
+            logits.append(ctx.bd_read_logits(rows).clone())
+            ctx.bd_crop(210)
+            if ctx is ctxs[0]:
+                got = {a[:3] for a in _instances(names, "pf_gemm_pipe_kernel")}
+                assert len(got) == 4 and not _instances(names, "pf_gemm_kernel"), (B, got)
+                taken |= got
+            else:
+                assert len(_instances(names, "pf_gemm_kernel")) == 4
+        a, b = logits
+        assert float((a - b).abs().max()) <= 2e-2 * float(b.abs().max()), rows
+        assert float((a - b).norm()) <= 1.2e-2 * float(b.norm()), rows
+    want = {0: "1x1 1x2 3x2 5x2 5x4", 1: "1x2 1x4 2x4 4x1 4x2 4x4", 2: "3x2 3x3 3x4 6x4 6x6 11x4 11x6 11x8", 3: "1x2 1x3 1x4 4x2 8x2 8x3 8x4"}
+    assert taken == {(str(ph), *t.split("x")) for ph, l in want.items() for t in l.split()}, taken
+    for ctx in ctxs:
+        ctx.bd_status()
         ctx.close()
 
 
