@@ -455,12 +455,20 @@ __device__ inline void stream_gemm_phase(const MegaArgs& a, FwdCtx& fc, Ring& rg
     if (norm) {
       const int parts = ver == 0 ? 1 : P.H >> 4;
       const rsrc_t sr = make_rsrc(a.ssq + (size_t)ver * a.ssq_parts * a.Mp, (unsigned)(parts * a.Mp * 4));
-      const int so = ((wave * 4 + g) * a.Mp + col) * 4;      // (parts that do not exist read as zero: the whole offset is
-#pragma unroll                                               // in the vector offset, the only one the range check covers)
-      for (int u = 0; u < kSsqPer; ++u)
+      // (Parts that do not exist read as zero: the whole offset is in the vector offset, the only one the range check covers.
+      // How it is formed decides what the compiler keeps in registers: a running offset, pinned, with bf16 weights, 32 rows 2207 us a
+      // forward against 2217 with eight sums; the sums with e4m3, 2150 us against 2190.)
+      int so = ((wave * 4 + g) * a.Mp + col) * 4;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-          sv[mt][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, so + u * 16 * a.Mp * 4 + mt * 64, 0, 0));
+      for (int u = 0; u < kSsqPer; ++u) {
+        const int off = so + (FP8 ? u * 16 * a.Mp * 4 : 0);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) sv[mt][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, off + mt * 64, 0, 0));
+        if constexpr (!FP8) {
+          so += 16 * a.Mp * 4;
+          asm volatile("" : "+v"(so));
+        }
+      }
       asm volatile("" ::: "memory");
     }
     // activation fragments of this wavefront's k-steps: one round trip, straight into registers
