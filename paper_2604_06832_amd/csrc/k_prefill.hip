@@ -47,6 +47,9 @@ int launch_pf_gemm_pipe(hipStream_t s, PfGemmArgs a) {
 // Tile shapes of the pipelined GEMM: 32*WN rows x 32*TW tokens per workgroup, one workgroup per CU.  A shape's cost is the
 // number of rounds of the chip (32 CUs per XCD; a row group and its K splits stay on one XCD) times the time of one
 // round, measured on the phase's 3B shape (launches back to back, weights from HBM); the cheapest shape is taken.
+// (A round is a fixed part and a part per k-step, so the shapes' order could shift with K.  With both parts measured for every
+// shape the choice over chunks of 33 to 1056 rows would differ by 0.3 % of the products' time at hidden 256, 0.03 % from
+// hidden 1024 on.)
 constexpr int kXcds = 8, kXcdCUs = 32, kCUs = kXcds * kXcdCUs;     // (an MI355X in one piece)
 struct PfTile { int wn, tw; float us; };
 template <int N>

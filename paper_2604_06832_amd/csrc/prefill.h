@@ -266,12 +266,12 @@ __device__ inline void unrolled(F&& f) {
 // k-steps in LDS filled by direct loads, and the LDS reads of the next k-step issued between the products of the current one:
 // the fragment of row tile i is read again as soon as the products of row i are issued, those of the tokens go into a
 // second register set.  So neither LDS nor barrier is waited for while the matrix cores have work: the K loop of the
-// 352 x 256 tile takes 0.94 us per k-step (1.54 PFLOP/s over the chip on random data, 2.1 with zeros in LDS and no loads:
+// 352 x 256 tile takes 1.02 us per k-step (1.45 PFLOP/s over the chip on random data, 2.1 with zeros in LDS and no loads:
 // the clock follows the power), and more stages in flight change nothing.  What is left on top is fixed: launch, first loads and epilogue
-// take 18.6 us (gate/up, 352 x 256), 11.9 (down, 256 x 128 x four K splits), 7.9 (QKV, 160 x 64), 6.0 (O, 128 x 64).  Measured on
+// take 16.8 us (gate/up, 352 x 256), 10.0 (down, 256 x 128 x four K splits), 6.9 (QKV, 160 x 64), 5.8 (O, 128 x 64).  Measured on
 // the 3B shape (launches back to back) against kernels without the overlap of LDS reads and products (1024 rows: two stages, two
-// to four workgroups per CU; 72 rows: two token groups of 64): 1024 rows gate/up 82 us / 98, down 47 / 52, QKV 19.9 / 22.9,
-// O 16.8 / 16.7; 72 rows gate/up 21.7 / 33.4, down 14.0 / 25.1, QKV 9.8 / 10.2, O 6.3 / 9.0.
+// to four workgroups per CU; 72 rows: two token groups of 64): 1024 rows gate/up 81 us / 98, down 50 / 52, QKV 19.9 / 22.9,
+// O 17.1 / 16.7; 72 rows gate/up 20.5 / 33.4, down 15.7 / 25.1, QKV 8.1 / 10.2, O 5.8 / 9.0; 64 rows gate/up 18.9 / 19.7.
 // Needs whole turns of the loop per K split (ODD: one k-step more, with stages of one and no split).  With SK > 1 the workgroups of an output tile split K among them and
 // each leaves its product in its own slice of `part` (O and down phases), which the norm that follows adds.
 template <int PH, int WN, int TW, int BKS, int NST, bool ODD = false>

@@ -180,7 +180,7 @@ __device__ inline void attn_block_wide(KvBlock<D>& b, FK next_k, FV next_v, cons
 
 // pf_attn_kernel with JT query tiles of a head per workgroup: its four wavefronts share out the key blocks, and each block is
 // loaded once for JT tiles.  What bounds the kernel above on long contexts is that traffic: 16 KiB per block, tile and
-// wavefront, 29 TB/s out of the L2s at 1024 rows against 8192 keys, where it takes 151 us and this one 91 (JT = 2, two workgroups
+// wavefront, 27 TB/s out of the L2s for 1024 rows behind 7168 keys, where it takes 151 us and this one 92 (JT = 2, two workgroups
 // per CU; JT = 4 with one 106; two register buffers, one block ahead, 120).  Wavefront w merges tiles w, w + 4, ...  The workgroups
 // of a kv head run on the same XCDs where the number of kv heads divides theirs, so that its keys and values stay in those L2s.
 template <int D, int JT> constexpr int pf_attn_wide_lds() { return 4 * JT * ((D / 16) * 1024 + 2 * 64); }

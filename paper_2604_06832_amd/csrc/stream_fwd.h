@@ -414,9 +414,9 @@ __device__ inline void epilogue_residual(const MegaArgs& a, int ver, int token, 
 // The four phases run the same code with the phase as a runtime value: the loads of the activations, the walk over the
 // ring and the reduction are there once.  What that is for is the instruction cache (64 KiB for two compute units): every
 // hand-over is a chain in which a miss is not hidden by anything.  With a copy per phase, and the partition of the
-// rows evaluated in each (64-bit divisions, a fifth of all instructions), the kernel was 156 KB and missed its cache about
-// 180 times per layer; now 70 KB and 6 times.  The K ranges are summed once per round of 6 (one token tile) or 4 (two:
-// more accumulators spill) row tiles instead of once per pair.  One forward, 3B shape, 1024 keys: 1 row 2116 -> 1995 us,
+// rows evaluated in each (64-bit divisions, a fifth of all instructions), the kernel was 156 KB and missed its cache 195,000
+// times per forward by the profiler's count; now 70 KB and 4,700.  The K ranges are summed once per round of 6 (one token
+// tile) or 4 (two: more accumulators spill) row tiles instead of once per pair.  One forward, 3B shape, 1024 keys: 1 row 2116 -> 1995 us,
 // 32 rows 2422 -> 2211 us (two token tiles: rounds of 6 tiles 2442, of 2 tiles 2243).
 template <int MT, int D, bool FP8>
 __device__ inline void stream_gemm_phase(const MegaArgs& a, FwdCtx& fc, Ring& rg, FwdSync& sy, int ph, int wave, int lane_in) {
