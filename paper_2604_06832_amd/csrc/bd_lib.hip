@@ -224,14 +224,14 @@ int launch_forward_kernels(bd_ctx* c, int MT, MegaArgs& a, bool lm_only = false)
       a.local_gu = c->plan.xcd_gu > 0 ? 1 : 0;
       a.n_xcd = c->xcds;
       AttnLocalPlan lp;
-      a.attn_local = (!(c->cfg.flags & BD_FLAG_ATTENTION_KEY_SPLIT) &&
-                      attn_local_plan(c->plan.nwg, c->xcds, c->cfg.n_kv_heads, c->G * MT, lp)) ? 1 : 0;
+      const bool attn_local = !(c->cfg.flags & BD_FLAG_ATTENTION_KEY_SPLIT) &&
+                      attn_local_plan(c->plan.nwg, c->xcds, c->cfg.n_kv_heads, c->G * MT, lp);
       a.xbar = c->xbar; a.xbar_epoch = c->xbar_epoch;
       a.no_weights = (c->cfg.flags & BD_FLAG_MEASURE_NO_WEIGHTS) ? 1 : 0;
-      BD_TRY(launch_stream_fwd(c->stream, MT, c->D, c->fp8, quad, a));
+      BD_TRY(launch_stream_fwd(c->stream, MT, c->D, c->fp8, quad, attn_local, a));
       c->bar_epoch += (a.local_gu ? 4u : 5u) * (unsigned)c->L;
-      c->xbar_epoch += (unsigned)((a.local_gu ? 1 : 0) + (a.attn_local ? 1 : 0)) * (unsigned)c->L;
-      a.local_gu = 0; a.attn_local = 0;
+      c->xbar_epoch += (unsigned)((a.local_gu ? 1 : 0) + (attn_local ? 1 : 0)) * (unsigned)c->L;
+      a.local_gu = 0;
     } else {
       if (c->fp8) return BD_E_ARG;                           // e4m3 weights are only streamed by the kernel above
       BD_TRY(launch_mega_fwd(c->stream, MT, c->D, quad, a));

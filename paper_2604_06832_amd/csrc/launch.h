@@ -37,8 +37,9 @@ inline int check_launch() {
   return BD_OK;
 }
 
-// k_stream.hip: the forward kernel with decoupled weight streaming, forwards of up to 32 rows (MT = 1, 2).
-int launch_stream_fwd(hipStream_t s, int MT, int D, bool fp8, bool quad, const MegaArgs& a);
+// k_stream.hip: the forward kernel with decoupled weight streaming, forwards of up to 32 rows (MT = 1, 2);
+// attn_local: the attention stays inside each XCD (attn_plan.h; else its keys are split over the chip).
+int launch_stream_fwd(hipStream_t s, int MT, int D, bool fp8, bool quad, bool attn_local, const MegaArgs& a);
 // Writes the XCD id of every workgroup of a launch shaped like the streaming forward kernel's to dev_out[nwg].
 int launch_xcc_probe(hipStream_t s, int nwg, unsigned* dev_out);
 

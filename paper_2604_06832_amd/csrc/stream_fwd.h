@@ -42,7 +42,7 @@ template <int MT> constexpr int round_tiles() { return MT == 1 ? 6 : 4; }
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 // words of the LDS synchronisation block
-enum { SY_LANDED = 0, SY_CONSUMED = 4, SY_DEAD = 8, SY_CBAR = 9, SY_ARRIVE = 10, SY_EPOCH = 11, SY_XEPOCH = 12, SY_WORDS = 16 };
+enum { SY_LANDED = 0, SY_CONSUMED = 4, SY_DEAD = 8, SY_CBAR = 9, SY_ARRIVE = 10, SY_EPOCH = 11, SY_XEPOCH = 12, SY_PACE = 13, SY_WORDS = 16 };
 
 __device__ inline unsigned lds_addr(const void* p) {
   return (unsigned)(size_t)(const __attribute__((address_space(3))) char*)p;
@@ -51,6 +51,13 @@ __device__ inline unsigned lds_ld32(unsigned addr) {
   unsigned v;
   asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v) : "v"(addr) : "memory");
   return (unsigned)__builtin_amdgcn_readfirstlane((int)v);
+}
+// Two words in one round trip.
+__device__ inline void lds_ld32_pair(unsigned addr0, unsigned addr1, unsigned& v0, unsigned& v1) {
+  unsigned a, b;
+  asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(a), "=v"(b) : "v"(addr0), "v"(addr1) : "memory");
+  v0 = (unsigned)__builtin_amdgcn_readfirstlane((int)a);
+  v1 = (unsigned)__builtin_amdgcn_readfirstlane((int)b);
 }
 __device__ inline void lds_st32(unsigned addr, unsigned v) {
   asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(v) : "memory");
@@ -104,7 +111,7 @@ __device__ inline void cbar(FwdSync& sy, int lane, DevState* st) {
 // HBM -> stash register -> ring slot, the stash being a circular buffer of NS / 4 groups of four fragments between the
 // two (fragment f in entry f mod NS).  Filling and draining advance independently: a group is moved to the ring as
 // soon as the ring has room (at LDS speed, whatever is in flight), and groups are re-loaded at a bounded rate (a token
-// bucket on the 100 MHz clock: kStashTicks per fragment, bursts of up to kStashBurst), so that the deep look-ahead
+// bucket on the 100 MHz clock, its rate a word the consumers write, see StreamPace), so that the deep look-ahead
 // never shows up as a deep queue in front of the latency-critical loads of the hand-overs.
 // Stash entries are registers and can only be named statically, so the loop sweeps over the groups: at group k it
 // moves group k if that is the next to move, then re-loads it if it is the next to load.  The loads are issued from
@@ -112,27 +119,31 @@ __device__ inline void cbar(FwdSync& sy, int lane, DevState* st) {
 // register can only be a wait for everything): vector-memory loads return in order, hence the group with y younger
 // loads behind it has landed once at most y are outstanding.  The build checks that the compiler keeps the entries in
 // place (no copy or spill of a register whose load may still be in flight) between the two markers below.
-#ifndef BD_STASH
-#define BD_STASH 48
-#endif
-#ifndef BD_STASH_TICKS
-#define BD_STASH_TICKS 30
-#endif
-constexpr int kStash = BD_STASH;                 // fragments a producer keeps in registers (4 registers each)
+constexpr int kStash = 48;                       // fragments a producer keeps in registers (4 registers each)
 constexpr int kStashGroup = 4;                   // fragments moved or requested per step
-constexpr unsigned kStashTicks = BD_STASH_TICKS; // 10-ns ticks per fragment of the background pace (1 KiB / 300 ns = 3.4 GB/s a wavefront: a layer needs 2.5)
-#ifndef BD_STASH_TICKS_FAST
-#define BD_STASH_TICKS_FAST 10
-#endif
-#ifndef BD_STASH_LOW
-#define BD_STASH_LOW 24
-#endif
-constexpr unsigned kStashTicksFast = BD_STASH_TICKS_FAST;   // pace while the consumer is about to run dry
-constexpr int kStashLow = BD_STASH_LOW;          // "about to run dry": at most this many fragments requested and not yet consumed
-#ifndef BD_STASH_BURST
-#define BD_STASH_BURST 16
-#endif
-constexpr unsigned kStashBurst = BD_STASH_BURST;  // fragments that may be requested back to back
+
+// Pace of the requests, in 10-ns ticks per fragment (1 KiB) of a wavefront, by what the consumers are at.  A request in flight
+// delays the hand-over beside it (the loads and stores of a CU queue behind each other), a request not made delays a
+// later product.  HBM gives every wavefront 1 KiB per 16 ticks when all ask; a layer needs 150 fragments (bf16, 3B shape) in some
+// 5200 ticks, 96 of them in gate/up, and ring and stash hold 72.  So the stash is refilled while attention and O run, gate/up and
+// down request at a rate HBM can follow, and the requests nearly stop behind the last product of down.  With one rate throughout
+// (30 ticks, 10 while at most 24 fragments were buffered) the fast one fell on the down projection's cross-workgroup sum, a chain of
+// far round trips, although nothing is urgent between it and the next gate/up: 3B shape, 1024 keys, the down phase took 15.3 us
+// a layer at 32 rows, now 11.9.  The values are the best of a random search over all of them, whole forwards timed, and flat
+// around the optimum.  One forward before and after: 4 rows 1959 -> 1875 us, 32 rows 2151 -> 2003; e4m3 (half the fragments), 333
+// keys, 32 rows 2031 -> 1968.  With e4m3 and one token tile there is so little to request that the one rate stays (1570 us, with a
+// rate per phase 1584: the kernel's registers spill over it).
+struct StreamPace {
+  unsigned qkv, attn, o, gu, gu_end, down, down_end;   // from the phase's start; from the last product of gate/up and of down on
+  unsigned low, low_ticks;                             // at most `low` fragments requested and not yet consumed: at least this pace
+  unsigned burst;                                      // fragments that may be requested back to back
+};
+template <int MT, bool FP8> constexpr bool stream_paced() { return !(FP8 && MT == 1); }
+template <int MT, bool FP8> constexpr StreamPace stream_pace() {
+  if (!stream_paced<MT, FP8>()) return StreamPace{30, 30, 30, 30, 30, 30, 30, 24, 10, 16};
+  if (FP8) return StreamPace{70, 40, 24, 22, 40, 11, 120, 16, 14, 8};
+  return MT == 1 ? StreamPace{44, 36, 20, 26, 32, 12, 150, 16, 14, 24} : StreamPace{56, 36, 20, 26, 26, 14, 90, 12, 14, 24};
+}
 static_assert(kStash % kStashGroup == 0 && kSlots % kStashGroup == 0, "whole groups");
 
 __device__ inline unsigned clock_ticks() { return (unsigned)wall_clock64(); }
@@ -146,9 +157,10 @@ __device__ inline void wait_for_loads(unsigned younger) {
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-template <int NS>
+template <int NS, int MT, bool FP8>
 __device__ inline void producer_loop_stash(const MegaArgs& a, int cw, char* ring, unsigned sync_base, int lane) {
   constexpr int NG = NS / kStashGroup;
+  constexpr StreamPace kPace = stream_pace<MT, FP8>();
   const MegaPlan& P = a.P;
   // (everything the inline assembly takes in scalar registers is made uniform explicitly)
   const unsigned total = (unsigned)__builtin_amdgcn_readfirstlane(a.wtab[blockIdx.x * kWavesPerWG + cw].frags);
@@ -159,24 +171,24 @@ __device__ inline void producer_loop_stash(const MegaArgs& a, int cw, char* ring
   const rsrc_t wr = make_rsrc(reinterpret_cast<const void*>(((size_t)whi << 32) | wlo), total * 1024u);
   const unsigned landed_addr = sync_base + (SY_LANDED + cw) * 4;
   const unsigned consumed_addr = sync_base + (SY_CONSUMED + cw) * 4;
-  const unsigned dead_addr = sync_base + SY_DEAD * 4;
+  const unsigned dead_addr = sync_base + SY_DEAD * 4, pace_addr = sync_base + SY_PACE * 4;
   bf16x8 st[NS];
 #pragma unroll
   for (int i = 0; i < NS; ++i) st[i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
   unsigned issued = 0, moved = 0, consumed = 0;     // fragments (multiples of the group size)
   int fill_g = 0, move_g = 0;                       // stash groups of fragment `issued` / fragment `moved`
   int slot = 0, spins = 0;
-  unsigned t_mark = clock_ticks() - kStashBurst * kStashTicksFast;   // start with a full bucket
+  unsigned t_mark = clock_ticks() - kPace.burst * kPace.qkv;   // start with a full bucket
   const bool no_w = __builtin_amdgcn_readfirstlane(a.no_weights) != 0;   // measurement only: everything but the loads
   asm volatile("; BD_STASH_BEGIN" ::: "memory");
   while (moved < total_up) {
-    // pace of the requests: the background pace while the consumer has plenty buffered, the demand pace once it is
-    // about to run dry (what is buffered is what was requested and not yet consumed)
     const unsigned now = clock_ticks();
-    consumed = lds_ld32(consumed_addr);
-    const unsigned ticks = (issued - consumed <= (unsigned)kStashLow) ? kStashTicksFast : kStashTicks;
+    unsigned pace = kPace.qkv;
+    if constexpr (stream_paced<MT, FP8>()) lds_ld32_pair(consumed_addr, pace_addr, consumed, pace);
+    else consumed = lds_ld32(consumed_addr);
+    const unsigned ticks = issued - consumed <= kPace.low ? min(pace, kPace.low_ticks) : pace;
     unsigned tokens = (now - t_mark) / ticks;
-    if (tokens > kStashBurst || no_w) { tokens = kStashBurst; t_mark = now - kStashBurst * ticks; }
+    if (tokens > kPace.burst || no_w) { tokens = kPace.burst; t_mark = now - kPace.burst * ticks; }
     bool progress = false;
 #pragma unroll
     for (int k = 0; k < NG; ++k) {
@@ -443,6 +455,9 @@ __device__ inline void stream_gemm_phase(const MegaArgs& a, FwdCtx& fc, Ring& rg
     if (a.trace2 != nullptr && fc.layer == 1 && threadIdx.x == 0) a.trace2[(size_t)blockIdx.x * 64 + ph * 12 + (k)] = wall_clock64(); \
   } while (0)
   BD_SUBTS2(0);
+  constexpr StreamPace kPace = stream_pace<MT, FP8>();
+  if (stream_paced<MT, FP8>() && wave == 0)
+    lds_st32(sy.base + SY_PACE * 4, ph == PH_GU ? kPace.gu : ph == PH_DOWN ? kPace.down : ph == PH_O ? kPace.o : kPace.qkv);
   if (n_tiles > 0) {
     const bool norm = ph == PH_QKV || ph == PH_GU;
     const int ver = 2 * fc.layer + (ph == PH_GU ? 1 : 0);
@@ -527,6 +542,7 @@ __device__ inline void stream_gemm_phase(const MegaArgs& a, FwdCtx& fc, Ring& rg
           else if (kT * c < nt) consume_chunk<MT, false, FP8>(rg, sy, xk, steps, acc[c], lane);
         }
       }
+      if (stream_paced<MT, FP8>() && wave == 0 && t0 + kRound >= n_tiles && ph >= PH_GU) lds_st32(sy.base + SY_PACE * 4, ph == PH_GU ? kPace.gu_end : kPace.down_end);
       BD_SUBTS2(3);
       // The operands fetched for the epilogue are taken here, before its first store: the vector-memory counter is
       // in order, so a wait for them placed behind a write-through store would also wait for that store's
@@ -1244,7 +1260,11 @@ __device__ inline bool stream_xcd_barrier(const MegaArgs& a, FwdSync& sy, unsign
 // ---- the kernel ------------------------------------------------------------------------------------------------
 template <int MT> constexpr int stream_lds_bytes() { return kWavesPerWG * kRingBytes + kShareBytes; }
 
-template <int MT, int D, bool FP8, bool QUAD = false>
+// LOCAL: the attention that stays inside each XCD, else the chip-wide key split.  One of them per instantiation: with both
+// compiled in the kernel was 70 KB with 376 B of scratch per lane, with one 52 KB and 80 B (3B shape, 1024 keys, 32 rows: a
+// forward 2151 us, with one 2139; up to 16 rows 1970 and 1962; e4m3, 32 rows, 333 keys 2031 and 2064, for the better with the
+// pace per phase above).
+template <int MT, int D, bool FP8, bool QUAD, bool LOCAL>
 __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) {
   constexpr int kRound = round_tiles<MT>();
   static_assert(kWavesPerWG * kRound * MT * 1024 <= kShareBytes, "K-reduction buffers exceed the shared region");
@@ -1257,16 +1277,16 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
   __shared__ int4 s_plan[PH_LM * kWavesPerWG];
   const MegaPlan& P = a.P;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (threadIdx.x < SY_WORDS) s_sync[threadIdx.x] = 0u;
+  if (threadIdx.x < SY_WORDS) s_sync[threadIdx.x] = threadIdx.x == SY_PACE ? stream_pace<MT, FP8>().qkv : 0u;
   if (threadIdx.x < PH_LM * kWavesPerWG)
     s_plan[threadIdx.x] = a.wtab[blockIdx.x * kWavesPerWG + threadIdx.x % kWavesPerWG].ph[threadIdx.x / kWavesPerWG];
   if (threadIdx.x == 0) {
     int go = (a.st->error == 0);
     if (go && a.skippable && a.st->skip) {
-      skip_barriers(a.bar, a.xbar, (a.local_gu ? 4u : 5u) * (unsigned)P.L, ((a.local_gu ? 1u : 0u) + (a.attn_local ? 1u : 0u)) * (unsigned)P.L);
+      skip_barriers(a.bar, a.xbar, (a.local_gu ? 4u : 5u) * (unsigned)P.L, ((a.local_gu ? 1u : 0u) + (LOCAL ? 1u : 0u)) * (unsigned)P.L);
       go = 0;
     }
-    if (go && (a.local_gu || a.attn_local) && xcc_id() != blockIdx.x % 8u) {   // the XCD-local hand-overs would be unsafe
+    if (go && (a.local_gu || LOCAL) && xcc_id() != blockIdx.x % 8u) {   // the XCD-local hand-overs would be unsafe
       __hip_atomic_store(&a.st->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       go = 0;
     }
@@ -1278,7 +1298,7 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
 
   if (wave >= kWavesPerWG) {
     const int cw = wave - kWavesPerWG;
-    producer_loop_stash<kStash>(a, cw, lds + cw * kRingBytes, sync_base, lane);
+    producer_loop_stash<kStash, MT, FP8>(a, cw, lds + cw * kRingBytes, sync_base, lane);
     return;
   }
 
@@ -1315,7 +1335,8 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
     for (int step = 0; step < 5; ++step) {
       asm volatile("" : "+s"(step));
       if (step == 1) {
-        if (a.attn_local) {
+        if (stream_paced<MT, FP8>() && wave == 0) lds_st32(sync_base + SY_PACE * 4, stream_pace<MT, FP8>().attn);
+        if constexpr (LOCAL) {
           alive = stream_attention_local<D, QUAD>(a, fc, sy, ++xepoch, wave, lane);
           if (!alive) break;
         } else {
