@@ -525,7 +525,7 @@ int bd_create(const bd_config* cfg, void* hip_stream, bd_ctx** out) {
   c->max_kb = ceil_div(k.max_seq, 32);
   // Large-M kernels for contexts whose cache can hold a chunk of 128 rows plus the prompt's last rows.
   c->pf_on = k.max_seq > kPfTokens && !(k.flags & BD_FLAG_PREFILL_DECODE);
-  c->pf_rows = c->pf_on ? std::min(1024, (k.max_seq - 1) / kPfTokens * kPfTokens) : 0;
+  c->pf_rows = c->pf_on ? std::min(k.max_seq >= kPfLongContext ? kPfChunkRows : kPfShortRows, (k.max_seq - 1) / kPfTokens * kPfTokens) : 0;
   {
     // the largest quadratic forward of this context: B (B + 1) rows for B = min(max_block, 32), if the cache can hold them
     const int Bq = std::min(k.max_block, kQuadMaxB);

@@ -53,7 +53,7 @@ int launch_pf_gemm_pipe(hipStream_t s, PfGemmArgs a) {
 constexpr int kXcds = 8, kXcdCUs = 32, kCUs = kXcds * kXcdCUs;     // (an MI355X in one piece)
 struct PfTile { int wn, tw; float us; };
 template <int N>
-int pick_tile(const PfTile (&t)[N], int NT, int MTc, int SK) {
+int pick_tile(const PfTile (&t)[N], int NT, int MTc, int SK, float* best_cost = nullptr) {
   int best = 0;
   float cost = 0.f;
   for (int i = 0; i < N; ++i) {
@@ -61,17 +61,20 @@ int pick_tile(const PfTile (&t)[N], int NT, int MTc, int SK) {
     const float c = (float)ceil_div(per_xcd, kXcdCUs) * t[i].us;
     if (i == 0 || c < cost) { best = i; cost = c; }
   }
+  if (best_cost != nullptr) *best_cost = cost;
   return best;
 }
 
 int launch_qkv(hipStream_t s, const PfGemmArgs& a) {
-  static constexpr PfTile t[] = {{1, 1, 8.3f}, {1, 2, 9.9f}, {3, 2, 13.8f}, {5, 2, 20.f}, {5, 4, 28.f}};
+  static constexpr PfTile t[] = {{1, 1, 8.3f}, {1, 2, 9.9f}, {3, 2, 13.8f}, {5, 2, 20.f}, {5, 4, 28.f}, {5, 8, 52.f}, {10, 8, 88.f}};
   switch (pick_tile(t, a.NT, a.MTc, 1)) {
     case 0: return launch_pf_gemm_pipe<PH_QKV, 1, 1, 2, 12>(s, a);
     case 1: return launch_pf_gemm_pipe<PH_QKV, 1, 2, 2, 12>(s, a);
     case 2: return launch_pf_gemm_pipe<PH_QKV, 3, 2, 2, 6>(s, a);
     case 3: return launch_pf_gemm_pipe<PH_QKV, 5, 2, 2, 5>(s, a);
-    default: return launch_pf_gemm_pipe<PH_QKV, 5, 4, 2, 4>(s, a);
+    case 4: return launch_pf_gemm_pipe<PH_QKV, 5, 4, 2, 4>(s, a);
+    case 5: return launch_pf_gemm_pipe<PH_QKV, 5, 8, 1, 5>(s, a);
+    default: return launch_pf_gemm_pipe<PH_QKV, 10, 8, 1, 4>(s, a);
   }
 }
 int launch_o(hipStream_t s, const PfGemmArgs& a) {
@@ -83,11 +86,13 @@ int launch_o(hipStream_t s, const PfGemmArgs& a) {
       default: return launch_pf_gemm_pipe<PH_O, 2, 4, 2, 6>(s, a);
     }
   }
-  static constexpr PfTile t[] = {{4, 1, 12.f}, {4, 2, 16.7f}, {4, 4, 23.f}};
+  static constexpr PfTile t[] = {{4, 1, 12.f}, {4, 2, 16.7f}, {4, 4, 23.f}, {4, 8, 44.f}, {8, 8, 70.f}};
   switch (pick_tile(t, a.NT, a.MTc, 1)) {
     case 0: return launch_pf_gemm_pipe<PH_O, 4, 1, 2, 6>(s, a);
     case 1: return launch_pf_gemm_pipe<PH_O, 4, 2, 2, 6>(s, a);
-    default: return launch_pf_gemm_pipe<PH_O, 4, 4, 2, 4>(s, a);
+    case 2: return launch_pf_gemm_pipe<PH_O, 4, 4, 2, 4>(s, a);
+    case 3: return launch_pf_gemm_pipe<PH_O, 4, 8, 1, 5>(s, a);
+    default: return launch_pf_gemm_pipe<PH_O, 8, 8, 1, 4>(s, a);
   }
 }
 int launch_gu(hipStream_t s, const PfGemmArgs& a) {
@@ -113,9 +118,10 @@ int launch_gu(hipStream_t s, const PfGemmArgs& a) {
     default: return launch_pf_gemm_pipe<PH_GU, 11, 8, 1, 4>(s, a);
   }
 }
-int launch_down(hipStream_t s, const PfGemmArgs& a) {
-  static constexpr PfTile t[] = {{1, 2, 12.4f}, {1, 3, 13.9f}, {1, 4, 15.5f}, {4, 2, 19.5f}, {8, 2, 30.f}, {8, 3, 38.5f}, {8, 4, 47.f}};
-  switch (pick_tile(t, a.NT, a.MTc, a.SK)) {
+constexpr PfTile kDownTiles[] = {{1, 2, 12.4f}, {1, 3, 13.9f}, {1, 4, 15.5f}, {4, 2, 19.5f}, {8, 2, 30.f}, {8, 3, 38.5f}, {8, 4, 47.f}};
+int launch_down(hipStream_t s, const PfGemmArgs& a, bool wide) {
+  if (wide) return launch_pf_gemm_pipe<PH_DOWN, 8, 8, 1, 4>(s, a);
+  switch (pick_tile(kDownTiles, a.NT, a.MTc, a.SK)) {
     case 0: return launch_pf_gemm_pipe<PH_DOWN, 1, 2, 2, 12>(s, a);
     case 1: return launch_pf_gemm_pipe<PH_DOWN, 1, 3, 2, 9>(s, a);
     case 2: return launch_pf_gemm_pipe<PH_DOWN, 1, 4, 2, 7>(s, a);
@@ -124,6 +130,34 @@ int launch_down(hipStream_t s, const PfGemmArgs& a) {
     case 5: return launch_pf_gemm_pipe<PH_DOWN, 8, 3, 1, 6>(s, a);
     default: return launch_pf_gemm_pipe<PH_DOWN, 8, 4, 1, 5>(s, a);
   }
+}
+
+// K splits (at most kPfSplit) that divide n_it pipeline iterations evenly.
+int k_split(int n_it) {
+  for (int sk = kPfSplit; sk > 1; --sk)
+    if (n_it % sk == 0) return sk;
+  return 1;
+}
+
+// K splits of the down projection, and whether it runs on 256 x 256 tiles.  Those do 1.4 PFLOP/s in the K loop against 1.0 of
+// 256 x 128, but need more rows, or fewer splits, to fill the chip: a round of them is 17 us and 0.78 us per k-step.  A split costs its
+// partial sums besides, written here and read by the norm (1 KiB a tile, both at about 4 TB/s).  3B shape, 4096 rows: two splits on
+// 256 x 256 152 us, four on 256 x 128 213; 2048 rows: four splits 84 and 107.
+int down_split(int KS, int NT, int MTc, bool& wide) {
+  const int sk0 = k_split(KS / 2);
+  auto parts = [&](int sk) { return sk > 1 ? (float)sk * (float)NT * (float)MTc * 5e-4f : 0.f; };
+  float cost = 0.f;
+  pick_tile(kDownTiles, NT, MTc, sk0, &cost);
+  cost += parts(sk0);
+  int best = sk0;
+  wide = false;
+  for (int sk = 1; sk <= kPfSplit; ++sk) {
+    if (KS % (2 * sk) != 0) continue;
+    const int per_xcd = ceil_div(ceil_div(NT, 16), kXcds) * ceil_div(MTc, 16) * sk;
+    const float c = (float)ceil_div(per_xcd, kXcdCUs) * (17.f + 0.78f * (float)(KS / sk)) + parts(sk);
+    if (c < cost) { best = sk; cost = c; wide = true; }
+  }
+  return best;
 }
 
 template <int D, int JT>
@@ -137,13 +171,6 @@ int launch_attn_wide(hipStream_t s, const PfAttnArgs& t) {
   }
   hipLaunchKernelGGL((pf_attn_wide_kernel<D, JT>), dim3(t.n_q * ceil_div(t.Mc / 16, JT)), dim3(256), lds, s, t);
   return check_launch();
-}
-
-// K splits (at most kPfSplit) that divide n_it pipeline iterations evenly.
-int k_split(int n_it) {
-  for (int sk = kPfSplit; sk > 1; --sk)
-    if (n_it % sk == 0) return sk;
-  return 1;
 }
 
 }  // namespace
@@ -266,8 +293,9 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
     g.NT = c.H / 16;
     // down: K split over workgroups (2048 output rows are too few tiles for the chip); the next norm adds the splits
     if (!c.staged && g.KS % 2 == 0) {
-      g.SK = k_split(g.KS / 2); g.part = g.SK > 1 ? c.part : nullptr;
-      BD_TRY(launch_down(s, g));
+      bool wide_tiles = false;
+      g.SK = down_split(g.KS, g.NT, MTc, wide_tiles); g.part = g.SK > 1 ? c.part : nullptr;
+      BD_TRY(launch_down(s, g, wide_tiles));
       parts = g.SK > 1 ? g.SK : 0;
       g.SK = 1; g.part = nullptr;
     } else {

@@ -2,7 +2,7 @@
 //
 // The decode kernels stream every weight once per forward of at most 64 rows, so a prompt of n tokens pushed
 // through them re-reads the model n/64 times.  For the bulk of the prompt this file provides the compute-bound
-// form: chunks of up to 1024 rows, each layer as a sequence of tiled MFMA GEMMs with the same fused epilogues as the
+// form: chunks of up to 8192 rows, each layer as a sequence of tiled MFMA GEMMs with the same fused epilogues as the
 // decode path (RMS factor, rotary + Q store + K/V store; residual add; SwiGLU) and a causal attention kernel that
 // walks the packed cache with the decode path's per-block routine.  Only the LM head, needed for the last row alone,
 // is the decode path's.
@@ -48,32 +48,33 @@ __device__ inline void pf_epilogue(const PfGemmArgs& a, f32x4 (&acc)[WN][TW], co
   const float* ep_rs = ep + 2 * WN * 16 + wm * TW * 16 + col;
   auto scale = [&](int i) { return *reinterpret_cast<const f32x4*>(ep + (wn * WN + i) * 16 + 4 * g); };   // of rows r .. r+3 of tile i
   if constexpr (PH == PH_QKV) {
+    // One token tile at a time, the (cos, sin) of the next one's rotary pairs requested ahead of this one's stores.  (All of them up
+    // front, 16 bytes per accumulator tile, spill at the largest tiles: 8192 rows on 320 x 256 159 us, in this form 99.)
     const int D = a.D, half = D >> 1;
     int key[TW];
-    f32x4 cs[WN][TW];                                          // (cos, sin) of the two rotary pairs
 #pragma unroll
-    for (int j = 0; j < TW; ++j) {
+    for (int j = 0; j < TW; ++j) key[j] = paged_key(a.pages, a.n0 + min((mtw + j) * 16 + col, a.Mvalid - 1));
+    f32x4 cs[2][WN];
+    auto fetch = [&](int j, f32x4 (&dst)[WN]) {
       const int tok = min((mtw + j) * 16 + col, a.Mvalid - 1);
-      key[j] = paged_key(a.pages, a.n0 + tok);
 #pragma unroll
       for (int i = 0; i < WN; ++i)
-        cs[i][j] = *reinterpret_cast<const f32x4*>(a.rope + (size_t)tok * half + ((((Tw + i) * 16 + 4 * g) % D) >> 1));
-    }
+        dst[i] = *reinterpret_cast<const f32x4*>(a.rope + (size_t)tok * half + ((((Tw + i) * 16 + 4 * g) % D) >> 1));
+    };
+    fetch(0, cs[0]);
+#pragma unroll
+    for (int j = 0; j < TW; ++j) asm volatile("" ::"v"(key[j]));
 #pragma unroll
     for (int j = 0; j < TW; ++j) {
-      asm volatile("" ::"v"(key[j]));
+      if (j + 1 < TW) fetch(j + 1, cs[(j + 1) & 1]);
 #pragma unroll
-      for (int i = 0; i < WN; ++i) asm volatile("" ::"v"(cs[i][j]));
-    }
+      for (int i = 0; i < WN; ++i) asm volatile("" ::"v"(cs[j & 1][i]));
+      const int token = (mtw + j) * 16 + col;
 #pragma unroll
-    for (int i = 0; i < WN; ++i) {
-      const int r = (Tw + i) * 16 + 4 * g;
-      if (Tw + i >= a.NT) continue;
-#pragma unroll
-      for (int j = 0; j < TW; ++j) {
-        const int token = (mtw + j) * 16 + col;
-        if (token >= a.Mvalid) continue;
-        const f32x4 v = acc[i][j] * scale(i) * ep_rs[j * 16], c = cs[i][j];
+      for (int i = 0; i < WN; ++i) {
+        const int r = (Tw + i) * 16 + 4 * g;
+        if (Tw + i >= a.NT || token >= a.Mvalid) continue;
+        const f32x4 v = acc[i][j] * scale(i) * ep_rs[j * 16], c = cs[j & 1][i];
         if (r < a.QD + a.KVD) {
           // rotary pairs: phase rows (2i, 2i+1) of a head hold dims (i, i + D/2)
           const uint32_t p0 = pack_bf16(v[0] * c[0] - v[1] * c[1], v[1] * c[0] + v[0] * c[1]);
@@ -90,7 +91,7 @@ __device__ inline void pf_epilogue(const PfGemmArgs& a, f32x4 (&acc)[WN][TW], co
           const int rv = r - a.QD - a.KVD;
           u16* vc = a.Vc + (size_t)(rv / D) * a.max_kb * 32 * D + vp_index(key[j], rv % D, D / 16);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) vc[e * 8] = f32_to_bf16_bits(v[e]);    // (four consecutive dims of one 16-dim tile)
+          for (int e = 0; e < 4; ++e) vc[e * 8] = f32_to_bf16_bits(v[e]);      // (four consecutive dims of one 16-dim tile)
         }
       }
     }

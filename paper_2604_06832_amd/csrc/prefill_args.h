@@ -7,6 +7,12 @@ namespace bd {
 constexpr int kPfTokens = 128;        // tokens per workgroup tile (8 token tiles of 16)
 constexpr int kPfThreads = 256;       // four wavefronts, 2 (rows) x 2 (tokens)
 constexpr int kPfSplit = 4;           // K splits of the down projection over workgroups
+// Rows of a prompt chunk.  The longer the chunk, the larger the tiles that still fill the chip in whole rounds, and a round's
+// fixed part (launch, first loads, epilogue) is paid less often: 3B shape, 8192 rows in chunks of 1024 71.5 ms, of 2048 62, of 4096
+// 59.2, in one 55.5; 3000 rows in chunks of 1024 23.8 ms, in one 20.5.  The working buffers take 75 KB a row, twice what a position of the cache
+// does, so a context that reserves fewer than 4096 positions keeps those of 1024 rows (77 MB).
+constexpr int kPfShortRows = 1024, kPfLongContext = 4096;
+constexpr int kPfChunkRows = 8192;
 
 struct PfGemmArgs {
   const bf16x8* w;        // fragments of this layer's phase, tile-major

@@ -203,7 +203,7 @@ __global__ __launch_bounds__(256, JT > 2 ? 1 : 2) void pf_attn_wide_kernel(PfAtt
     kvh = blockIdx.x / (G * TG);
     idx = blockIdx.x % (G * TG);
   }
-  const int head = kvh * G + idx % G, qt0 = (idx / G) * JT;    // (tiles past the last one repeat it and store nothing)
+  const int head = kvh * G + idx % G, qt0 = (TG - 1 - idx / G) * JT;   // (tiles past the last one repeat it and store nothing)
   const size_t kv_block = (size_t)32 * D / 8;
   const bf16x8* Kh = reinterpret_cast<const bf16x8*>(a.Kc) + (size_t)kvh * a.max_kb * kv_block;
   const bf16x8* Vh = reinterpret_cast<const bf16x8*>(a.Vc) + (size_t)kvh * a.max_kb * kv_block;

@@ -1319,6 +1319,34 @@ def test_every_tile_shape_of_the_pipelined_gemms():
         ctx.close()
 
 
+@pytest.mark.parametrize("rows,want", [
+    (2040, {("0", "5", "4"), ("1", "4", "4"), ("2", "11", "8"), ("3", "8", "8")}),     # four K splits of the down projection
+    (4083, {("0", "5", "8"), ("1", "4", "8"), ("2", "11", "8"), ("3", "8", "8")}),     # two
+    (8190, {("0", "10", "8"), ("1", "8", "8"), ("2", "11", "8"), ("3", "8", "8")})])   # none
+def test_tiles_of_chunks_of_up_to_8192_rows(rows, want):
+    """Prompts in one chunk on a context of more than 4096 positions: the tile shapes of the pipelined GEMMs (the names of the
+    launched kernels must show them), last tiles ragged; keys and values of the second layer against the decode kernels, 64
+    rows at a time.  Bars as above."""
+    shape = _wide(2, vocab=8192)
+    w = inputs.make_weights(shape, 4, "bf16", threads=8)
+    emb, ids = inputs.make_prompt(shape, rows - 700, 700, seed=15)
+    e, i = torch.from_numpy(emb).cuda(), torch.from_numpy(ids).cuda()
+    res = []
+    for flags in (0, binding.BD_FLAG_PREFILL_DECODE):
+        ctx = binding.Context(shape, max_seq=8320, max_block=64, flags=flags)
+        ctx.load_model(w, as_bf16_bits=True)
+        names = _kernels_of(lambda: ctx.bd_prefill(e, i))
+        if flags == 0:
+            assert {a[:3] for a in _instances(names, "pf_gemm_pipe_kernel")} == want
+        k, v = ctx.bd_read_kv(1, 0, rows)
+        res.append((k.clone(), v.clone()))
+        ctx.bd_status()
+        ctx.close()
+    for a, b in zip(*res):
+        assert float((a - b).abs().max()) <= 2e-2 * float(b.abs().max())
+        assert float((a - b).norm()) <= 1.2e-2 * float(b.norm())
+
+
 @pytest.mark.parametrize("heads,n_kv,dim,rows,first", [
     (16, 2, 128, 1000, True),          # one chunk: 63 tiles, the last of 8 rows
     (16, 2, 128, 1353, True),          # 1024 + 329 rows: 21 tiles, the last of 9 rows
