@@ -80,6 +80,7 @@ struct bd_ctx {
   bool pf_on = false; int pf_rows = 0;   // large-M kernels in use; rows of a prompt chunk
   int pf_cap = 0;                        // rows their working buffers hold: a prompt chunk, or the largest quadratic forward
   u16* pf_w = nullptr; size_t pf_layer_elems = 0; size_t pf_off[4] = {0, 0, 0, 0};
+  u16* pf_lm_w = nullptr; f32x4* pf_lm_stats = nullptr;   // LM head over more than 32 rows: tile-major weights, row groups' statistics
   float* pf_x = nullptr; u16* pf_xb = nullptr; float* pf_rs = nullptr; float2* pf_rope = nullptr;
   u16* pf_q = nullptr; u16* pf_ap = nullptr; u16* pf_act = nullptr;
   bool pf_staged = false;
@@ -354,12 +355,25 @@ int forward_large(bd_ctx* c, int M, int mode, bool want_lm, const float* embeds,
   if (p.block && (embeds != nullptr || n_embed != 0 || off != 0)) return BD_E_ARG;
   p.seed_tokens = seed_tokens; p.seed_mask = seed_mask; p.mask = mask;
   p.mode = mode; p.quad_W = quad_B > 0 ? quad_B + 1 : 0; p.skippable = skippable ? 1 : 0;
+  // (hidden sizes that are an odd multiple of 32 and the register-staged GEMMs keep the decode path's LM head)
+  const bool lm_large = want_lm && c->pf_lm_w != nullptr;
+  p.lm = lm_large;
   {
     Prof pr(c, KC_LAYERS);
     BD_TRY(launch_prefill_chunk(c->stream, p));
   }
   c->last_rows = M;
   c->last_had_logits = 0;
+  if (lm_large) {
+    Prof pr(c, KC_LMHEAD);
+    PfLm h{};
+    h.w = c->pf_lm_w; h.vocab = c->V; h.H = c->H; h.rows = M; h.xb = c->pf_xb; h.rs = c->pf_rs;
+    h.logits = c->logits_on ? c->logits : nullptr; h.stats = c->pf_lm_stats;
+    h.row_cand = c->row_cand; h.row_conf = c->row_conf; h.st = c->st; h.skippable = skippable ? 1 : 0;
+    BD_TRY(launch_lm_large(c->stream, h));
+    c->last_had_logits = c->logits_on ? 1 : 0;
+    return BD_OK;
+  }
   if (want_lm) BD_TRY(lm_head_of_rows(c, c->pf_x, M, mode, skippable, quad_B));
   return BD_OK;
 }
@@ -628,6 +642,10 @@ int bd_create(const bd_config* cfg, void* hip_stream, bd_ctx** out) {
       for (int ph = 0; ph < 4; ++ph) { c->pf_off[ph] = off; off += (size_t)NP[ph] * ceil_div(KP[ph], 32) * 32; }
       c->pf_layer_elems = off;
       A(c->pf_w, L * c->pf_layer_elems * 2);
+      if (c->H % 64 == 0 && !c->pf_staged) {
+        A(c->pf_lm_w, (size_t)c->V * c->H * 2);
+        A(c->pf_lm_stats, pf_lm_stats_elems(c->V, c->rows_max) * sizeof(f32x4));
+      }
       A(c->pf_x, R * c->H * 4);
       A(c->pf_xb, R * c->H * 2);
       A(c->pf_rs, R * 4);
@@ -771,8 +789,8 @@ int bd_load_weight(bd_ctx* c, const char* name, const void* host_ptr, size_t byt
         hipLaunchKernelGGL(pack_stream_kernel<u16>, dim3(4096), dim3(256), 0, c->stream, (const u16*)stage, rows, K,
                            c->plan, ph, std::max(layer, 0), row_base, row_map, c->D, col_gain, c->wstream);
       }
-      if (c->pf_on && !is_embed && ph >= 0 && ph != PH_LM) {
-        u16* dst = c->pf_w + (size_t)layer * c->pf_layer_elems + c->pf_off[ph];
+      if (c->pf_on && !is_embed && ph >= 0 && (ph != PH_LM || c->pf_lm_w != nullptr)) {
+        u16* dst = ph == PH_LM ? c->pf_lm_w : c->pf_w + (size_t)layer * c->pf_layer_elems + c->pf_off[ph];
         if (dtype == BD_F32)
           hipLaunchKernelGGL(pack_tiles_kernel<float>, dim3(4096), dim3(256), 0, c->stream, (const float*)stage, rows, K,
                              ceil_div(K, 32), row_base, row_map, c->D, col_gain, dst);

@@ -118,6 +118,21 @@ int launch_gu(hipStream_t s, const PfGemmArgs& a) {
     default: return launch_pf_gemm_pipe<PH_GU, 11, 8, 1, 4>(s, a);
   }
 }
+template <int WN, int TW, int BKS, int NST>
+int launch_lm_tile(hipStream_t s, PfGemmArgs a) {
+  static bool attr_set = false;
+  constexpr int lds = pf_gemm_pipe_lds<WN, TW, BKS, NST>();
+  static_assert(lds <= 160 * 1024 && WN >= kPfLmMinTiles, "");
+  if (!attr_set) {
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_lm_kernel<WN, TW, BKS, NST>), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    attr_set = true;
+  }
+  a.RG = ceil_div(a.NT, 2 * WN);
+  a.TG = ceil_div(a.MTc, 2 * TW);
+  hipLaunchKernelGGL((pf_lm_kernel<WN, TW, BKS, NST>), dim3(ceil_div(a.RG, 8) * 8 * a.TG), dim3(kPfThreads), lds, s, a);
+  return check_launch();
+}
+
 constexpr PfTile kDownTiles[] = {{1, 2, 12.4f}, {1, 3, 13.9f}, {1, 4, 15.5f}, {4, 2, 19.5f}, {8, 2, 30.f}, {8, 3, 38.5f}, {8, 4, 47.f}};
 int launch_down(hipStream_t s, const PfGemmArgs& a, bool wide) {
   if (wide) return launch_pf_gemm_pipe<PH_DOWN, 8, 8, 1, 4>(s, a);
@@ -302,11 +317,36 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
       BD_TRY((launch_pf_gemm<PH_DOWN, 2, 4, 2>(s, g, c.H)));
     }
   }
-  if (parts > 0) {
-    // the last layer's splits: the same kernel completes the residual stream (its other outputs are not used)
+  if (parts > 0 || c.lm) {
+    // the last layer's splits: the same kernel completes the residual stream (its other outputs serve the LM head over all rows)
     BD_TRY(norm(nullptr, c.part, parts));
   }
   return BD_OK;
+}
+
+// The LM head over the c.rows rows the last chunk left: logits (if asked for), argmax and its softmax probability per row.
+int launch_lm_large(hipStream_t s, const PfLm& c) {
+  PfGemmArgs g{};
+  g.MTc = ceil_div(c.rows, 16); g.Mvalid = c.rows; g.rs = c.rs; g.SK = 1; g.st = c.st; g.skippable = c.skippable;
+  g.w = reinterpret_cast<const bf16x8*>(c.w); g.NT = c.vocab / 16; g.KS = c.H / 32;
+  g.xin = reinterpret_cast<const bf16x8*>(c.xb);
+  g.logits = c.logits; g.stats = c.stats;
+  if (g.KS % 2 != 0) return BD_E_ARG;
+  static constexpr PfTile t[] = {{3, 2, 20.5f}, {3, 3, 22.f}, {3, 4, 24.f}, {6, 4, 31.f}, {6, 6, 39.f}, {11, 4, 49.f}, {11, 6, 62.f}, {11, 8, 81.f}};   // (gate/up's: the same K)
+  const int i = pick_tile(t, g.NT, g.MTc, 1);
+  switch (i) {
+    case 0: BD_TRY((launch_lm_tile<3, 2, 2, 7>(s, g))); break;
+    case 1: BD_TRY((launch_lm_tile<3, 3, 2, 6>(s, g))); break;
+    case 2: BD_TRY((launch_lm_tile<3, 4, 2, 5>(s, g))); break;
+    case 3: BD_TRY((launch_lm_tile<6, 4, 1, 6>(s, g))); break;
+    case 4: BD_TRY((launch_lm_tile<6, 6, 1, 5>(s, g))); break;
+    case 5: BD_TRY((launch_lm_tile<11, 4, 1, 5>(s, g))); break;
+    case 6: BD_TRY((launch_lm_tile<11, 6, 1, 4>(s, g))); break;
+    default: BD_TRY((launch_lm_tile<11, 8, 1, 4>(s, g))); break;
+  }
+  hipLaunchKernelGGL(pf_lm_fold_kernel, dim3(c.rows), dim3(kPfThreads), 0, s, c.stats, ceil_div(g.NT, 2 * t[i].wn), g.MTc * 16, c.row_cand, c.row_conf,
+                     c.skippable ? c.st : nullptr);
+  return check_launch();
 }
 
 }  // namespace bd

@@ -49,5 +49,7 @@ int launch_lm_head(hipStream_t s, int MT, const MegaArgs& a);
 
 // k_prefill.hip: one chunk of prompt rows through all layers with the large-M kernels.
 int launch_prefill_chunk(hipStream_t s, const PfChunk& c);
+// The LM head over all rows of the last chunk.
+int launch_lm_large(hipStream_t s, const PfLm& c);
 
 }  // namespace bd

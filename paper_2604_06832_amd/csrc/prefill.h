@@ -27,7 +27,7 @@ namespace bd {
 template <int AT, int BT> constexpr int pf_ep_bytes() { return (AT + BT) * 16 * 4; }
 template <int PH, int AT, int BT>
 __device__ inline void pf_ep_fetch(const PfGemmArgs& a, float* ep, int T0, int mt0) {
-  constexpr bool kNorm = PH == PH_QKV || PH == PH_GU;
+  constexpr bool kNorm = PH == PH_QKV || PH == PH_GU || PH == PH_LM;
   for (int i = threadIdx.x; i < AT * 16; i += kPfThreads) ep[i] = a.wscale != nullptr ? a.wscale[min(T0 * 16 + i, a.NT * 16 - 1)] : 1.f;
   if constexpr (kNorm)
     for (int i = threadIdx.x; i < BT * 16; i += kPfThreads) ep[AT * 16 + i] = a.rs[min(mt0 * 16 + i, a.MTc * 16 - 1)];
@@ -41,8 +41,8 @@ __device__ inline uint32_t pack_bf16(float lo, float hi) {
 // Epilogue of both GEMM kernels: lane (token column col, row quad g) of a 16 x 16 accumulator tile holds rows
 // r .. r+3 of one token.  The loads that remain (rotary factors, old residual values) precede the stores they go with.
 template <int PH, int WN, int TW>
-__device__ inline void pf_epilogue(const PfGemmArgs& a, f32x4 (&acc)[WN][TW], const float* ep, int T0, int mt0, int wn, int wm, int lane,
-                                   int kz = 0) {
+__device__ inline void pf_epilogue(const PfGemmArgs& a, f32x4 (&acc)[WN][TW], const float* ep, char* lds, int T0, int mt0, int wn, int wm,
+                                   int lane, int kz = 0) {
   const int col = lane & 15, g = lane >> 4;
   const int Tw = T0 + wn * WN, mtw = mt0 + wm * TW;            // this wavefront's first row tile, first token tile
   const float* ep_rs = ep + 2 * WN * 16 + wm * TW * 16 + col;
@@ -113,6 +113,53 @@ __device__ inline void pf_epilogue(const PfGemmArgs& a, f32x4 (&acc)[WN][TW], co
         const uint32_t h = pack_bf16(v[0] / (1.f + __expf(-v[0])) * v[1], v[2] / (1.f + __expf(-v[2])) * v[3]);
         __builtin_amdgcn_raw_buffer_store_b32(h, ar, Tw + i < a.NT && mtw + j < a.MTc ? off + j * 1024 : kOob, 0, 0);
       }
+    }
+  } else if constexpr (PH == PH_LM) {
+    // Logits of four vocabulary entries of a token per lane and tile; the largest one, its id and the sum of exponentials of the
+    // workgroup's rows, per token: in the lane, over the four row quads, over the two wavefronts that share the tokens (through
+    // the stages of the K loop, which nobody reads any more behind the barrier).
+    __syncthreads();
+    f32x4* st = reinterpret_cast<f32x4*>(lds);                   // [2 (row half)][2 * TW * 16 tokens]
+#pragma unroll
+    for (int j = 0; j < TW; ++j) {
+      const int token = (mtw + j) * 16 + col;
+      const float rs = ep_rs[j * 16];
+      float m = -INFINITY, s = 0.f;
+      int id = 0x7FFFFFFF;
+      f32x4 v[WN];
+#pragma unroll
+      for (int i = 0; i < WN; ++i) {
+        v[i] = acc[i][j] * rs;
+        if (Tw + i >= a.NT) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (v[i][e] > m || id == 0x7FFFFFFF) { m = v[i][e]; id = (Tw + i) * 16 + 4 * g + e; }   // (ascending ids: equal maxima keep the lower)
+      }
+#pragma unroll
+      for (int i = 0; i < WN; ++i) {
+        if (Tw + i >= a.NT) continue;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s += __expf(v[i][e] - m);
+        if (a.logits != nullptr && token < a.Mvalid)
+          *reinterpret_cast<f32x4*>(a.logits + (size_t)token * a.NT * 16 + (Tw + i) * 16 + 4 * g) = v[i];
+      }
+#pragma unroll
+      for (int off = 16; off < 64; off <<= 1) {
+        const float m2 = __shfl_xor(m, off);
+        const int i2 = __shfl_xor(id, off);
+        const float s2 = __shfl_xor(s, off);
+        stat_merge(m, id, s, m2, i2, s2);
+      }
+      if (g == 0) st[wn * (2 * TW * 16) + (wm * TW + j) * 16 + col] = f32x4{m, __int_as_float(id), s, 0.f};
+    }
+    __syncthreads();
+    const int T0g = T0 / (2 * WN), mt0 = mtw - wm * TW;
+    for (int t = threadIdx.x; t < 2 * TW * 16 && mt0 * 16 + t < a.MTc * 16; t += kPfThreads) {
+      const f32x4 p = st[t], q = st[2 * TW * 16 + t];
+      float m = p[0], s = p[2];
+      int id = __float_as_int(p[1]);
+      stat_merge(m, id, s, q[0], __float_as_int(q[1]), q[2]);
+      a.stats[(size_t)T0g * (a.MTc * 16) + mt0 * 16 + t] = f32x4{m, __int_as_float(id), s, 0.f};
     }
   } else if (a.part != nullptr) {
 #pragma unroll
@@ -237,7 +284,7 @@ __global__ __launch_bounds__(kPfThreads, (2 * (2 * WN * BKS * 64 + 2 * TW * BKS 
     __syncthreads();
   }
 
-  pf_epilogue<PH, WN, TW>(a, acc, ep, T0, mt0, wn, wm, lane);
+  pf_epilogue<PH, WN, TW>(a, acc, ep, lds, T0, mt0, wn, wm, lane);
 }
 
 // ---- the same product, pipelined: every phase whose K is a whole number of turns of its loop -----------------------------
@@ -275,8 +322,8 @@ __device__ inline void unrolled(F&& f) {
 // O 17.1 / 16.7; 72 rows gate/up 20.5 / 33.4, down 15.7 / 25.1, QKV 8.1 / 10.2, O 5.8 / 9.0; 64 rows gate/up 18.9 / 19.7.
 // Needs whole turns of the loop per K split (ODD: one k-step more, with stages of one and no split).  With SK > 1 the workgroups of an output tile split K among them and
 // each leaves its product in its own slice of `part` (O and down phases), which the norm that follows adds.
-template <int PH, int WN, int TW, int BKS, int NST, bool ODD = false>
-__global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs a) {
+template <int PH, int WN, int TW, int BKS, int NST, bool ODD>
+__device__ __forceinline__ void pf_gemm_pipe(const PfGemmArgs a) {
   constexpr int AT = 2 * WN, BT = 2 * TW;
   constexpr int AF = AT * BKS, TF = AF + BT * BKS;                  // weight fragments, all fragments of a stage
   constexpr int PER = (TF + 3) / 4;                                 // loads per wavefront and stage
@@ -310,6 +357,7 @@ __global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs 
     const int f = min(i * 4 + wave, TF - 1);
     if (f < AF) fo[i] = ((unsigned)min(T0 + f % AT, a.NT - 1) * a.KS + f / AT) * 1024u;
     else fo[i] = ((unsigned)((f - AF) / BT) * a.MTc + min(mt0 + (f - AF) % BT, a.MTc - 1)) * 1024u;
+    fo[i] = (unsigned)__builtin_amdgcn_readfirstlane((int)fo[i]);   // (uniform; the loads take it in a scalar register)
   }
   int s_issue = 0, itr = rot;                                       // slot and (rotated) iteration of the next stage to issue
   auto issue = [&]() {
@@ -385,7 +433,45 @@ __global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs 
     unrolled<WN>([&](auto i) { unrolled<TW>([&](auto j) { mfma_in_place<(i * TW + j < 64)>(acc[i][j], af[i], bf[0][j]); }); });
   asm volatile("s_nop 15\n\ts_nop 15\n\t; BD_ACC_END" ::: "memory");
   unrolled<WN>([&](auto i) { unrolled<TW>([&](auto j) { pin_acc<(i * TW + j < 64)>(acc[i][j]); }); });
-  pf_epilogue<PH, WN, TW>(a, acc, ep, T0, mt0, wn, wm, lane, kz);
+  pf_epilogue<PH, WN, TW>(a, acc, ep, lds, T0, mt0, wn, wm, lane, kz);
+}
+template <int PH, int WN, int TW, int BKS, int NST, bool ODD = false>
+__global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs a) {
+  pf_gemm_pipe<PH, WN, TW, BKS, NST, ODD>(a);
+}
+// LM head over all rows of a large forward, by the same loop: the weights are read once for up to 128 rows, where the decode
+// path's LM head takes 64 at a time and, at four token tiles, reads 3.3 TB/s.  3B shape, the fold below included: 64 rows 191 -> 127 us
+// (622 MB: 4.9 TB/s), 72 rows 310 -> 128, 210 rows 678 -> 178, 1056 rows 3035 -> 711.
+template <int WN, int TW, int BKS, int NST>
+__global__ __launch_bounds__(kPfThreads, 1) void pf_lm_kernel(PfGemmArgs a) {
+  pf_gemm_pipe<PH_LM, WN, TW, BKS, NST, false>(a);
+}
+// One workgroup per row: the row groups' statistics merged (equal maxima keep the lower id).
+__global__ __launch_bounds__(kPfThreads) void pf_lm_fold_kernel(const f32x4* __restrict__ stats, int RG, int stride, int* __restrict__ row_cand,
+                                                                float* __restrict__ row_conf, const DevState* st) {
+  __shared__ f32x4 part[kPfThreads / 64];
+  if (st != nullptr && st->skip) return;
+  const int r = blockIdx.x, lane = threadIdx.x & 63;
+  float m = -INFINITY, s = 0.f;
+  int id = 0x7FFFFFFF;
+  for (int p = threadIdx.x; p < RG; p += kPfThreads) {
+    const f32x4 v = stats[(size_t)p * stride + r];
+    stat_merge(m, id, s, v[0], __float_as_int(v[1]), v[2]);
+  }
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const float m2 = __shfl_xor(m, off);
+    const int i2 = __shfl_xor(id, off);
+    const float s2 = __shfl_xor(s, off);
+    stat_merge(m, id, s, m2, i2, s2);
+  }
+  if (lane == 0) part[threadIdx.x >> 6] = f32x4{m, __int_as_float(id), s, 0.f};
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kPfThreads / 64; ++w) stat_merge(m, id, s, part[w][0], __float_as_int(part[w][1]), part[w][2]);
+    row_cand[r] = id;
+    row_conf[r] = 1.f / s;
+  }
 }
 template <int WN, int TW, int BKS, int NST> constexpr int pf_gemm_pipe_lds() { return NST * (2 * WN + 2 * TW) * BKS * 1024 + pf_ep_bytes<2 * WN, 2 * TW>(); }
 

@@ -34,6 +34,8 @@ struct PfGemmArgs {
   int H, QD, KVD, D, n_q;
   const int* pages;       // page of every 32-key block of the cache (null: contiguous)
   const DevState* st; int skippable;   // nothing to do once the block is complete (DevState::skip)
+  float* logits;          // LM head: [rows][vocab], or null
+  f32x4* stats;           // LM head: [RG][MTc * 16] (largest logit, its id, sum of exp(logit - largest), -) of a row group's rows
 };
 
 struct PfAttnArgs {
@@ -60,6 +62,21 @@ struct PfAttnArgs {
 constexpr int kPfAttnChunks = BD_PF_ATTN_CHUNKS;   // key chunks per attention item in forwards of at most 64 rows
 constexpr int kPfAttnTiles = BD_PF_ATTN_TILES;     // query tiles of a head that share a workgroup (and its key/value loads) there
 
+// The LM head over all rows of the last chunk (k_prefill.hip): tile-major weights with the final norm's gain in them.
+struct PfLm {
+  const u16* w; int vocab, H;
+  int rows;
+  const u16* xb; const float* rs;         // packed bf16 rows and 1/rms, as the chunk's last norm left them
+  float* logits;                          // [rows][vocab], or null
+  f32x4* stats;                           // pf_lm_stats_elems(vocab, rows)
+  int* row_cand; float* row_conf;
+  const DevState* st; int skippable;
+};
+constexpr int kPfLmMinTiles = 3;          // a wavefront's row tiles in the smallest tile shape of the LM head
+inline size_t pf_lm_stats_elems(int vocab, int rows) {
+  return (size_t)ceil_div(vocab / 16, 2 * kPfLmMinTiles) * (size_t)(ceil_div(rows, 16) * 16);
+}
+
 // One chunk of rows through all layers (k_prefill.hip): plain pointers and sizes of the context.  The rows are prompt
 // rows (embeds / ids from row `off`), or, with `block` set, the tokens of a decode block (ids[0..rows), masked rows
 // taking the mask token, position 0 seeded from the carry like the prologue of the decode kernels does).
@@ -72,6 +89,7 @@ struct PfChunk {
   int mode;                       // BD_MODE_* among the chunk's rows (prompt chunks: causal)
   int quad_W;                     // > 0: rows are groups of quad_W tokens, row r at position n + r / W + r % W (Alg. 2)
   int skippable;
+  bool lm;                        // leave the bf16 copy and 1/rms of the last residual rows (for the LM head over all rows)
   const u16* table; int vocab, mask_id;
   int L, H, QD, KVD, NQKV, F, D, n_q, n_kv, max_kb;
   float rms_eps, rope_theta;

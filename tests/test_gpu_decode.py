@@ -1319,6 +1319,38 @@ def test_every_tile_shape_of_the_pipelined_gemms():
         ctx.close()
 
 
+@pytest.mark.parametrize("B,quad", [(33, False), (64, False), (9, True), (11, True), (14, True), (32, True)])
+def test_lm_head_over_all_rows_of_a_large_forward(B, quad):
+    """The LM head of forwards of more than 32 rows, vocabularies that end inside a workgroup's rows: ids and confidences against
+    the logits it stores (the id exactly, lowest of equals; the softmax in float64: 8208 exponentials of relative error 2^-21 and
+    a float32 sum, 1e-4 is ample), and the logits against the decode path's LM head behind the register-staged products (bar of
+    the tests below)."""
+    shape = _wide(2, vocab=8208)
+    w = inputs.make_weights(shape, 4, "bf16", threads=8)
+    emb, ids = inputs.make_prompt(shape, 100, 60, seed=16)
+    rows = B * (B + 1) if quad else B
+    res = []
+    for flags in (0, binding.BD_FLAG_PREFILL_STAGED):
+        ctx = binding.Context(shape, max_seq=160 + 1056, max_block=64, flags=flags)
+        ctx.load_model(w, as_bf16_bits=True)
+        ctx.bd_debug_logits(True)
+        ctx.bd_prefill(torch.from_numpy(emb).cuda(), torch.from_numpy(ids).cuda())
+        draft = torch.arange(40, 40 + B, dtype=torch.int32, device="cuda")
+        nxt = torch.zeros(B, dtype=torch.int32, device="cuda")
+        names = _kernels_of(lambda: ctx.bd_quad_step(B, draft, nxt) if quad else ctx.bd_verify_block(draft, False))
+        got = {a[:2] for a in _instances(names, "pf_lm_kernel")}
+        assert len(got) == (1 if flags == 0 else 0), got
+        res.append((ctx.bd_read_logits(rows).clone(), *[t.clone() for t in ctx.bd_read_rows(rows)]))
+        ctx.bd_status()
+        ctx.close()
+    (a, cand, conf), (b, _, _) = res
+    assert torch.equal(cand.long(), a.argmax(1))
+    want = torch.softmax(a.double(), 1).amax(1)
+    assert float((conf.double() / want - 1).abs().max()) <= 1e-4
+    assert float((a - b).abs().max()) <= 2e-2 * float(b.abs().max())
+    assert float((a - b).norm()) <= 1.2e-2 * float(b.norm())
+
+
 @pytest.mark.parametrize("rows,want", [
     (2040, {("0", "5", "4"), ("1", "4", "4"), ("2", "11", "8"), ("3", "8", "8")}),     # four K splits of the down projection
     (4083, {("0", "5", "8"), ("1", "4", "8"), ("2", "11", "8"), ("3", "8", "8")}),     # two
