@@ -849,6 +849,24 @@ int bd_prefill(bd_ctx* c, const float* dev_embeds, int n_embed, const int32_t* d
     c->prefilled = true; c->carry_valid = true;
     return BD_OK;
   }
+  if (c->pf_on && total > std::max(step, kStreamRows)) {
+    // Up to 128 rows that are more than one chunk of max_block: the layers once over all of them (the weights are read once; 3B
+    // shape, max_block 64: 65 rows 2.5 ms, as two chunks 4.4, 128 rows 2.9 and 4.9), the LM head over the rows of the chunk that
+    // would be the last.
+    const int M = (total - 1) % step + 1;
+    BD_TRY(prefill_chunk(c, dev_embeds, n_embed, dev_ids, 0, total));
+    hipLaunchKernelGGL(advance_kernel, dim3(1), dim3(1), 0, s, c->st, total - M);
+    BD_TRY(check_launch());
+    c->n = total - M;
+    BD_TRY(lm_head_of_rows(c, c->pf_x + (size_t)(total - M) * c->H, M, BD_MODE_CAUSAL, false, 0));
+    FinishArgs f = finish_args(c, M);
+    f.commit = 1;
+    hipLaunchKernelGGL(finish_causal_kernel, dim3(1), dim3(64), 0, s, f);
+    BD_TRY(check_launch());
+    c->n = total;
+    c->prefilled = true; c->carry_valid = true;
+    return BD_OK;
+  }
   for (int off = off0; off < total; off += step) {
     const int M = std::min(step, total - off);
     const bool last = off + M >= total;

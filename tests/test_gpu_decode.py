@@ -1351,6 +1351,40 @@ def test_lm_head_over_all_rows_of_a_large_forward(B, quad):
     assert float((a - b).norm()) <= 1.2e-2 * float(b.norm())
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("rows,block", [(33, 16), (65, 64), (100, 48), (127, 64), (128, 32)])
+def test_prompts_of_up_to_128_rows_in_one_chunk(rows, block, dtype):
+    """Prompts longer than max_block and than 32 rows, but not than 128: keys and values of the second layer, the last chunk's
+    logits and the state behind it against the decode kernels, max_block rows at a time.  Bars as above."""
+    shape = _wide(2, vocab=8192)
+    w = inputs.make_weights(shape, 4 if dtype == "bf16" else 2, dtype, threads=8)
+    emb, ids = inputs.make_prompt(shape, rows // 2, rows - rows // 2, seed=17)
+    last = (rows - 1) % block + 1
+    res = []
+    for flags in (0, binding.BD_FLAG_PREFILL_DECODE):
+        ctx = binding.Context(shape, max_seq=256, max_block=block if dtype == "bf16" or flags == 0 else min(block, 32), flags=flags,
+                              weight_dtype=binding.BD_FP8_E4M3 if dtype == "fp8" else binding.BD_BF16)
+        ctx.load_model(w, as_bf16_bits=True) if dtype == "bf16" else ctx.load_model(w)
+        ctx.bd_debug_logits(True)
+        ctx.bd_prefill(torch.from_numpy(emb).cuda(), torch.from_numpy(ids).cuda())
+        assert ctx.bd_cache_len() == rows
+        k, v = ctx.bd_read_kv(1, 0, rows)
+        n = last if flags == 0 else (rows - 1) % min(block, 32 if dtype == "fp8" else 64) + 1
+        res.append((k.clone(), v.clone(), ctx.bd_read_logits(n).clone()[-min(last, n):], n))
+        if flags == 0:
+            cand, conf = ctx.bd_read_carry()
+            assert cand == int(ctx.bd_read_logits(last)[-1].argmax())
+            tok = torch.arange(5, 9, dtype=torch.int32, device="cuda")
+            ctx.bd_commit_block(tok)                        # the context goes on behind the prompt
+            assert ctx.bd_cache_len() == rows + 4
+        ctx.bd_status()
+        ctx.close()
+    m = min(res[0][2].shape[0], res[1][2].shape[0])
+    for a, b in ((res[0][0], res[1][0]), (res[0][1], res[1][1]), (res[0][2][-m:], res[1][2][-m:])):
+        assert float((a - b).abs().max()) <= 2e-2 * float(b.abs().max())
+        assert float((a - b).norm()) <= 1.2e-2 * float(b.norm())
+
+
 @pytest.mark.parametrize("rows,want", [
     (2040, {("0", "5", "4"), ("1", "4", "4"), ("2", "11", "8"), ("3", "8", "8")}),     # four K splits of the down projection
     (4083, {("0", "5", "8"), ("1", "4", "8"), ("2", "11", "8"), ("3", "8", "8")}),     # two
