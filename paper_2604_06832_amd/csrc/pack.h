@@ -37,7 +37,7 @@ __global__ __launch_bounds__(kWGThreads) void prologue_kernel(PrologueArgs a) {
     }
   }
   const int p = a.off + r;
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == kWGThreads - 1) {                      // (not the wavefront that computes the rotary factors: the two chains overlap)
     int id = -1;
     if (p >= a.n_embed) {
       const int j = p - a.n_embed;

@@ -1319,6 +1319,40 @@ def test_every_tile_shape_of_the_pipelined_gemms():
         ctx.close()
 
 
+@pytest.mark.parametrize("B", [2, 17, 32, 64])
+@pytest.mark.parametrize("fixed_k,tau,scale", [(0, 0.3, 20.0), (0, 0.9, 1.0), (1, 0.9, 1.0), (4, 0.9, 1.0), (64, 0.9, 40.0)])
+def test_unmask_rule_against_its_serial_form(B, fixed_k, tau, scale):
+    """Tokens, mask, count and confidences of a denoising step against the rule applied position by position to the forward's own ids
+    and confidences (exact; with the LM head times 40 some confidences are 1.0 and tie)."""
+    shape = inputs.TINY
+    w = dict(inputs.make_weights(shape, 3, "bf16", threads=4))
+    w["lm_head"] = inputs.round_to_bf16(w["lm_head"] * np.float32(scale))
+    emb, ids = inputs.make_prompt(shape, 20, 40, seed=18)
+    ctx = binding.Context(shape, max_seq=256, max_block=64)
+    ctx.load_model(w)
+    ctx.bd_prefill(torch.from_numpy(emb).cuda(), torch.from_numpy(ids).cuda())
+    carry, carry_conf = ctx.bd_read_carry()
+    rng = np.random.default_rng(B * 10 + fixed_k)
+    tok = rng.integers(0, 500, B).astype(np.int32)
+    mask = (rng.random(B) < 0.7).astype(np.uint8)
+    mask[0], mask[-1] = 1, 1
+    d_tok, d_mask = torch.from_numpy(tok.copy()).cuda(), torch.from_numpy(mask.copy()).cuda()
+    n, conf_out = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(B, device="cuda")
+    ctx.bd_denoise_step(d_tok, d_mask, tau, fixed_k, n, conf_out)
+    cand, conf = (t.cpu().numpy() for t in ctx.bd_read_rows(B))
+    ctx.bd_status()
+    tok[0], mask[0], shown = carry, 0, 1
+    left = [i for i in range(1, B) if mask[i]]
+    order = sorted(left, key=lambda i: (-conf[i - 1], i))
+    take = order[:fixed_k] if fixed_k else [i for i in left if conf[i - 1] > np.float32(tau)] or order[:1]
+    for i in take:
+        tok[i], mask[i] = cand[i - 1], 0
+    assert np.array_equal(d_tok.cpu().numpy(), tok) and np.array_equal(d_mask.cpu().numpy(), mask)
+    assert int(n.item()) == shown + len(take)
+    assert np.array_equal(conf_out.cpu().numpy(), np.concatenate([[np.float32(carry_conf)], conf[:B - 1]]))
+    ctx.close()
+
+
 @pytest.mark.parametrize("B,quad", [(33, False), (64, False), (9, True), (11, True), (14, True), (32, True)])
 def test_lm_head_over_all_rows_of_a_large_forward(B, quad):
     """The LM head of forwards of more than 32 rows, vocabularies that end inside a workgroup's rows: ids and confidences against
