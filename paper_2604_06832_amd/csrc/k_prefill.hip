@@ -212,8 +212,9 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
   }
   hipLaunchKernelGGL(rope_table_kernel, dim3(mc), dim3(64), 0, s, c.rope, c.st, c.D / 2, c.rope_theta, c.quad_W);
   BD_TRY(check_launch());
-  // Up to 128 rows: one workgroup per row in the norm, and (up to 64) the keys dealt to workgroups in the attention.
-  const bool skinny = MTc <= 8 && !c.staged;
+  // One workgroup per row in the norm while that fills the chip no more than a few times over, beyond a wavefront per row (us of a
+  // prompt, 3B shape, row by row against wavefronts: 200 rows 3450 / 3735, 333 4440 / 4590, 600 6005 / 6060, 1024 7290 / 7250).
+  const bool norm_rows = MTc <= 48 && !c.staged;
   PfGemmArgs g{};
   g.MTc = MTc; g.Mvalid = rows; g.rs = c.rs; g.rope = c.rope; g.x = c.x; g.q = c.q; g.max_kb = c.max_kb; g.n0 = c.n0;
   g.act = c.act; g.H = c.H; g.QD = c.QD; g.KVD = c.KVD; g.D = c.D; g.n_q = c.n_q;
@@ -221,7 +222,7 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
   g.st = c.st; g.skippable = c.skippable; g.pages = c.pages;
   int parts = 0;                                   // K splits of the last down projection still to be added to x
   auto norm = [&](const float* gain, const float* kparts, int n_kparts) -> int {
-    if (skinny) hipLaunchKernelGGL(pf_norm_row_kernel, dim3(mc), dim3(kPfThreads), 0, s, c.x, c.H, c.rms_eps, c.xb, MTc, c.rs, gain, kparts, n_kparts, skip);
+    if (norm_rows) hipLaunchKernelGGL(pf_norm_row_kernel, dim3(mc), dim3(kPfThreads), 0, s, c.x, c.H, c.rms_eps, c.xb, MTc, c.rs, gain, kparts, n_kparts, skip);
     else hipLaunchKernelGGL(pf_norm_kernel, dim3(mc / 4), dim3(kPfThreads), 0, s, c.x, c.H, c.rms_eps, c.xb, MTc, c.rs, gain, kparts, n_kparts, skip);
     return check_launch();
   };
@@ -250,7 +251,7 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
       const bool quad = c.mode >= 2;
       // (few rows: query tiles of a head share a workgroup, the keys are dealt to kPfAttnChunks workgroups, a second
       // kernel sums the chunks)
-      const bool split = skinny && MTc <= 4 && c.apart != nullptr;
+      const bool split = MTc <= 4 && !c.staged && c.apart != nullptr;
       // Two query tiles per workgroup halve what comes out of the L2s, and the number of workgroups.  (Tiles of 16 rows, keys before
       // the chunk) -> us for one and for two tiles, 16 heads.  They are faster once the one-tile kernel, of which three workgroups of
       // D = 128 fit a CU, needs another round of the chip: D = 128 (48, 0) 14.1 / 14.2, (56, 0) 18.1 / 16.0, (64, 0) 21.1 / 17.9; D = 64 (48, 0)
