@@ -124,12 +124,12 @@ int launch_lm_tile(hipStream_t s, PfGemmArgs a) {
   constexpr int lds = pf_gemm_pipe_lds<WN, TW, BKS, NST>();
   static_assert(lds <= 160 * 1024 && WN >= kPfLmMinTiles, "");
   if (!attr_set) {
-    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_lm_kernel<WN, TW, BKS, NST>), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_pipe_kernel_lm<WN, TW, BKS, NST>), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     attr_set = true;
   }
   a.RG = ceil_div(a.NT, 2 * WN);
   a.TG = ceil_div(a.MTc, 2 * TW);
-  hipLaunchKernelGGL((pf_lm_kernel<WN, TW, BKS, NST>), dim3(ceil_div(a.RG, 8) * 8 * a.TG), dim3(kPfThreads), lds, s, a);
+  hipLaunchKernelGGL((pf_gemm_pipe_kernel_lm<WN, TW, BKS, NST>), dim3(ceil_div(a.RG, 8) * 8 * a.TG), dim3(kPfThreads), lds, s, a);
   return check_launch();
 }
 

@@ -443,7 +443,7 @@ __global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel(PfGemmArgs 
 // path's LM head takes 64 at a time and, at four token tiles, reads 3.3 TB/s.  3B shape, the fold below included: 64 rows 191 -> 127 us
 // (622 MB: 4.9 TB/s), 72 rows 310 -> 128, 210 rows 678 -> 178, 1056 rows 3035 -> 711.
 template <int WN, int TW, int BKS, int NST>
-__global__ __launch_bounds__(kPfThreads, 1) void pf_lm_kernel(PfGemmArgs a) {
+__global__ __launch_bounds__(kPfThreads, 1) void pf_gemm_pipe_kernel_lm(PfGemmArgs a) {
   pf_gemm_pipe<PH_LM, WN, TW, BKS, NST, false>(a);
 }
 // One workgroup per row: the row groups' statistics merged (equal maxima keep the lower id).

@@ -1372,7 +1372,7 @@ def test_lm_head_over_all_rows_of_a_large_forward(B, quad):
         draft = torch.arange(40, 40 + B, dtype=torch.int32, device="cuda")
         nxt = torch.zeros(B, dtype=torch.int32, device="cuda")
         names = _kernels_of(lambda: ctx.bd_quad_step(B, draft, nxt) if quad else ctx.bd_verify_block(draft, False))
-        got = {a[:2] for a in _instances(names, "pf_lm_kernel")}
+        got = {a[:2] for a in _instances(names, "pf_gemm_pipe_kernel_lm")}
         assert len(got) == (1 if flags == 0 else 0), got
         res.append((ctx.bd_read_logits(rows).clone(), *[t.clone() for t in ctx.bd_read_rows(rows)]))
         ctx.bd_status()
