@@ -91,6 +91,7 @@ struct bd_ctx {
   DevState* st = nullptr;
   unsigned* bar = nullptr; unsigned bar_epoch = 0;
   unsigned* xbar = nullptr; unsigned xbar_epoch = 0;   // barriers among the workgroups of one XCD (stream_fwd.h)
+  unsigned chip_epoch = 0;         // chip-wide barriers through the XCDs' counters (the same memory; stream_fwd.h)
   int xcds = 0;                    // XCDs, if workgroup b of a forward-shaped launch runs on XCD b mod xcds (probed); else 0
   unsigned long long* trace = nullptr; int trace_on = 0;
   // host mirror of the decode state
@@ -229,8 +230,10 @@ int launch_forward_kernels(bd_ctx* c, int MT, MegaArgs& a, bool lm_only = false)
                       attn_local_plan(c->plan.nwg, c->xcds, c->cfg.n_kv_heads, c->G * MT, lp);
       a.xbar = c->xbar; a.xbar_epoch = c->xbar_epoch;
       a.no_weights = (c->cfg.flags & BD_FLAG_MEASURE_NO_WEIGHTS) ? 1 : 0;
+      unsigned& epoch = attn_local ? c->chip_epoch : c->bar_epoch;   // (each form of the attention has its form of the chip-wide barrier)
+      a.bar_epoch = epoch;
       BD_TRY(launch_stream_fwd(c->stream, MT, c->D, c->fp8, quad, attn_local, a));
-      c->bar_epoch += (a.local_gu ? 4u : 5u) * (unsigned)c->L;
+      epoch += (a.local_gu ? 4u : 5u) * (unsigned)c->L;
       c->xbar_epoch += (unsigned)((a.local_gu ? 1 : 0) + (attn_local ? 1 : 0)) * (unsigned)c->L;
       a.local_gu = 0;
     } else {
@@ -669,7 +672,7 @@ int bd_create(const bd_config* cfg, void* hip_stream, bd_ctx** out) {
   }
   A(c->st, sizeof(DevState));
   A(c->bar, (size_t)(1 + 2 * ceil_div(P.nwg, kBarGroup)) * 32 * 4);
-  A(c->xbar, (size_t)8 * 32 * 4);
+  A(c->xbar, (size_t)24 * 32 * 4);
 #undef A
   hipError_t e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {

@@ -179,7 +179,8 @@ struct MegaArgs {
   const int* kv_pages;        // page of every 32-key block of the cache (null: contiguous)
   int no_weights;             // measurement only: the producers request nothing (the consumers multiply what the ring held)
   int n_xcd;                  // XCDs (8) when workgroup b runs on XCD b mod n_xcd, else 0
-  unsigned* xbar;             // [xcd][32 words] arrival counters of the XCD barriers
+  unsigned* xbar;             // [24][32 words]: arrival counters of the XCD barriers and, per XCD, of the chip-wide ones, then
+                              // the lines the last arrivers write (stream_grid_barrier)
   unsigned xbar_epoch;        // XCD barriers run before this launch
   int fp8;                    // the decoder linears are e4m3 codes with one scale per output row: the scale multiplies
                               // the accumulators, and the norm gains (which cannot be folded into the codes) multiply
