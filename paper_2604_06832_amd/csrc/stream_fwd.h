@@ -427,7 +427,8 @@ __device__ inline void epilogue_residual(const MegaArgs& a, int ver, int token, 
 // ring and the reduction are there once.  What that is for is the instruction cache (64 KiB for two compute units): every
 // hand-over is a chain in which a miss is not hidden by anything.  With a copy per phase, and the partition of the
 // rows evaluated in each (64-bit divisions, a fifth of all instructions), the kernel was 156 KB and missed its cache 195,000
-// times per forward by the profiler's count; now 70 KB and 4,700.  The K ranges are summed once per round of 6 (one token
+// times per forward by the profiler's count; with one copy 70 KB and 4,700
+// (and 52 KB with one form of the attention per kernel).  The K ranges are summed once per round of 6 (one token
 // tile) or 4 (two: more accumulators spill) row tiles instead of once per pair.  One forward, 3B shape, 1024 keys: 1 row 2116 -> 1995 us,
 // 32 rows 2422 -> 2211 us (two token tiles: rounds of 6 tiles 2442, of 2 tiles 2243).
 template <int MT, int D, bool FP8>
@@ -1175,7 +1176,7 @@ __device__ inline bool stream_attention_local(const MegaArgs& a, FwdCtx& fc, Fwd
 
 // ---- grid barrier of the consumer wavefronts ---------------------------------------------------------------------
 // Every consumer has waited for its own stores (each phase ends with that wait).  Consumer 0 collects the four
-// arrivals, takes part in the chip-wide barrier (two-level counters of mega.h) and hands the new epoch to the
+// arrivals, takes part in the chip-wide barrier (key split: two-level counters of mega.h) and hands the new epoch to the
 // others through LDS.
 // LOCAL: the workgroups of an XCD meet at a counter in its L2, and the last one there writes the epoch into its word of every
 // XCD's line (a.xbar: lines 8.. hold the counters, lines 16.. the words), which the workgroups of that XCD poll: one far
