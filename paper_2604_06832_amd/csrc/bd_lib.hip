@@ -251,9 +251,6 @@ int launch_forward_kernels(bd_ctx* c, int MT, MegaArgs& a, bool lm_only = false)
   return BD_OK;
 }
 
-constexpr int kQuadMaxB = 32;      // largest block of a quadratic step: B (B + 1) = 1056 rows
-constexpr int kStreamRows = 32;    // rows of a forward the decode kernels stream the weights against (two token tiles)
-
 // ---- paged cache: the host owns the page list, the device holds a copy that the kernels index ---------------------
 // Pages for every block that holds a position below `upto`, taken off the free list in order; the device table follows
 // in stream order.
@@ -392,6 +389,7 @@ int forward(bd_ctx* c, int M, int mode, bool want_lm, const float* embeds, int n
   // norm + LM head run (the large-M prefill hands its last row over this way)
   const int MT = ceil_div(M, 16);
   const int Mp = c->Mp_max;
+  if (M > Mp) return BD_E_ARG;                              // (the working buffers' rows)
   hipStream_t s = c->stream;
   if (!lm_only) {
     PrologueArgs p{};
@@ -538,10 +536,10 @@ int bd_create(const bd_config* cfg, void* hip_stream, bd_ctx** out) {
   c->use_stream = c->fp8 || !(k.flags & BD_FLAG_REGISTER_RING);
   c->H = k.hidden; c->D = k.head_dim; c->QD = k.n_q_heads * k.head_dim; c->KVD = k.n_kv_heads * k.head_dim;
   c->NQKV = c->QD + 2 * c->KVD; c->F = k.ffn; c->V = k.vocab; c->L = k.n_layers; c->G = k.n_q_heads / k.n_kv_heads;
-  c->Mp_max = ceil_div(k.max_block, 16) * 16;
   c->max_kb = ceil_div(k.max_seq, 32);
   // Large-M kernels for contexts whose cache can hold a chunk of 128 rows plus the prompt's last rows.
   c->pf_on = k.max_seq > kPfTokens && !(k.flags & BD_FLAG_PREFILL_DECODE);
+  c->Mp_max = ceil_div(decode_rows(k.max_block, c->pf_on), 16) * 16;
   c->pf_rows = c->pf_on ? std::min(k.max_seq >= kPfLongContext ? kPfChunkRows : kPfShortRows, (k.max_seq - 1) / kPfTokens * kPfTokens) : 0;
   {
     // the largest quadratic forward of this context: B (B + 1) rows for B = min(max_block, 32), if the cache can hold them

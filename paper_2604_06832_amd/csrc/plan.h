@@ -12,6 +12,16 @@ constexpr int kMaxKW = 16;   // k-steps (of 32) one wavefront covers in a GEMM p
 constexpr int kT = 2;        // 16-row tiles a wavefront accumulates side by side (one chunk of its stream)
 constexpr int kBarGroup = 16;
 constexpr int kSpinLimit = 1 << 19;
+constexpr int kQuadMaxB = 32;      // largest block of a quadratic step: B (B + 1) = 1056 rows
+constexpr int kStreamRows = 32;    // rows of a forward the decode kernels stream the weights against (two token tiles)
+
+// Rows a context's decode kernels have to hold: a block, or, where the large-M kernels are there (a quadratic step may then have more
+// rows than max_block), the largest quadratic step that does not go to those kernels.  (Four rows or five of max_block: 20 or 30.)
+__host__ __device__ inline int decode_rows(int max_block, bool large_m) {
+  int rows = max_block;
+  for (int B = 1; large_m && B <= max_block && B * (B + 1) <= kStreamRows; ++B) rows = rows < B * (B + 1) ? B * (B + 1) : rows;
+  return rows;
+}
 
 enum { PH_QKV = 0, PH_O = 1, PH_GU = 2, PH_DOWN = 3, PH_LM = 4, PH_COUNT = 5, PH_END = 6 };
 

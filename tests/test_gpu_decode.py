@@ -500,6 +500,38 @@ def test_quadratic_step_rejects_blocks_that_do_not_fit():
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("max_block,B", [(4, 4), (5, 4), (5, 5), (16, 4), (16, 5)])
+def test_quadratic_step_of_more_rows_than_the_block_on_the_decode_kernels(max_block, B, dtype):
+    """20 and 30 rows are more than a block of these contexts (and than its row tiles of 16), but not enough for the large-M kernels:
+    every row's logits, the accept length, the next draft and the moved keys and values equal, bit for bit, those of a context
+    whose blocks may have 64 rows (the same kernels on larger buffers)."""
+    shape = inputs.TINY
+    w = inputs.make_weights(shape, 0 if dtype == "bf16" else 2, dtype, lm_head_scale=20.0, threads=1)
+    M = B * (B + 1)
+    _say(f"quadratic step, {dtype}, max_block {max_block}, {M} rows")
+    res = []
+    for mb in (max_block, 64):
+        ctx = binding.Context(shape, max_seq=300, max_block=mb, weight_dtype=binding.BD_FP8_E4M3 if dtype == "fp8" else binding.BD_BF16)
+        ctx.load_model(w, as_bf16_bits=True) if dtype == "bf16" else ctx.load_model(w)
+        ctx.bd_debug_logits(True)
+        ctx.bd_prefill(None, torch.arange(150, dtype=torch.int32, device="cuda"))
+        d = torch.zeros(B, dtype=torch.int32, device="cuda")
+        nxt = torch.zeros(B, dtype=torch.int32, device="cuda")
+        ctx.bd_quad_draft(B, d)
+        got = []
+        for _ in range(3):
+            k = ctx.bd_quad_step(B, d, nxt)
+            got += [torch.tensor(k), ctx.bd_read_logits(M).clone().cpu(), nxt.clone().cpu()]
+            d.copy_(nxt)
+        n = ctx.bd_cache_len()
+        got += [t.clone().cpu() for t in ctx.bd_read_kv(shape.n_layers - 1, 0, n)]
+        ctx.bd_status()
+        ctx.close()
+        res.append(got)
+    assert len(res[0]) == len(res[1]) and all(torch.equal(a, b) for a, b in zip(*res))
+
+
 @pytest.mark.parametrize("B", [5, 8, 16, 32])
 def test_quadratic_step_3b_shaped_two_layers(B):
     M = B * (B + 1)

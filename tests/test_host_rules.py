@@ -1,0 +1,29 @@
+"""The host's own rules (csrc/plan.h and the headers beside it): sizes of buffers, waits, choices of kernels.  tests/host_rules_check.cpp
+includes those headers; it is compiled for the host only and needs no GPU."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = "/opt/rocm/bin/hipcc"
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    if not os.path.exists(HIPCC):
+        pytest.skip("no ROCm compiler here")
+    out = str(tmp_path_factory.mktemp("host_rules") / "host_rules_check")
+    subprocess.run([HIPCC, "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-Wno-unused-value",
+                    os.path.join(ROOT, "tests", "host_rules_check.cpp"), "-o", out], check=True)
+    return out
+
+
+def _run(program, name):
+    r = subprocess.run([program, name], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout.strip().endswith("OK"), r.stdout[-3000:]
+
+
+def test_decode_buffers_hold_every_forward_that_uses_them(program):
+    """A quadratic step of B (B + 1) <= 32 rows runs on the decode kernels, also where max_block is smaller than that."""
+    _run(program, "decode_rows")
