@@ -23,6 +23,7 @@
 #pragma once
 #include "attn_plan.h"
 #include "mega.h"
+#include "stream_sync.h"
 
 namespace bd {
 
@@ -40,9 +41,6 @@ constexpr int kSsqPer = kWavesPerWG * kMaxKW * 32 / 16 / 16;
 template <int MT> constexpr int round_tiles() { return MT == 1 ? 6 : 4; }
 
 typedef __attribute__((address_space(3))) void lds_void_t;
-
-// words of the LDS synchronisation block
-enum { SY_LANDED = 0, SY_CONSUMED = 4, SY_DEAD = 8, SY_CBAR = 9, SY_ARRIVE = 10, SY_EPOCH = 11, SY_XEPOCH = 12, SY_PACE = 13, SY_WORDS = 16 };
 
 __device__ inline unsigned lds_addr(const void* p) {
   return (unsigned)(size_t)(const __attribute__((address_space(3))) char*)p;
@@ -84,7 +82,7 @@ __device__ inline void mark_dead(FwdSync& sy, DevState* st) {
 __device__ inline bool lds_wait_ge(FwdSync& sy, unsigned addr, unsigned target, DevState* st) {
   if (sy.dead) return false;
   int spins = 0;
-  while ((int)(lds_ld32(addr) - target) < 0) {
+  while (!counter_reached(lds_ld32(addr), target)) {
     if ((++spins & 63) == 0) {
       if (lds_ld32(sy.base + SY_DEAD * 4) != 0u) { sy.dead = true; return false; }
       if (spins > kLdsSpin) { mark_dead(sy, st); return false; }
@@ -1203,7 +1201,7 @@ __device__ inline bool stream_grid_barrier(const MegaArgs& a, FwdSync& sy, unsig
           __hip_atomic_store(a.xbar + 32 * (16 + lane) + x, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const unsigned* mine = a.xbar + 32 * (16 + x) + lane % nx;
         int spins = 0;
-        while (__builtin_amdgcn_ballot_w64((int)(__hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - epoch) < 0) != 0ull) {
+        while (__builtin_amdgcn_ballot_w64(!counter_reached(__hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), epoch)) != 0ull) {
           if (++spins > kSpinLimit) { ok = false; break; }
           __builtin_amdgcn_s_sleep(1);
         }
@@ -1227,7 +1225,7 @@ __device__ inline bool stream_grid_barrier(const MegaArgs& a, FwdSync& sy, unsig
       }
       const unsigned* mine = rel + 32 * g;
       int spins = 0;
-      while ((int)(__hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - epoch) < 0) {
+      while (!counter_reached(__hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), epoch)) {
         if (++spins > kSpinLimit) { ok = false; break; }
         __builtin_amdgcn_s_sleep(1);
       }
@@ -1271,7 +1269,7 @@ __device__ inline bool stream_xcd_barrier(const MegaArgs& a, FwdSync& sy, unsign
       const unsigned target = xepoch * (unsigned)(a.P.nwg / nx);
       __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       int spins = 0;
-      while ((int)(l2_atomic_peek(cnt) - target) < 0) {
+      while (!counter_reached(l2_atomic_peek(cnt), target)) {
         if (++spins > kSpinLimit) { ok = false; break; }
         __builtin_amdgcn_s_sleep(1);
       }
@@ -1307,7 +1305,7 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
   __shared__ int4 s_plan[PH_LM * kWavesPerWG];
   const MegaPlan& P = a.P;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (threadIdx.x < SY_WORDS) s_sync[threadIdx.x] = threadIdx.x == SY_PACE ? stream_pace<MT, FP8>().qkv : 0u;
+  if (threadIdx.x < SY_WORDS) s_sync[threadIdx.x] = sync_word_at_start(threadIdx.x, stream_pace<MT, FP8>().qkv, a.bar_epoch, a.xbar_epoch);
   if (threadIdx.x < PH_LM * kWavesPerWG)
     s_plan[threadIdx.x] = a.wtab[blockIdx.x * kWavesPerWG + threadIdx.x % kWavesPerWG].ph[threadIdx.x / kWavesPerWG];
   if (threadIdx.x == 0) {

@@ -4,6 +4,7 @@
 #include <cstring>
 
 #include "../paper_2604_06832_amd/csrc/plan.h"
+#include "../paper_2604_06832_amd/csrc/stream_sync.h"
 
 using namespace bd;
 
@@ -26,8 +27,28 @@ static void decode_rows_hold_every_forward() {
     }
 }
 
+// The barrier words of a launch: from whatever epoch its context has come to, each barrier of the launch waits until it is
+// published and passes then.
+static void barrier_words_wait_at_every_epoch() {
+  const unsigned far[] = {0u, 1u, 144u, 0x7FFFFFFEu, 0x7FFFFFFFu, 0x80000000u, 0x80000001u, 0xC0000000u, 0xFFFFFF70u, 0xFFFFFFFEu, 0xFFFFFFFFu};
+  for (unsigned bar : far)
+    for (unsigned xbar : far) {
+      unsigned words[SY_WORDS];
+      for (int i = 0; i < SY_WORDS; ++i) words[i] = sync_word_at_start(i, 30u, bar, xbar);
+      CHECK(words[SY_PACE] == 30u && words[SY_DEAD] == 0u && words[SY_ARRIVE] == 0u && words[SY_CBAR] == 0u, "epoch %u", bar);
+      for (int w = 0; w < 4; ++w) CHECK(words[SY_LANDED + w] == 0u && words[SY_CONSUMED + w] == 0u, "epoch %u", bar);
+      for (unsigned k = 1; k <= 180u; ++k)
+        for (int i : {(int)SY_EPOCH, (int)SY_XEPOCH}) {
+          const unsigned target = (i == SY_EPOCH ? bar : xbar) + k;
+          CHECK(!counter_reached(words[i], target), "barrier %u of a launch from epoch %u does not wait", k, target - k);
+          words[i] = target;
+          CHECK(counter_reached(words[i], target), "barrier %u of a launch from epoch %u does not pass", k, target - k);
+        }
+    }
+}
+
 int main(int argc, char** argv) {
-  struct { const char* name; void (*run)(); } checks[] = {{"decode_rows", decode_rows_hold_every_forward}};
+  struct { const char* name; void (*run)(); } checks[] = {{"decode_rows", decode_rows_hold_every_forward}, {"barrier_words", barrier_words_wait_at_every_epoch}};
   for (auto& c : checks)
     if (argc == 2 && std::strcmp(argv[1], c.name) == 0) {
       c.run();

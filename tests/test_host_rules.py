@@ -27,3 +27,8 @@ def _run(program, name):
 def test_decode_buffers_hold_every_forward_that_uses_them(program):
     """A quadratic step of B (B + 1) <= 32 rows runs on the decode kernels, also where max_block is smaller than that."""
     _run(program, "decode_rows")
+
+
+def test_barriers_wait_whatever_the_number_of_barriers_before(program):
+    """The epochs of a context run through 2^31 and 2^32: no barrier may count as passed when its launch starts."""
+    _run(program, "barrier_words")
