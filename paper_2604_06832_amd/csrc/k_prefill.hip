@@ -4,6 +4,7 @@
 
 #include "launch.h"
 #include "prefill.h"
+#include "prefill_tiles.h"
 
 namespace bd {
 namespace {
@@ -49,19 +50,16 @@ int launch_pf_gemm_pipe(hipStream_t s, PfGemmArgs a) {
 // round, measured on the phase's 3B shape (launches back to back, weights from HBM); the cheapest shape is taken.
 // (A round is a fixed part and a part per k-step, so the shapes' order could shift with K.  With both parts measured for every
 // shape the choice over chunks of 33 to 1056 rows would differ by 0.3 % of the products' time at hidden 256, 0.03 % from
-// hidden 1024 on.)
-constexpr int kXcds = 8, kXcdCUs = 32, kCUs = kXcds * kXcdCUs;     // (an MI355X in one piece)
+// hidden 1024 on.  The down projection, whose K is the FFN and may be split, does weigh both: prefill_tiles.h.)
 struct PfTile { int wn, tw; float us; };
 template <int N>
-int pick_tile(const PfTile (&t)[N], int NT, int MTc, int SK, float* best_cost = nullptr) {
+int pick_tile(const PfTile (&t)[N], int NT, int MTc, int SK) {
   int best = 0;
   float cost = 0.f;
   for (int i = 0; i < N; ++i) {
-    const int per_xcd = ceil_div(ceil_div(NT, 2 * t[i].wn), kXcds) * ceil_div(MTc, 2 * t[i].tw) * SK;
-    const float c = (float)ceil_div(per_xcd, kXcdCUs) * t[i].us;
+    const float c = (float)tile_rounds(t[i].wn, t[i].tw, NT, MTc, SK) * t[i].us;
     if (i == 0 || c < cost) { best = i; cost = c; }
   }
-  if (best_cost != nullptr) *best_cost = cost;
   return best;
 }
 
@@ -133,17 +131,16 @@ int launch_lm_tile(hipStream_t s, PfGemmArgs a) {
   return check_launch();
 }
 
-constexpr PfTile kDownTiles[] = {{1, 2, 12.4f}, {1, 3, 13.9f}, {1, 4, 15.5f}, {4, 2, 19.5f}, {8, 2, 30.f}, {8, 3, 38.5f}, {8, 4, 47.f}};
-int launch_down(hipStream_t s, const PfGemmArgs& a, bool wide) {
-  if (wide) return launch_pf_gemm_pipe<PH_DOWN, 8, 8, 1, 4>(s, a);
-  switch (pick_tile(kDownTiles, a.NT, a.MTc, a.SK)) {
+int launch_down(hipStream_t s, const PfGemmArgs& a, int tile) {
+  switch (tile) {
     case 0: return launch_pf_gemm_pipe<PH_DOWN, 1, 2, 2, 12>(s, a);
     case 1: return launch_pf_gemm_pipe<PH_DOWN, 1, 3, 2, 9>(s, a);
     case 2: return launch_pf_gemm_pipe<PH_DOWN, 1, 4, 2, 7>(s, a);
     case 3: return launch_pf_gemm_pipe<PH_DOWN, 4, 2, 2, 6>(s, a);
     case 4: return launch_pf_gemm_pipe<PH_DOWN, 8, 2, 1, 6>(s, a);
     case 5: return launch_pf_gemm_pipe<PH_DOWN, 8, 3, 1, 6>(s, a);
-    default: return launch_pf_gemm_pipe<PH_DOWN, 8, 4, 1, 5>(s, a);
+    case 6: return launch_pf_gemm_pipe<PH_DOWN, 8, 4, 1, 5>(s, a);
+    default: return launch_pf_gemm_pipe<PH_DOWN, 8, 8, 1, 4>(s, a);
   }
 }
 
@@ -152,27 +149,6 @@ int k_split(int n_it) {
   for (int sk = kPfSplit; sk > 1; --sk)
     if (n_it % sk == 0) return sk;
   return 1;
-}
-
-// K splits of the down projection, and whether it runs on 256 x 256 tiles.  Those do 1.4 PFLOP/s in the K loop against 1.0 of
-// 256 x 128, but need more rows, or fewer splits, to fill the chip: a round of them is 17 us and 0.78 us per k-step.  A split costs its
-// partial sums besides, written here and read by the norm (1 KiB a tile, both at about 4 TB/s).  3B shape, 4096 rows: two splits on
-// 256 x 256 152 us, four on 256 x 128 213; 2048 rows: four splits 84 and 107.
-int down_split(int KS, int NT, int MTc, bool& wide) {
-  const int sk0 = k_split(KS / 2);
-  auto parts = [&](int sk) { return sk > 1 ? (float)sk * (float)NT * (float)MTc * 5e-4f : 0.f; };
-  float cost = 0.f;
-  pick_tile(kDownTiles, NT, MTc, sk0, &cost);
-  cost += parts(sk0);
-  int best = sk0;
-  wide = false;
-  for (int sk = 1; sk <= kPfSplit; ++sk) {
-    if (KS % (2 * sk) != 0) continue;
-    const int per_xcd = ceil_div(ceil_div(NT, 16), kXcds) * ceil_div(MTc, 16) * sk;
-    const float c = (float)ceil_div(per_xcd, kXcdCUs) * (17.f + 0.78f * (float)(KS / sk)) + parts(sk);
-    if (c < cost) { best = sk; cost = c; wide = true; }
-  }
-  return best;
 }
 
 template <int D, int JT>
@@ -309,9 +285,9 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
     g.NT = c.H / 16;
     // down: K split over workgroups (2048 output rows are too few tiles for the chip); the next norm adds the splits
     if (!c.staged && g.KS % 2 == 0) {
-      bool wide_tiles = false;
-      g.SK = down_split(g.KS, g.NT, MTc, wide_tiles); g.part = g.SK > 1 ? c.part : nullptr;
-      BD_TRY(launch_down(s, g, wide_tiles));
+      const int tile = down_plan(g.KS, g.NT, MTc, g.SK);
+      g.part = g.SK > 1 ? c.part : nullptr;
+      BD_TRY(launch_down(s, g, tile));
       parts = g.SK > 1 ? g.SK : 0;
       g.SK = 1; g.part = nullptr;
     } else {

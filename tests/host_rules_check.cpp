@@ -4,6 +4,7 @@
 #include <cstring>
 
 #include "../paper_2604_06832_amd/csrc/plan.h"
+#include "../paper_2604_06832_amd/csrc/prefill_tiles.h"
 #include "../paper_2604_06832_amd/csrc/stream_sync.h"
 
 using namespace bd;
@@ -47,8 +48,47 @@ static void barrier_words_wait_at_every_epoch() {
     }
 }
 
+// Down projection: the choice is one that can be launched, for every K, and one that was measured (whole prompts of four-layer models,
+// every tile shape and split) within 3 % of the best, for several FFN sizes.
+static void down_projection_takes_measured_tiles() {
+  for (int KS = 2; KS <= 1024; KS += 2)
+    for (int NT : {1, 2, 16, 31, 64, 66, 96, 128})
+      for (int MTc : {1, 2, 3, 4, 5, 8, 13, 21, 38, 64, 65, 97, 128, 188, 256, 375, 512}) {
+        int SK = 0;
+        const int tile = down_plan(KS, NT, MTc, SK);
+        CHECK(tile >= 0 && tile < kDownShapes && SK >= 1 && SK <= kPfSplit && KS % (2 * SK) == 0, "K steps %d, row tiles %d, token tiles %d: tile %d, %d splits", KS, NT, MTc, tile, SK);
+      }
+  struct Measured { int hidden, ffn, rows; struct { int wn, tw, sk; } good[12]; };
+  static const Measured list[] = {
+    {1024, 2816, 600, {{4, 2, 2}, {1, 3, 1}, {1, 4, 1}}},
+    {1024, 2816, 1024, {{4, 2, 2}, {1, 4, 1}}},
+    {1024, 2816, 2048, {{4, 2, 1}}},
+    {1024, 3072, 600, {{4, 2, 3}, {4, 2, 2}, {1, 3, 1}}},
+    {1024, 3072, 1024, {{4, 2, 2}, {1, 4, 1}}},
+    {1024, 3072, 4096, {{4, 2, 1}}},
+    {2048, 4096, 1024, {{4, 2, 1}, {8, 4, 4}, {8, 2, 2}}},
+    {2048, 4096, 8192, {{8, 8, 1}}},
+    {2048, 5504, 1024, {{4, 2, 1}, {8, 2, 2}, {8, 3, 2}}},
+    {2048, 8192, 3000, {{8, 3, 1}, {8, 8, 2}, {8, 4, 1}, {8, 3, 2}}},
+    {2048, 11008, 333, {{4, 2, 2}, {8, 2, 4}, {4, 2, 4}, {1, 3, 1}}},
+    {2048, 11008, 1024, {{8, 4, 4}}},
+    {2048, 11008, 4096, {{8, 8, 2}, {8, 4, 1}}},
+    {2048, 11008, 8192, {{8, 8, 1}}},
+    {1536, 8960, 128, {{1, 4, 4}, {1, 2, 2}, {1, 3, 2}}},
+    {1536, 8960, 2048, {{8, 4, 2}, {8, 8, 4}}},
+  };
+  for (const Measured& m : list) {
+    int SK = 0;
+    const PfDownTile& t = kDownTiles[down_plan(m.ffn / 32, m.hidden / 16, ceil_div(m.rows, 16), SK)];
+    bool ok = false;
+    for (auto& g : m.good) ok = ok || (g.wn == t.wn && g.tw == t.tw && g.sk == SK);
+    CHECK(ok, "hidden %d, FFN %d, %d rows: %dx%d tiles, %d splits", m.hidden, m.ffn, m.rows, t.wn, t.tw, SK);
+  }
+}
+
 int main(int argc, char** argv) {
-  struct { const char* name; void (*run)(); } checks[] = {{"decode_rows", decode_rows_hold_every_forward}, {"barrier_words", barrier_words_wait_at_every_epoch}};
+  struct { const char* name; void (*run)(); } checks[] = {{"decode_rows", decode_rows_hold_every_forward}, {"barrier_words", barrier_words_wait_at_every_epoch},
+                                                                  {"down_plan", down_projection_takes_measured_tiles}};
   for (auto& c : checks)
     if (argc == 2 && std::strcmp(argv[1], c.name) == 0) {
       c.run();

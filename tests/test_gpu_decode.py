@@ -1479,6 +1479,34 @@ def test_tiles_of_chunks_of_up_to_8192_rows(rows, want):
         assert float((a - b).norm()) <= 1.2e-2 * float(b.norm())
 
 
+@pytest.mark.parametrize("hidden,heads,n_kv,dim,ffn,rows,want", [
+    (1024, 16, 4, 64, 2816, 600, ("3", "1", "3")), (1024, 16, 4, 64, 2816, 1500, ("3", "4", "2")),
+    (1024, 8, 4, 128, 3072, 600, ("3", "4", "2")),                                      # three K splits
+    (1536, 12, 2, 128, 8960, 1024, ("3", "8", "4")), (2048, 16, 2, 128, 5504, 3000, ("3", "8", "3")), (2048, 16, 2, 128, 4096, 8192, ("3", "8", "8"))])
+def test_down_projection_of_other_ffn_sizes(hidden, heads, n_kv, dim, ffn, rows, want):
+    """Tile shape of the down projection by its own K (the names of the launched kernels must show it), keys and values of the
+    second layer against the decode kernels, 64 rows at a time.  Bars as above."""
+    shape = inputs.ModelShape(n_layers=2, hidden=hidden, n_q_heads=heads, n_kv_heads=n_kv, head_dim=dim, ffn=ffn, vocab=1024)
+    w = inputs.make_weights(shape, 4, "bf16", threads=8)
+    emb, ids = inputs.make_prompt(shape, rows - 300, 300, seed=19)
+    e, i = torch.from_numpy(emb).cuda(), torch.from_numpy(ids).cuda()
+    res = []
+    for flags in (0, binding.BD_FLAG_PREFILL_DECODE):
+        ctx = binding.Context(shape, max_seq=8320, max_block=64, flags=flags)
+        ctx.load_model(w, as_bf16_bits=True)
+        names = _kernels_of(lambda: ctx.bd_prefill(e, i))
+        if flags == 0:
+            got = {a[:3] for a in _instances(names, "pf_gemm_pipe_kernel")}
+            assert [t for t in got if t[0] == "3"] == [want], got
+        k, v = ctx.bd_read_kv(1, 0, rows)
+        res.append((k.clone(), v.clone()))
+        ctx.bd_status()
+        ctx.close()
+    for a, b in zip(*res):
+        assert float((a - b).abs().max()) <= 2e-2 * float(b.abs().max())
+        assert float((a - b).norm()) <= 1.2e-2 * float(b.norm())
+
+
 @pytest.mark.parametrize("heads,n_kv,dim,rows,first", [
     (16, 2, 128, 1000, True),          # one chunk: 63 tiles, the last of 8 rows
     (16, 2, 128, 1353, True),          # 1024 + 329 rows: 21 tiles, the last of 9 rows

@@ -32,3 +32,8 @@ def test_decode_buffers_hold_every_forward_that_uses_them(program):
 def test_barriers_wait_whatever_the_number_of_barriers_before(program):
     """The epochs of a context run through 2^31 and 2^32: no barrier may count as passed when its launch starts."""
     _run(program, "barrier_words")
+
+
+def test_down_projection_takes_tiles_that_measured_well_at_every_ffn(program):
+    """The rule weighs a round's fixed part and its part per k-step: what is right for FFN 11008 is not for 2816."""
+    _run(program, "down_plan")
