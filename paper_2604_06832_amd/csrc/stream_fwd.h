@@ -131,14 +131,17 @@ constexpr int kStashGroup = 4;                   // fragments moved or requested
 // around the optimum.  One forward before and after: 4 rows 1959 -> 1875 us, 32 rows 2151 -> 2003; e4m3 (half the fragments), 333
 // keys, 32 rows 2031 -> 1968.  With e4m3 and one token tile there is so little to request that the one rate stays (1570 us, with a
 // rate per phase 1584: the kernel's registers spill over it).
+// The rates are those of the attention inside the XCDs.  Where it is split over the chip (LOCAL false: head counts that do not deal out over
+// the XCDs, or BD_FLAG_ATTENTION_KEY_SPLIT) attention and barriers take other shares of a layer and one rate is the better one: hidden 1536, 12 heads,
+// FFN 8960, eight layers, bf16, 8 keys 1 row 371 -> 353 us and 32 rows 425 -> 392, 700 keys 406 -> 388 and 459 -> 426; e4m3 32 rows 421 -> 411.
 struct StreamPace {
   unsigned qkv, attn, o, gu, gu_end, down, down_end;   // from the phase's start; from the last product of gate/up and of down on
   unsigned low, low_ticks;                             // at most `low` fragments requested and not yet consumed: at least this pace
   unsigned burst;                                      // fragments that may be requested back to back
 };
-template <int MT, bool FP8> constexpr bool stream_paced() { return !(FP8 && MT == 1); }
-template <int MT, bool FP8> constexpr StreamPace stream_pace() {
-  if (!stream_paced<MT, FP8>()) return StreamPace{30, 30, 30, 30, 30, 30, 30, 24, 10, 16};
+template <int MT, bool FP8, bool LOCAL> constexpr bool stream_paced() { return LOCAL && !(FP8 && MT == 1); }
+template <int MT, bool FP8, bool LOCAL> constexpr StreamPace stream_pace() {
+  if (!stream_paced<MT, FP8, LOCAL>()) return StreamPace{30, 30, 30, 30, 30, 30, 30, 24, 10, 16};
   if (FP8) return StreamPace{70, 40, 24, 22, 40, 11, 120, 16, 14, 8};
   return MT == 1 ? StreamPace{44, 36, 20, 26, 32, 12, 150, 16, 14, 24} : StreamPace{56, 36, 20, 26, 26, 14, 90, 12, 14, 24};
 }
@@ -155,10 +158,10 @@ __device__ inline void wait_for_loads(unsigned younger) {
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-template <int NS, int MT, bool FP8>
+template <int NS, int MT, bool FP8, bool LOCAL>
 __device__ inline void producer_loop_stash(const MegaArgs& a, int cw, char* ring, unsigned sync_base, int lane) {
   constexpr int NG = NS / kStashGroup;
-  constexpr StreamPace kPace = stream_pace<MT, FP8>();
+  constexpr StreamPace kPace = stream_pace<MT, FP8, LOCAL>();
   const MegaPlan& P = a.P;
   // (everything the inline assembly takes in scalar registers is made uniform explicitly)
   const unsigned total = (unsigned)__builtin_amdgcn_readfirstlane(a.wtab[blockIdx.x * kWavesPerWG + cw].frags);
@@ -182,7 +185,7 @@ __device__ inline void producer_loop_stash(const MegaArgs& a, int cw, char* ring
   while (moved < total_up) {
     const unsigned now = clock_ticks();
     unsigned pace = kPace.qkv;
-    if constexpr (stream_paced<MT, FP8>()) lds_ld32_pair(consumed_addr, pace_addr, consumed, pace);
+    if constexpr (stream_paced<MT, FP8, LOCAL>()) lds_ld32_pair(consumed_addr, pace_addr, consumed, pace);
     else consumed = lds_ld32(consumed_addr);
     const unsigned ticks = issued - consumed <= kPace.low ? min(pace, kPace.low_ticks) : pace;
     unsigned tokens = (now - t_mark) / ticks;
@@ -429,7 +432,7 @@ __device__ inline void epilogue_residual(const MegaArgs& a, int ver, int token, 
 // (and 52 KB with one form of the attention per kernel).  The K ranges are summed once per round of 6 (one token
 // tile) or 4 (two: more accumulators spill) row tiles instead of once per pair.  One forward, 3B shape, 1024 keys: 1 row 2116 -> 1995 us,
 // 32 rows 2422 -> 2211 us (two token tiles: rounds of 6 tiles 2442, of 2 tiles 2243).
-template <int MT, int D, bool FP8>
+template <int MT, int D, bool FP8, bool LOCAL>
 __device__ inline void stream_gemm_phase(const MegaArgs& a, FwdCtx& fc, Ring& rg, FwdSync& sy, int ph, int wave, int lane_in) {
   constexpr int kRound = round_tiles<MT>();
   int lane = lane_in;
@@ -454,8 +457,8 @@ __device__ inline void stream_gemm_phase(const MegaArgs& a, FwdCtx& fc, Ring& rg
     if (a.trace2 != nullptr && fc.layer == 1 && threadIdx.x == 0) a.trace2[(size_t)blockIdx.x * 64 + ph * 12 + (k)] = wall_clock64(); \
   } while (0)
   BD_SUBTS2(0);
-  constexpr StreamPace kPace = stream_pace<MT, FP8>();
-  if (stream_paced<MT, FP8>() && wave == 0)
+  constexpr StreamPace kPace = stream_pace<MT, FP8, LOCAL>();
+  if (stream_paced<MT, FP8, LOCAL>() && wave == 0)
     lds_st32(sy.base + SY_PACE * 4, ph == PH_GU ? kPace.gu : ph == PH_DOWN ? kPace.down : ph == PH_O ? kPace.o : kPace.qkv);
   if (n_tiles > 0) {
     const bool norm = ph == PH_QKV || ph == PH_GU;
@@ -541,7 +544,7 @@ __device__ inline void stream_gemm_phase(const MegaArgs& a, FwdCtx& fc, Ring& rg
           else if (kT * c < nt) consume_chunk<MT, false, FP8>(rg, sy, xk, steps, acc[c], lane);
         }
       }
-      if (stream_paced<MT, FP8>() && wave == 0 && t0 + kRound >= n_tiles && ph >= PH_GU) lds_st32(sy.base + SY_PACE * 4, ph == PH_GU ? kPace.gu_end : kPace.down_end);
+      if (stream_paced<MT, FP8, LOCAL>() && wave == 0 && t0 + kRound >= n_tiles && ph >= PH_GU) lds_st32(sy.base + SY_PACE * 4, ph == PH_GU ? kPace.gu_end : kPace.down_end);
       BD_SUBTS2(3);
       // The operands fetched for the epilogue are taken here, before its first store: the vector-memory counter is
       // in order, so a wait for them placed behind a write-through store would also wait for that store's
@@ -1305,7 +1308,7 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
   __shared__ int4 s_plan[PH_LM * kWavesPerWG];
   const MegaPlan& P = a.P;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (threadIdx.x < SY_WORDS) s_sync[threadIdx.x] = sync_word_at_start(threadIdx.x, stream_pace<MT, FP8>().qkv, a.bar_epoch, a.xbar_epoch);
+  if (threadIdx.x < SY_WORDS) s_sync[threadIdx.x] = sync_word_at_start(threadIdx.x, stream_pace<MT, FP8, LOCAL>().qkv, a.bar_epoch, a.xbar_epoch);
   if (threadIdx.x < PH_LM * kWavesPerWG)
     s_plan[threadIdx.x] = a.wtab[blockIdx.x * kWavesPerWG + threadIdx.x % kWavesPerWG].ph[threadIdx.x / kWavesPerWG];
   if (threadIdx.x == 0) {
@@ -1332,7 +1335,7 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
 
   if (wave >= kWavesPerWG) {
     const int cw = wave - kWavesPerWG;
-    producer_loop_stash<kStash, MT, FP8>(a, cw, lds + cw * kRingBytes, sync_base, lane);
+    producer_loop_stash<kStash, MT, FP8, LOCAL>(a, cw, lds + cw * kRingBytes, sync_base, lane);
     return;
   }
 
@@ -1369,7 +1372,7 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
     for (int step = 0; step < 5; ++step) {
       asm volatile("" : "+s"(step));
       if (step == 1) {
-        if (stream_paced<MT, FP8>() && wave == 0) lds_st32(sync_base + SY_PACE * 4, stream_pace<MT, FP8>().attn);
+        if (stream_paced<MT, FP8, LOCAL>() && wave == 0) lds_st32(sync_base + SY_PACE * 4, stream_pace<MT, FP8, LOCAL>().attn);
         if constexpr (LOCAL) {
           alive = stream_attention_local<D, QUAD>(a, fc, sy, ++xepoch, wave, lane);
           if (!alive) break;
@@ -1377,7 +1380,7 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
           stream_attention_phase<D, QUAD>(a, fc, sy, wave, lane);
         }
       } else {
-        stream_gemm_phase<MT, D, FP8>(a, fc, rg, sy, step == 0 ? (int)PH_QKV : step - 1, wave, lane);
+        stream_gemm_phase<MT, D, FP8, LOCAL>(a, fc, rg, sy, step == 0 ? (int)PH_QKV : step - 1, wave, lane);
       }
       BD_TS2();
       if (step == 3 && a.local_gu) alive = stream_xcd_barrier(a, sy, ++xepoch, wave, lane);
