@@ -188,9 +188,7 @@ int launch_prefill_chunk(hipStream_t s, const PfChunk& c) {
   }
   hipLaunchKernelGGL(rope_table_kernel, dim3(mc), dim3(64), 0, s, c.rope, c.st, c.D / 2, c.rope_theta, c.quad_W);
   BD_TRY(check_launch());
-  // One workgroup per row in the norm while that fills the chip no more than a few times over, beyond a wavefront per row (us of a
-  // prompt, 3B shape, row by row against wavefronts: 200 rows 3450 / 3735, 333 4440 / 4590, 600 6005 / 6060, 1024 7290 / 7250).
-  const bool norm_rows = MTc <= 48 && !c.staged;
+  const bool norm_rows = !c.staged && norm_by_rows(c.H, MTc);
   PfGemmArgs g{};
   g.MTc = MTc; g.Mvalid = rows; g.rs = c.rs; g.rope = c.rope; g.x = c.x; g.q = c.q; g.max_kb = c.max_kb; g.n0 = c.n0;
   g.act = c.act; g.H = c.H; g.QD = c.QD; g.KVD = c.KVD; g.D = c.D; g.n_q = c.n_q;

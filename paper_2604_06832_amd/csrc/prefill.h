@@ -574,7 +574,7 @@ __global__ __launch_bounds__(kPfThreads) void pf_norm_kernel(float* __restrict__
   if (lane == 0) rs[token] = rsqrtf(ss / (float)H + eps);
 }
 
-// The same for chunks of up to 768 rows: one workgroup per row, so that the rows of a 64-row forward spread over 64 CUs
+// The same for shorter chunks (norm_by_rows): one workgroup per row, so that the rows of a 64-row forward spread over 64 CUs
 // instead of 16 and every lane has one group of eight columns per pass.  Same sums in the same order per column; the sum
 // of squares is reduced over the workgroup's lanes in a fixed order.
 __global__ __launch_bounds__(kPfThreads) void pf_norm_row_kernel(float* __restrict__ x, int H, float eps, u16* __restrict__ xb,

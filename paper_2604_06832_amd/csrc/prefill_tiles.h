@@ -56,4 +56,15 @@ inline int down_plan(int KS, int NT, int MTc, int& SK) {
   return tile;
 }
 
+// Norm of a chunk: one workgroup per row while the rows do not fill the chip several times over, beyond that one wavefront per row, which
+// passes over a row 512 columns at a time.  The more passes, the longer a row keeps its wavefront, and the further the workgroups reach; with
+// one pass they have nothing to win (us, workgroup / wavefront per row, two K splits added: hidden 512 384 rows 3.25 / 3.08; 1024 384 rows
+// 3.79 / 3.89, 512 rows 4.09 / 3.98; 1536 512 rows 4.71 / 5.03, 640 rows 5.19 / 5.17; 2048 512 rows 5.35 / 5.83, 640 rows 6.04 / 5.98, with four
+// splits 768 rows 8.55 / 9.31; whole prompts of the 3B shape: 600 rows 6005 / 6060, 1024 7290 / 7250).  Up to 128 rows either is within
+// 0.1 us or the workgroup is ahead.
+inline bool norm_by_rows(int H, int MTc) {
+  const int passes = ceil_div(H, 512);
+  return MTc <= 8 || (passes > 1 && MTc <= 12 * passes);
+}
+
 }  // namespace bd

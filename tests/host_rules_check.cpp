@@ -86,9 +86,19 @@ static void down_projection_takes_measured_tiles() {
   }
 }
 
+// Norm: the kernel that was measured the faster one, two K splits added (us, workgroup per row against wavefront per row).
+static void norm_takes_the_faster_kernel() {
+  struct { int hidden, rows; float by_rows, by_waves; } const list[] = {
+    {256, 384, 3.11f, 2.99f}, {256, 768, 3.31f, 3.05f}, {512, 192, 3.03f, 3.01f}, {512, 512, 3.40f, 3.14f}, {512, 768, 3.72f, 3.25f},
+    {1024, 192, 3.27f, 3.78f}, {1024, 384, 3.79f, 3.89f}, {1024, 640, 4.41f, 4.10f}, {1024, 768, 4.74f, 4.23f},
+    {1536, 384, 4.25f, 4.86f}, {1536, 768, 5.54f, 5.32f}, {2048, 128, 3.49f, 5.33f}, {2048, 512, 5.35f, 5.83f}, {2048, 1024, 9.44f, 6.48f}};
+  for (auto& m : list)
+    CHECK(norm_by_rows(m.hidden, m.rows / 16) == (m.by_rows < m.by_waves), "hidden %d, %d rows", m.hidden, m.rows);
+}
+
 int main(int argc, char** argv) {
   struct { const char* name; void (*run)(); } checks[] = {{"decode_rows", decode_rows_hold_every_forward}, {"barrier_words", barrier_words_wait_at_every_epoch},
-                                                                  {"down_plan", down_projection_takes_measured_tiles}};
+                                                                  {"down_plan", down_projection_takes_measured_tiles}, {"norm", norm_takes_the_faster_kernel}};
   for (auto& c : checks)
     if (argc == 2 && std::strcmp(argv[1], c.name) == 0) {
       c.run();

@@ -37,3 +37,7 @@ def test_barriers_wait_whatever_the_number_of_barriers_before(program):
 def test_down_projection_takes_tiles_that_measured_well_at_every_ffn(program):
     """The rule weighs a round's fixed part and its part per k-step: what is right for FFN 11008 is not for 2816."""
     _run(program, "down_plan")
+
+
+def test_norm_kernel_by_rows_and_hidden_size(program):
+    _run(program, "norm")
