@@ -330,12 +330,12 @@ int lm_head_of_rows(bd_ctx* c, const float* xrows, int M, int mode, bool skippab
   hipStream_t s = c->stream;
   const int ver = 2 * c->L, parts = phase_tiles(c->plan, PH_DOWN);
   const DevState* skip = skippable ? c->st : nullptr;
+  float* ssq = c->ssq + (size_t)ver * c->ssq_parts * c->Mp_max;
   // (the LM head takes as many rows at a time as the decode kernels' buffers hold)
   for (int r0 = 0; r0 < M; r0 += c->Mp_max) {
     const int rows = std::min(c->Mp_max, M - r0), MT = ceil_div(rows, 16);
-    float* ssq = c->ssq + (size_t)ver * c->ssq_parts * (MT * 16);
     hipLaunchKernelGGL(pf_rows_to_lm_kernel, dim3(MT * 16), dim3(kPfThreads), 0, s, xrows + (size_t)r0 * c->H, c->H, rows, MT,
-                       c->xb + (size_t)ver * c->xb_elems, ssq, parts, MT * 16, skip);
+                       c->xb + (size_t)ver * c->xb_elems, ssq, parts, c->Mp_max, skip);
     BD_TRY(check_launch());
     BD_TRY(forward(c, rows, mode, true, nullptr, 0, nullptr, 0, nullptr, nullptr, nullptr, skippable, quad_B, true, r0));
   }
@@ -387,10 +387,9 @@ int forward(bd_ctx* c, int M, int mode, bool want_lm, const float* embeds, int n
     return forward_large(c, M, mode, want_lm, embeds, n_embed, ids, off, seed_tokens, seed_mask, mask, skippable, quad_B);
   // lm_only: the last residual version of the rows (bf16 copy and sums of squares) is already in place; only the final
   // norm + LM head run (the large-M prefill hands its last row over this way)
-  if (M > c->Mp_max) return BD_E_ARG;                       // (the working buffers' rows)
-  // The rows of a residual version, of Q and of the sums of squares sit this forward's own padded row count apart, whatever the buffers
-  // hold.  (hidden 512, four layers, 16 rows 147.4 us; with buffers of 32 rows and their count for a stride 150.5.)
-  const int MT = ceil_div(M, 16), Mp = MT * 16;
+  const int MT = ceil_div(M, 16);
+  const int Mp = c->Mp_max;
+  if (M > Mp) return BD_E_ARG;                              // (the working buffers' rows)
   hipStream_t s = c->stream;
   if (!lm_only) {
     PrologueArgs p{};
