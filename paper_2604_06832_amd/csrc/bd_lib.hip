@@ -22,6 +22,7 @@
 #include "pack.h"
 #include "plan.h"
 #include "prefill_args.h"
+#include "prefill_tiles.h"
 
 using namespace bd;
 
@@ -355,7 +356,6 @@ int forward_large(bd_ctx* c, int M, int mode, bool want_lm, const float* embeds,
   if (p.block && (embeds != nullptr || n_embed != 0 || off != 0)) return BD_E_ARG;
   p.seed_tokens = seed_tokens; p.seed_mask = seed_mask; p.mask = mask;
   p.mode = mode; p.quad_W = quad_B > 0 ? quad_B + 1 : 0; p.skippable = skippable ? 1 : 0;
-  // (hidden sizes that are an odd multiple of 32 and the register-staged GEMMs keep the decode path's LM head)
   const bool lm_large = want_lm && c->pf_lm_w != nullptr;
   p.lm = lm_large;
   {
@@ -643,7 +643,7 @@ int bd_create(const bd_config* cfg, void* hip_stream, bd_ctx** out) {
       for (int ph = 0; ph < 4; ++ph) { c->pf_off[ph] = off; off += (size_t)NP[ph] * ceil_div(KP[ph], 32) * 32; }
       c->pf_layer_elems = off;
       A(c->pf_w, L * c->pf_layer_elems * 2);
-      if (c->H % 64 == 0 && !c->pf_staged) {
+      if (lm_as_product(c->V, c->H, c->pf_staged)) {
         A(c->pf_lm_w, (size_t)c->V * c->H * 2);
         A(c->pf_lm_stats, pf_lm_stats_elems(c->V, c->rows_max) * sizeof(f32x4));
       }

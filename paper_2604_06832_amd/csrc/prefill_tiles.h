@@ -56,6 +56,10 @@ inline int down_plan(int KS, int NT, int MTc, int& SK) {
   return tile;
 }
 
+// Does a context's LM head of forwards of more than 32 rows run as a pipelined product over a tile-major copy of its weights?  (K a whole
+// number of turns of the loop; descriptor and offsets of the product have 32 bits.  Else the decode path's LM head, 64 rows at a time.)
+inline bool lm_as_product(int vocab, int H, bool staged) { return !staged && H % 64 == 0 && (size_t)vocab * (size_t)H * 2 < ((size_t)1 << 32); }
+
 // Norm of a chunk: one workgroup per row while the rows do not fill the chip several times over, beyond that one wavefront per row, which
 // passes over a row 512 columns at a time.  The more passes, the longer a row keeps its wavefront, and the further the workgroups reach; with
 // one pass they have nothing to win (us, workgroup / wavefront per row, two K splits added: hidden 512 384 rows 3.25 / 3.08; 1024 384 rows

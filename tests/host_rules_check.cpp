@@ -96,9 +96,20 @@ static void norm_takes_the_faster_kernel() {
     CHECK(norm_by_rows(m.hidden, m.rows / 16) == (m.by_rows < m.by_waves), "hidden %d, %d rows", m.hidden, m.rows);
 }
 
+// LM head as a pipelined product: only where its 32-bit descriptor and offsets reach the whole matrix.
+static void lm_head_product_fits_its_descriptor() {
+  for (int H : {64, 256, 1024, 2048})
+    for (long long bytes = (1ll << 32) - 64 * H; bytes <= (1ll << 32) + 64 * H; bytes += 32 * H) {
+      const int vocab = (int)(bytes / (2 * H));
+      CHECK(lm_as_product(vocab, H, false) == (bytes < (1ll << 32)), "vocabulary %d, hidden %d", vocab, H);
+    }
+  CHECK(lm_as_product(151936, 2048, false) && !lm_as_product(151936, 2048, true) && !lm_as_product(1024, 1056, false), "3B shape, staged, odd k-steps");
+}
+
 int main(int argc, char** argv) {
   struct { const char* name; void (*run)(); } checks[] = {{"decode_rows", decode_rows_hold_every_forward}, {"barrier_words", barrier_words_wait_at_every_epoch},
-                                                                  {"down_plan", down_projection_takes_measured_tiles}, {"norm", norm_takes_the_faster_kernel}};
+                                                                  {"down_plan", down_projection_takes_measured_tiles}, {"norm", norm_takes_the_faster_kernel},
+                                                                  {"lm_product", lm_head_product_fits_its_descriptor}};
   for (auto& c : checks)
     if (argc == 2 && std::strcmp(argv[1], c.name) == 0) {
       c.run();

@@ -41,3 +41,8 @@ def test_down_projection_takes_tiles_that_measured_well_at_every_ffn(program):
 
 def test_norm_kernel_by_rows_and_hidden_size(program):
     _run(program, "norm")
+
+
+def test_lm_head_product_only_where_its_offsets_reach(program):
+    """Vocabularies of 4 GiB and more keep the decode path's LM head, which has no such limit."""
+    _run(program, "lm_product")
