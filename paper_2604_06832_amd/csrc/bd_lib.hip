@@ -643,7 +643,7 @@ int bd_create(const bd_config* cfg, void* hip_stream, bd_ctx** out) {
       for (int ph = 0; ph < 4; ++ph) { c->pf_off[ph] = off; off += (size_t)NP[ph] * ceil_div(KP[ph], 32) * 32; }
       c->pf_layer_elems = off;
       A(c->pf_w, L * c->pf_layer_elems * 2);
-      if (lm_as_product(c->V, c->H, c->pf_staged)) {
+      if (lm_as_product(c->V, c->H, c->rows_max, c->pf_staged)) {
         A(c->pf_lm_w, (size_t)c->V * c->H * 2);
         A(c->pf_lm_stats, pf_lm_stats_elems(c->V, c->rows_max) * sizeof(f32x4));
       }

@@ -1,6 +1,7 @@
 // Which tile shape a product of the large-M kernels takes (host only).
 #pragma once
 #include "common.h"
+#include "plan.h"
 #include "prefill_args.h"
 
 namespace bd {
@@ -56,9 +57,12 @@ inline int down_plan(int KS, int NT, int MTc, int& SK) {
   return tile;
 }
 
-// Does a context's LM head of forwards of more than 32 rows run as a pipelined product over a tile-major copy of its weights?  (K a whole
-// number of turns of the loop; descriptor and offsets of the product have 32 bits.  Else the decode path's LM head, 64 rows at a time.)
-inline bool lm_as_product(int vocab, int H, bool staged) { return !staged && H % 64 == 0 && (size_t)vocab * (size_t)H * 2 < ((size_t)1 << 32); }
+// Does a context's LM head of forwards of more than 32 rows run as a pipelined product over a tile-major copy of its weights (3B shape:
+// 622 MB)?  Only if it has such forwards (rows_max: its largest).  K must be a whole number of turns of the loop, and descriptor and offsets of
+// the product have 32 bits.  (Else the decode path's LM head, as many rows at a time as its buffers hold.)
+inline bool lm_as_product(int vocab, int H, int rows_max, bool staged) {
+  return rows_max > kStreamRows && !staged && H % 64 == 0 && (size_t)vocab * (size_t)H * 2 < ((size_t)1 << 32);
+}
 
 // Norm of a chunk: one workgroup per row while the rows do not fill the chip several times over, beyond that one wavefront per row, which
 // passes over a row 512 columns at a time.  The more passes, the longer a row keeps its wavefront, and the further the workgroups reach; with

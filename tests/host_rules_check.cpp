@@ -101,9 +101,11 @@ static void lm_head_product_fits_its_descriptor() {
   for (int H : {64, 256, 1024, 2048})
     for (long long bytes = (1ll << 32) - 64 * H; bytes <= (1ll << 32) + 64 * H; bytes += 32 * H) {
       const int vocab = (int)(bytes / (2 * H));
-      CHECK(lm_as_product(vocab, H, false) == (bytes < (1ll << 32)), "vocabulary %d, hidden %d", vocab, H);
+      CHECK(lm_as_product(vocab, H, 64, false) == (bytes < (1ll << 32)), "vocabulary %d, hidden %d", vocab, H);
     }
-  CHECK(lm_as_product(151936, 2048, false) && !lm_as_product(151936, 2048, true) && !lm_as_product(1024, 1056, false), "3B shape, staged, odd k-steps");
+  CHECK(lm_as_product(151936, 2048, 64, false) && !lm_as_product(151936, 2048, 64, true) && !lm_as_product(1024, 1056, 64, false), "3B shape, staged, odd k-steps");
+  // and only for contexts that have forwards of more than 32 rows
+  for (int rows = 1; rows <= 1056; ++rows) CHECK(lm_as_product(151936, 2048, rows, false) == (rows > 32), "%d rows", rows);
 }
 
 int main(int argc, char** argv) {

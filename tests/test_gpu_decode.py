@@ -1417,6 +1417,20 @@ def test_lm_head_over_all_rows_of_a_large_forward(B, quad):
     assert float((a - b).norm()) <= 1.2e-2 * float(b.norm())
 
 
+def test_small_blocks_hold_no_copy_of_the_lm_head():
+    """A context whose largest forward has 32 rows (max_block 5: a quadratic step of 30) never reads the tile-major LM head: what it
+    allocates must leave it out.  (256 MB here; the other buffers of the two contexts differ by far less.)"""
+    shape = inputs.ModelShape(n_layers=1, hidden=1024, n_q_heads=8, n_kv_heads=4, head_dim=128, ffn=1024, vocab=131072)
+    used = []
+    for block in (5, 6):
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        ctx = binding.Context(shape, max_seq=256, max_block=block)
+        used.append(free - torch.cuda.mem_get_info()[0])
+        ctx.close()
+    assert used[1] - used[0] >= 200 << 20, used
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 @pytest.mark.parametrize("rows,block", [(33, 16), (65, 64), (100, 48), (127, 64), (128, 32)])
 def test_prompts_of_up_to_128_rows_in_one_chunk(rows, block, dtype):

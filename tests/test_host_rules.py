@@ -44,5 +44,6 @@ def test_norm_kernel_by_rows_and_hidden_size(program):
 
 
 def test_lm_head_product_only_where_its_offsets_reach(program):
-    """Vocabularies of 4 GiB and more keep the decode path's LM head, which has no such limit."""
+    """Vocabularies of 4 GiB and more keep the decode path's LM head, which has no such limit; so do contexts without a forward of
+    more than 32 rows, which would never read the copy of the weights."""
     _run(program, "lm_product")
