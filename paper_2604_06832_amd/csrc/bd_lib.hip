@@ -458,8 +458,8 @@ int read_accept_length(bd_ctx* c, int B, const char* what, int32_t* k_out) {
   HIP_TRY(hipMemcpyAsync(&k, c->spec_k, 4, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipMemcpyAsync(&h, c->st, sizeof h, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
-  if (h.error != 0) {
-    snprintf(g_last_error, sizeof g_last_error, "a grid barrier of the forward kernel timed out; the context is unusable");
+  if (const char* why = dev_error_text(h)) {
+    set_last_error("a forward kernel gave up: %s; the context is unusable", why);
     return BD_E_HIP;
   }
   if (k < 1 || k > B || h.n != c->n + k) {
@@ -1094,8 +1094,8 @@ int bd_status(bd_ctx* c) {
   HIP_TRY(hipStreamSynchronize(c->stream));
   DevState h;
   HIP_TRY(hipMemcpy(&h, c->st, sizeof h, hipMemcpyDeviceToHost));
-  if (h.error != 0) {
-    snprintf(g_last_error, sizeof g_last_error, "a grid barrier of the forward kernel timed out; the context is unusable");
+  if (const char* why = dev_error_text(h)) {
+    set_last_error("a forward kernel gave up: %s; the context is unusable", why);
     return BD_E_HIP;
   }
   return BD_OK;

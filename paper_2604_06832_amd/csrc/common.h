@@ -105,15 +105,34 @@ __device__ inline bool block_key_visible(int mode, int row, int jb) {
   }
 }
 
+// What the forward kernels gave up at: words of DevState::error.  A workgroup that gives up makes the barriers of the others time out, so each
+// reason has a word of its own, and the text names a cause ahead of the barriers.
+enum DevError { DE_CHIP_BARRIER = 0, DE_XCD_BARRIER = 1, DE_IN_WORKGROUP = 2, DE_OTHER = 3, DE_WORDS = 4 };
+enum { DE_LDS_WAIT = 1, DE_RING = 2 };          // values of the third word
+enum { DE_OTHER_XCD = 1, DE_RAISED = 2 };       // and of the fourth
+
 // State that lives on the device so that replayed launch sequences need no new kernel arguments.
 struct DevState {
   int n;             // committed context length
   int seeded;        // 1 if the current denoise call revealed position 0 from the carry
   int carry_cand;    // prediction for position n
   float carry_conf;
-  int error;         // sticky device-side error flag (bounded waits)
+  alignas(16) int error[DE_WORDS];   // sticky (DevError: bounded waits that gave up); zero in a usable context
   int skip;          // bd_decode_block: the current block has no masked position left; its remaining steps do nothing
   int steps;         // bd_decode_block: denoising forwards that really ran for the current block
 };
+
+__device__ inline bool usable(const DevState* st) {
+  const int4 e = *reinterpret_cast<const int4*>(st->error);
+  return (e.x | e.y | e.z | e.w) == 0;
+}
+// The reason a context is unusable; null for one that is not.
+inline const char* dev_error_text(const DevState& st) {
+  if (st.error[DE_OTHER] != 0) return st.error[DE_OTHER] == DE_RAISED ? "raised through bd_k_raise_device_error" : "a workgroup ran on another XCD than the one it was planned for";
+  if (st.error[DE_IN_WORKGROUP] != 0)
+    return st.error[DE_IN_WORKGROUP] == DE_RING ? "a wait for weights in the ring timed out" : "a wait among the wavefronts of a workgroup timed out";
+  if (st.error[DE_XCD_BARRIER] != 0) return "a barrier of one XCD's workgroups timed out";
+  return st.error[DE_CHIP_BARRIER] != 0 ? "a chip-wide barrier timed out" : nullptr;
+}
 
 }  // namespace bd

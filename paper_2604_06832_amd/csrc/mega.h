@@ -73,7 +73,7 @@ __device__ inline bool grid_barrier(unsigned* bar, unsigned epoch, int nwg, DevS
         __builtin_amdgcn_s_sleep(2);
       }
       if (!ok) {
-        __hip_atomic_store(&st->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&st->error[DE_CHIP_BARRIER], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         *s_flag = 0;
       }
     }
@@ -842,7 +842,7 @@ __global__ __launch_bounds__(kWGThreads, 1) void mega_kernel(MegaArgs a) {
   const MegaPlan& P = a.P;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave id in an SGPR: all branches on it are scalar
   if (threadIdx.x == 0) {
-    int go = (a.st->error == 0);
+    int go = usable(a.st);
     if (go && a.skippable && a.st->skip) {
       skip_barriers(a.bar, nullptr, 5u * (unsigned)P.L, 0u);
       go = 0;
@@ -916,7 +916,7 @@ __global__ __launch_bounds__(kWGThreads, 1) void lm_kernel(MegaArgs a) {
   const MegaPlan& P = a.P;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave id in an SGPR: all branches on it are scalar
   if (threadIdx.x == 0) {
-    int go = (a.st->error == 0);
+    int go = usable(a.st);
     if (go && a.skippable && a.st->skip) {
       skip_barriers(a.bar, nullptr, 1u, 0u);
       go = 0;

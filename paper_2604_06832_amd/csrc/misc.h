@@ -237,7 +237,7 @@ __global__ void fill_masked_kernel(int* tokens, uint8_t* mask, int B, int mask_i
   if (i == 0) { st->skip = 0; st->steps = 0; }
 }
 __global__ void raise_error_kernel(DevState* st) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) st->error = 1;
+  if (threadIdx.x == 0 && blockIdx.x == 0) st->error[DE_OTHER] = DE_RAISED;
 }
 __global__ void read_steps_kernel(const DevState* st, int* out) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *out = st->steps;

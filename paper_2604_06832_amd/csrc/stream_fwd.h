@@ -65,6 +65,10 @@ __device__ inline void lds_inc(unsigned addr) {
   asm volatile("ds_add_u32 %0, %1" ::"v"(addr), "v"(one) : "memory");
 }
 
+// SY_DEAD: what gave up in this workgroup.  kDeadReported: said so itself; else the low bits name the word of DevState::error that the
+// consumers set when they leave (a store at the place itself costs the two-tile kernel a spilled register, 32 rows 1997 -> 2014 us).
+enum { kDeadReported = 1, kDeadRing = DE_IN_WORKGROUP, kDeadChip = 4 + DE_CHIP_BARRIER };
+static_assert(kDeadRing == 2 && kDeadChip == 4 && DE_RING == 2, "words of DevState::error");
 struct FwdSync {
   unsigned base;          // LDS address of the synchronisation block
   unsigned cbar_target;   // arrivals expected at the next consumer barrier
@@ -74,8 +78,8 @@ struct FwdSync {
 
 __device__ inline void mark_dead(FwdSync& sy, DevState* st) {
   sy.dead = true;
-  lds_st32(sy.base + SY_DEAD * 4, 1u);
-  __hip_atomic_store(&st->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  lds_st32(sy.base + SY_DEAD * 4, kDeadReported);
+  __hip_atomic_store(&st->error[DE_IN_WORKGROUP], DE_LDS_WAIT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Wait until the LDS word at `addr` has reached `target` (wrap-safe); false on time-out or dead workgroup.
@@ -271,7 +275,7 @@ __device__ inline void ring_need(Ring& rg, FwdSync& sy, int nf) {
     while ((int)(rg.have - need) < 0 && ++spins < kLdsSpin);
     if ((int)(rg.have - need) < 0) {
       sy.dead = true;
-      lds_st32(sy.base + SY_DEAD * 4, 1u);
+      lds_st32(sy.base + SY_DEAD * 4, kDeadRing);
       rg.have = need + 0x40000000u;
     }
   }
@@ -1209,10 +1213,7 @@ __device__ inline bool stream_grid_barrier(const MegaArgs& a, FwdSync& sy, unsig
           __builtin_amdgcn_s_sleep(1);
         }
         if (ok) lds_st32(sy.base + SY_EPOCH * 4, epoch);
-        else {
-          lds_st32(sy.base + SY_DEAD * 4, 1u);
-          if (lane == 0) __hip_atomic_store(&a.st->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        else lds_st32(sy.base + SY_DEAD * 4, kDeadChip);
       }
     } else if (ok && lane == 0) {
       const int ng = (nwg + kBarGroup - 1) / kBarGroup;
@@ -1233,10 +1234,7 @@ __device__ inline bool stream_grid_barrier(const MegaArgs& a, FwdSync& sy, unsig
         __builtin_amdgcn_s_sleep(1);
       }
       if (ok) lds_st32(sy.base + SY_EPOCH * 4, epoch);
-      else {
-        lds_st32(sy.base + SY_DEAD * 4, 1u);
-        __hip_atomic_store(&a.st->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+      else lds_st32(sy.base + SY_DEAD * 4, kDeadChip);
     }
   }
   const bool ok = lds_wait_ge(sy, sy.base + SY_EPOCH * 4, epoch, a.st);
@@ -1278,8 +1276,8 @@ __device__ inline bool stream_xcd_barrier(const MegaArgs& a, FwdSync& sy, unsign
       }
       if (ok) lds_st32(sy.base + SY_XEPOCH * 4, xepoch);
       else {
-        lds_st32(sy.base + SY_DEAD * 4, 1u);
-        __hip_atomic_store(&a.st->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        lds_st32(sy.base + SY_DEAD * 4, kDeadReported);
+        __hip_atomic_store(&a.st->error[DE_XCD_BARRIER], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
   }
@@ -1312,7 +1310,7 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
   if (threadIdx.x < PH_LM * kWavesPerWG)
     s_plan[threadIdx.x] = a.wtab[blockIdx.x * kWavesPerWG + threadIdx.x % kWavesPerWG].ph[threadIdx.x / kWavesPerWG];
   if (threadIdx.x == 0) {
-    int go = (a.st->error == 0);
+    int go = usable(a.st);
     if (go && a.skippable && a.st->skip) {
       const unsigned n_chip = (a.local_gu ? 4u : 5u) * (unsigned)P.L, n_xcd = ((a.local_gu ? 1u : 0u) + (LOCAL ? 1u : 0u)) * (unsigned)P.L;
       if constexpr (LOCAL) {                               // (the words of the lines stay behind; the next real barrier overwrites them)
@@ -1324,7 +1322,7 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
       go = 0;
     }
     if (go && (a.local_gu || LOCAL) && xcc_id() != blockIdx.x % 8u) {   // the XCD-local hand-overs would be unsafe
-      __hip_atomic_store(&a.st->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&a.st->error[DE_OTHER], DE_OTHER_XCD, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       go = 0;
     }
     s_flags[0] = go;
@@ -1389,8 +1387,11 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
       if (!alive) break;
     }
   }
-  if (!alive && lane == 0) lds_st32(sync_base + SY_DEAD * 4, 1u);   // let the producers go
-  if (sy.dead && lane == 0) __hip_atomic_store(&a.st->error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (sy.dead && lane == 0) {
+    const unsigned why = lds_ld32(sync_base + SY_DEAD * 4);
+    if (why > (unsigned)kDeadReported) __hip_atomic_store(a.st->error + (why & 3u), (int)DE_RING, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // (SY_DEAD is set by whoever gave up first, so the producers leave too)
 #undef BD_TS2
 }
 

@@ -108,10 +108,30 @@ static void lm_head_product_fits_its_descriptor() {
   for (int rows = 1; rows <= 1056; ++rows) CHECK(lm_as_product(151936, 2048, rows, false) == (rows > 32), "%d rows", rows);
 }
 
+// Every reason to give up has a text of its own, and a cause goes ahead of the barriers that time out because of it.
+static void every_device_error_has_its_text() {
+  DevState ok{};
+  CHECK(dev_error_text(ok) == nullptr, "usable context");
+  const int reasons[][2] = {{DE_OTHER, DE_RAISED}, {DE_OTHER, DE_OTHER_XCD}, {DE_IN_WORKGROUP, DE_RING}, {DE_IN_WORKGROUP, DE_LDS_WAIT}, {DE_XCD_BARRIER, 1}, {DE_CHIP_BARRIER, 1}};
+  for (auto& r : reasons) {
+    DevState st{}, with{};
+    st.error[r[0]] = r[1];
+    CHECK(dev_error_text(st) != nullptr, "word %d", r[0]);
+    for (auto& q : reasons) {
+      DevState other{};
+      other.error[q[0]] = q[1];
+      if (&q != &r) CHECK(std::strcmp(dev_error_text(st), dev_error_text(other)) != 0, "words %d and %d", r[0], q[0]);
+    }
+    with.error[DE_CHIP_BARRIER] = 1;
+    with.error[r[0]] = r[1];
+    CHECK(dev_error_text(with) == dev_error_text(st), "word %d behind a barrier's", r[0]);
+  }
+}
+
 int main(int argc, char** argv) {
   struct { const char* name; void (*run)(); } checks[] = {{"decode_rows", decode_rows_hold_every_forward}, {"barrier_words", barrier_words_wait_at_every_epoch},
                                                                   {"down_plan", down_projection_takes_measured_tiles}, {"norm", norm_takes_the_faster_kernel},
-                                                                  {"lm_product", lm_head_product_fits_its_descriptor}};
+                                                                  {"lm_product", lm_head_product_fits_its_descriptor}, {"device_errors", every_device_error_has_its_text}};
   for (auto& c : checks)
     if (argc == 2 && std::strcmp(argv[1], c.name) == 0) {
       c.run();

@@ -1112,6 +1112,7 @@ def test_a_context_whose_kernels_gave_up_reports_it_and_never_hangs():
         with pytest.raises(binding.BdError) as e:
             ctx.bd_status()
         assert e.value.code == binding.BD_E_HIP
+        assert "raised through bd_k_raise_device_error" in str(e.value) and "timed out" not in str(e.value)   # (what happened, not a guess)
         assert ctx.bd_cache_len() == n
         ctx.close()
 

@@ -47,3 +47,7 @@ def test_lm_head_product_only_where_its_offsets_reach(program):
     """Vocabularies of 4 GiB and more keep the decode path's LM head, which has no such limit; so do contexts without a forward of
     more than 32 rows, which would never read the copy of the weights."""
     _run(program, "lm_product")
+
+
+def test_every_reason_to_give_up_has_its_own_text(program):
+    _run(program, "device_errors")
