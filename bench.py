@@ -84,7 +84,7 @@ def main():
                          "(B*(B+1) <= 64 rows, one forward per iteration)")
     ap.add_argument("--timeline", action="store_true",
                     help="instead of the benchmark: print the per-phase time line of one denoising forward (in-kernel "
-                         "timestamps) at this prefix, as text")
+                         "timestamps) at this prefix, as text; with --block up to 16 (the trace refuses 17 to 32 rows)")
     ap.add_argument("--flags", type=int, default=0, help="bd_config.flags of the context (alternative code paths, see include/bd.h)")
     ap.add_argument("--shuffle-pages", action="store_true",
                     help="hand the cache pages out in a shuffled order (the kernels then follow the page table)")
@@ -94,6 +94,8 @@ def main():
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run one 1 GiB device-to-device copy kernel (reference for hardware byte counters)")
     args = ap.parse_args()
+    if args.timeline and 16 < args.block <= 32:
+        ap.error("--timeline needs --block of at most 16: the phase trace refuses forwards of 17 to 32 rows")
     if args.gpus != 1:
         print("bench.py: this build is a single-GPU path (batch-1 decode); run with --gpus 1. "
               "Independent requests per GPU are the multi-GPU form and need no communication.", file=sys.stderr)

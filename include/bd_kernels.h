@@ -49,10 +49,6 @@ const char* bd_k_class_name(int kclass);
  * GEMM, or the layer's cached K/V for the attention); 0 for classes that stream nothing. */
 int64_t bd_k_class_bytes(const bd_ctx* ctx, int kclass);
 
-/* Phase trace of the forward kernel: with enable != 0 every workgroup stores a 100 MHz timestamp at each
- * phase boundary of the next forwards (start; then per layer: QKV done, barrier, attention done, barrier,
- * O done, barrier, gate/up done, barrier, down done, barrier; then LM head done, barrier).  read copies
- * the last forward's [n_wg][per_wg] table to host memory (capacity in entries). */
 /* Measurement: time of reading the decoder layers' weight stream of one forward with no consumer, hand-over or barrier
  * (each wavefront its own contiguous share, as the streaming kernel's producers read it): mean of `repeats` launches
  * in milliseconds to *host_ms, the bytes read per launch to *host_bytes.  Synchronises the stream. */
@@ -63,6 +59,12 @@ int bd_k_stream_floor(bd_ctx* ctx, int repeats, double* host_ms, int64_t* host_b
  * that read a result back (bd_speculative_step, bd_quad_step) return BD_E_HIP, and the context stays unusable. */
 int bd_k_raise_device_error(bd_ctx* ctx);
 
+/* Phase trace of the forward kernel: with enable != 0 every workgroup stores a 100 MHz timestamp at each
+ * phase boundary of the next forwards (start; then per layer: QKV done, barrier, attention done, barrier,
+ * O done, barrier, gate/up done, barrier, down done, barrier; then LM head done, barrier).  read copies
+ * the last forward's [n_wg][per_wg] table to host memory (capacity in entries).
+ * While the trace is on, calls that would run a forward of 17 to 32 rows through the streaming kernel are refused
+ * (BD_E_STATE): traced forwards of that size of experimental builds ran out of a bounded wait, cause not known. */
 int bd_k_trace(bd_ctx* ctx, int enable);
 int bd_k_trace_read(bd_ctx* ctx, unsigned long long* host_out, int capacity, int* n_wg, int* per_wg);
 

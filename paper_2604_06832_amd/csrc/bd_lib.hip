@@ -382,6 +382,10 @@ int forward_large(bd_ctx* c, int M, int mode, bool want_lm, const float* embeds,
 // Source of the rows: prompt rows [off, off+M) (embeds then ids), or block tokens with an optional mask.
 int forward(bd_ctx* c, int M, int mode, bool want_lm, const float* embeds, int n_embed, const int32_t* ids, int off,
             int32_t* seed_tokens, uint8_t* seed_mask, const uint8_t* mask, bool skippable, int quad_B, bool lm_only, int row0) {
+  if (!lm_only && c->trace_on && !trace_takes(M, c->use_stream)) {
+    set_last_error("the phase trace takes forwards of at most %d rows through the streaming kernel (this one has %d): switch it off first", kTraceRows, M);
+    return BD_E_STATE;
+  }
   if (!lm_only) BD_TRY(ensure_pages(c, c->n + M));          // the new rows' keys and values land at [n, n + M)
   if (!lm_only && M > kStreamRows && c->pf_on && M <= std::max(c->Mp_max, c->rows_max))
     return forward_large(c, M, mode, want_lm, embeds, n_embed, ids, off, seed_tokens, seed_mask, mask, skippable, quad_B);

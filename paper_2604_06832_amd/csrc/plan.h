@@ -15,6 +15,11 @@ constexpr int kSpinLimit = 1 << 19;
 constexpr int kQuadMaxB = 32;      // largest block of a quadratic step: B (B + 1) = 1056 rows
 constexpr int kStreamRows = 32;    // rows of a forward the decode kernels stream the weights against (two token tiles)
 
+// Forwards that may run with the phase trace on (bd_k_trace).  With two token tiles, traced forwards of two experimental builds of the streaming
+// kernel ran out of a bounded wait; the cause was not found, so none is traced: those of up to 16 rows never did, nor did the other kernels.
+constexpr int kTraceRows = 16;
+__host__ __device__ inline bool trace_takes(int rows, bool streamed) { return !streamed || rows <= kTraceRows || rows > kStreamRows; }
+
 // Rows a context's decode kernels have to hold: a block, or, where the large-M kernels are there (a quadratic step may then have more
 // rows than max_block), the largest quadratic step that does not go to those kernels.  (Four rows or five of max_block: 20 or 30.)
 __host__ __device__ inline int decode_rows(int max_block, bool large_m) {

@@ -128,10 +128,19 @@ static void every_device_error_has_its_text() {
   }
 }
 
+// The phase trace: no forward of two token tiles of the streaming kernel.
+static void trace_leaves_out_two_token_tiles() {
+  for (int rows = 1; rows <= 1056; ++rows) {
+    CHECK(trace_takes(rows, true) == (rows <= 16 || rows > 32), "%d rows", rows);
+    CHECK(trace_takes(rows, false), "%d rows, register ring", rows);
+  }
+}
+
 int main(int argc, char** argv) {
   struct { const char* name; void (*run)(); } checks[] = {{"decode_rows", decode_rows_hold_every_forward}, {"barrier_words", barrier_words_wait_at_every_epoch},
                                                                   {"down_plan", down_projection_takes_measured_tiles}, {"norm", norm_takes_the_faster_kernel},
-                                                                  {"lm_product", lm_head_product_fits_its_descriptor}, {"device_errors", every_device_error_has_its_text}};
+                                                                  {"lm_product", lm_head_product_fits_its_descriptor}, {"device_errors", every_device_error_has_its_text},
+                                                                  {"trace", trace_leaves_out_two_token_tiles}};
   for (auto& c : checks)
     if (argc == 2 && std::strcmp(argv[1], c.name) == 0) {
       c.run();

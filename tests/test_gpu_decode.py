@@ -1117,6 +1117,32 @@ def test_a_context_whose_kernels_gave_up_reports_it_and_never_hangs():
         ctx.close()
 
 
+def test_phase_trace_of_one_token_tile_and_its_refusal_of_two():
+    """With the trace on, forwards of up to 16 rows leave a stamp at every phase boundary of every workgroup; those of 17 to 32 rows are
+    refused with the context as it was, and run once the trace is off."""
+    shape = inputs.TINY
+    w = inputs.make_weights(shape, 0, "bf16", threads=1)
+    ctx = binding.Context(shape, max_seq=300, max_block=32)
+    ctx.load_model(w, as_bf16_bits=True)
+    ctx.bd_prefill(None, torch.arange(40, dtype=torch.int32, device="cuda"))
+    ctx.bd_k_trace(True)
+    ctx.bd_verify_block(torch.zeros(16, dtype=torch.int32, device="cuda"), False)
+    ctx.bd_status()
+    t = ctx.bd_k_trace_read().astype(np.int64)
+    steps = np.diff(t[:, :10 * shape.n_layers + 1], axis=1)
+    assert (t[:, :10 * shape.n_layers + 1] > 0).all() and (steps >= 0).all()
+    for B in (17, 32):
+        tok = torch.zeros(B, dtype=torch.int32, device="cuda")
+        with pytest.raises(binding.BdError) as e:
+            ctx.bd_commit_block(tok)
+        assert e.value.code == binding.BD_E_STATE and ctx.bd_cache_len() == 40
+    ctx.bd_k_trace(False)
+    ctx.bd_commit_block(torch.zeros(32, dtype=torch.int32, device="cuda"))
+    ctx.bd_status()
+    assert ctx.bd_cache_len() == 72
+    ctx.close()
+
+
 # ---- error paths that need a live context -------------------------------------------------------------------
 
 def test_call_order_and_capacity_errors():

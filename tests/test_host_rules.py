@@ -2,6 +2,7 @@
 includes those headers; it is compiled for the host only and needs no GPU."""
 import os
 import subprocess
+import sys
 
 import pytest
 
@@ -51,3 +52,14 @@ def test_lm_head_product_only_where_its_offsets_reach(program):
 
 def test_every_reason_to_give_up_has_its_own_text(program):
     _run(program, "device_errors")
+
+
+def test_phase_trace_leaves_out_two_token_tiles(program):
+    _run(program, "trace")
+
+
+def test_timeline_of_17_to_32_rows_is_refused_before_anything_runs():
+    for block in ("17", "32"):
+        r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--timeline", "--block", block], stdout=subprocess.PIPE,
+                           stderr=subprocess.STDOUT, text=True, timeout=120)
+        assert r.returncode == 2 and "at most 16" in r.stdout, r.stdout[-2000:]
