@@ -68,20 +68,20 @@ def main():
     ap.add_argument("--layers", type=int, default=36, help="debug only: fewer layers (result is then not the metric)")
     ap.add_argument("--prefix", type=int, default=None, help="committed prefix length (default 1024; 2048 with --weights fp8)")
     ap.add_argument("--weights", choices=["bf16", "fp8"], default="bf16",
-                    help="fp8 = configs[4]: e4m3 decoder linears with per-output-channel scales (seed 2), prefix 2048; "
+                    help="fp8: e4m3 decoder linears with per-output-channel scales (seed 2), prefix 2048; "
                          "not the headline metric")
     ap.add_argument("--block", type=int, default=32)
     ap.add_argument("--fixed-k", type=int, default=4)
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-kernel-pass", action="store_true")
     ap.add_argument("--verify", action="store_true",
-                    help="also time the speculative verify pass (configs[3]): B drafted ids, one causal forward + accept")
+                    help="also time the speculative verify pass: B drafted ids, one causal forward + accept")
     ap.add_argument("--speculative", type=int, default=0, metavar="N",
                     help="also time N iterations of the linear self-speculative loop (Alg. 1: draft + verify + accept "
                          "per call); with random weights nearly every draft is rejected, so this is ~2 forwards per token")
     ap.add_argument("--quadratic", type=int, default=0, metavar="B",
                     help="also time 8 iterations of the quadratic speculative loop (Alg. 2) with block size B "
-                         "(B*(B+1) <= 64 rows, one forward per iteration)")
+                         "(B up to 32: B*(B+1) rows, one forward per iteration)")
     ap.add_argument("--timeline", action="store_true",
                     help="instead of the benchmark: print the per-phase time line of one denoising forward (in-kernel "
                          "timestamps) at this prefix, as text; with --block up to 16 (the trace refuses 17 to 32 rows)")

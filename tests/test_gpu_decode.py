@@ -33,7 +33,7 @@ def _say(msg):
         pass
 
 
-# ---- configs[0]: the tiny plumbing model ---------------------------------------------------------------
+# ---- the tiny plumbing model ---------------------------------------------------------------
 
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
 def test_tiny_config_block_decode(storage):
@@ -124,7 +124,7 @@ def test_fixed_schedule(B, K):
     p.close()
 
 
-# ---- verify / accept / crop (configs[3] on the tiny model) --------------------------------------------
+# ---- verify / accept / crop on the tiny model --------------------------------------------
 
 @pytest.mark.parametrize("B", [4, 8, 16, 32, 64])
 def test_verify_accept_and_crop(B):
@@ -675,7 +675,7 @@ def test_long_prefix_3b_shaped_two_layers():
     p.close()
 
 
-# ---- configs[3] at 3B width: verification of drafts of every block size on a 2048-token prefix -----------------
+# ---- 3B width: verification of drafts of every block size on a 2048-token prefix -----------------
 
 def test_verify_block_sizes_3b_shaped_prefix_2048():
     """bd_verify_block on a 2048-token prefix (1536 embeddings + 512 ids), 3B-shaped x2 layers, drafts of 4 .. 64
@@ -870,7 +870,7 @@ def test_page_order_is_fixed_while_pages_are_in_use():
     ctx.close()
 
 
-# ---- configs[4]: e4m3 decoder weights with per-output-channel scales ---------------------------------------
+# ---- e4m3 decoder weights with per-output-channel scales ---------------------------------------
 
 def test_fp8_tiny_block_decode():
     _say("tiny config, e4m3 decoder linears (seed 2), jittered norm gains")
@@ -1018,7 +1018,7 @@ def test_fp8_context_rejects_wide_blocks_and_bf16_linears():
     ctx.close()
 
 
-# ---- configs[1] at full size ----------------------------------------------------------------------------
+# ---- full size: bf16, prefix 1024 ----------------------------------------------------------------------------
 
 @pytest.mark.slow
 def test_headline_config_first_block_full_depth():
@@ -1056,7 +1056,7 @@ def test_headline_config_first_block_full_depth():
 
 @pytest.mark.slow
 def test_fp8_config_first_block_full_depth():
-    """configs[4] at full depth: e4m3 decoder linears, 36 layers, the first block of 32 tokens (8 denoising forwards +
+    """Full depth: e4m3 decoder linears, 36 layers, the first block of 32 tokens (8 denoising forwards +
     commit) against the fp32 oracle on the same codes and scales, to the e4m3 bars.  The prefix is 1024 tokens here (the
     oracle's prompt pass over 2048 takes minutes; the 2048-token prefix is held at reduced depth above)."""
     shape = inputs.QWEN3B
@@ -1238,14 +1238,18 @@ def test_prefill_with_the_k_split_down_projection(n_embed, n_ids):
     p.close()
 
 
-def _kernels_of(call):
-    """Names of the device kernels that `call` launches."""
+def _launches_of(call):
+    """Names of the device kernels that `call` launches, one per launch."""
     from torch.profiler import ProfilerActivity, profile
     torch.cuda.synchronize()
     with profile(activities=[ProfilerActivity.CUDA]) as prof:
         call()
         torch.cuda.synchronize()
-    return {e.name for e in prof.events()}
+    return [e.name for e in prof.events()]
+
+
+def _kernels_of(call):
+    return set(_launches_of(call))
 
 
 def _instances(names, kernel):
@@ -1473,8 +1477,13 @@ def test_prompts_of_up_to_128_rows_in_one_chunk(rows, block, dtype):
                               weight_dtype=binding.BD_FP8_E4M3 if dtype == "fp8" else binding.BD_BF16)
         ctx.load_model(w, as_bf16_bits=True) if dtype == "bf16" else ctx.load_model(w)
         ctx.bd_debug_logits(True)
-        ctx.bd_prefill(torch.from_numpy(emb).cuda(), torch.from_numpy(ids).cuda())
+        e, i = torch.from_numpy(emb).cuda(), torch.from_numpy(ids).cuda()
+        names = _launches_of(lambda: ctx.bd_prefill(e, i))
         assert ctx.bd_cache_len() == rows
+        if flags == 0:                                      # one chunk: every phase once per layer, no decode forward
+            assert [sum(bool(_instances([x], "pf_gemm_pipe_kernel")) for x in names), sum("stream_fwd_kernel" in x for x in names)] == [4 * shape.n_layers, 0]
+        else:
+            assert not any("pf_gemm" in x for x in names) and any("stream_fwd_kernel" in x or "mega_kernel" in x for x in names)
         k, v = ctx.bd_read_kv(1, 0, rows)
         n = last if flags == 0 else (rows - 1) % min(block, 32 if dtype == "fp8" else 64) + 1
         res.append((k.clone(), v.clone(), ctx.bd_read_logits(n).clone()[-min(last, n):], n))
@@ -1490,6 +1499,78 @@ def test_prompts_of_up_to_128_rows_in_one_chunk(rows, block, dtype):
     for a, b in ((res[0][0], res[1][0]), (res[0][1], res[1][1]), (res[0][2][-m:], res[1][2][-m:])):
         assert float((a - b).abs().max()) <= 2e-2 * float(b.abs().max())
         assert float((a - b).norm()) <= 1.2e-2 * float(b.norm())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("rows", [1025, 3000, 4100])
+def test_long_chunks_on_scattered_pages(rows, dtype):
+    """Chunks of more than 1024 rows, bf16 and e4m3, on cache pages handed out in a shuffled order: one chunk, keys, values and carry equal to
+    those of a context whose pages are in order (the same arithmetic), and keys and values against the decode kernels on pages in
+    order.  Bars as above."""
+    shape = _wide(2, vocab=8192)
+    w = inputs.make_weights(shape, 4 if dtype == "bf16" else 2, dtype, threads=8)
+    emb, ids = inputs.make_prompt(shape, rows - 500, 500, seed=20)
+    e, i = torch.from_numpy(emb).cuda(), torch.from_numpy(ids).cuda()
+    res = []
+    for flags, shuffled in ((0, True), (0, False), (binding.BD_FLAG_PREFILL_DECODE, False)):
+        ctx = binding.Context(shape, max_seq=4288, max_block=32, flags=flags, weight_dtype=binding.BD_FP8_E4M3 if dtype == "fp8" else binding.BD_BF16)
+        ctx.load_model(w, as_bf16_bits=True) if dtype == "bf16" else ctx.load_model(w)
+        if shuffled:
+            ctx.bd_kv_page_order(np.random.default_rng(5).permutation(4288 // 32))
+        names = _launches_of(lambda: ctx.bd_prefill(e, i))
+        if flags == 0:
+            assert sum(bool(_instances([x], "pf_gemm_pipe_kernel")) for x in names) == 4 * shape.n_layers
+        assert (list(ctx.bd_kv_pages()) != list(range(len(ctx.bd_kv_pages())))) == shuffled
+        k, v = ctx.bd_read_kv(1, 0, rows)
+        res.append((k.clone(), v.clone(), torch.tensor(ctx.bd_read_carry())))
+        ctx.bd_status()
+        ctx.close()
+    assert all(torch.equal(a, b) for a, b in zip(res[0], res[1]))
+    for a, b in zip(res[0][:2], res[2][:2]):
+        assert float((a - b).abs().max()) <= 2e-2 * float(b.abs().max())
+        assert float((a - b).norm()) <= 1.2e-2 * float(b.norm())
+
+
+def test_forwards_of_one_and_two_token_tiles_with_different_barriers():
+    """Four query heads: a forward of one token tile has four column tiles, too few for the XCDs (keys split over the chip, barrier through two
+    levels of counters); with two token tiles it stays inside them (barrier through the XCDs' counters).  One context runs both in turn,
+    steps that are skipped on the device among them, and every result equals that of a context that runs only this call."""
+    shape = inputs.TINY
+    w = inputs.make_weights(shape, 0, "bf16", lm_head_scale=40.0, threads=1)
+
+    def context():
+        ctx = binding.Context(shape, max_seq=512, max_block=32)
+        ctx.load_model(w, as_bf16_bits=True)
+        ctx.bd_debug_logits(True)
+        ctx.bd_prefill(None, torch.arange(100, dtype=torch.int32, device="cuda"))
+        return ctx
+
+    def run(ctx, B, whole):
+        if whole:                                           # B - 1 steps are launched, the last ones skip
+            out, steps = torch.zeros(B, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+            ctx.bd_decode_block(B, 0.3, 4, out, steps)
+            got = [out.cpu(), steps.cpu(), ctx.bd_read_logits(B).cpu()]
+            ctx.bd_crop(100)
+            return got
+        ctx.bd_verify_block(torch.arange(7, 7 + B, dtype=torch.int32, device="cuda"), False)
+        return [ctx.bd_read_logits(B).clone().cpu()]
+
+    both = context()
+    forms = set()
+    for B, whole in [(16, False), (32, False)] * 3 + [(1, False), (17, False), (3, False), (32, False)]:
+        names = _kernels_of(lambda: both.bd_verify_block(torch.arange(7, 7 + B, dtype=torch.int32, device="cuda"), False))
+        forms |= {(a[0], a[-1]) for a in _instances(names, "stream_fwd_kernel")}
+        alone = context()
+        assert all(torch.equal(x, y) for x, y in zip(run(both, B, whole), run(alone, B, whole)))
+        alone.close()
+    assert forms == {("1", "false"), ("2", "true")}, forms
+    for B in (8, 32, 8, 20):                                # (bd_decode_block needs the carry the prompt left)
+        both.bd_prefill(None, torch.arange(100, dtype=torch.int32, device="cuda"))
+        alone = context()
+        assert all(torch.equal(x, y) for x, y in zip(run(both, B, True), run(alone, B, True)))
+        alone.close()
+    both.bd_status()
+    both.close()
 
 
 @pytest.mark.parametrize("rows,want", [
