@@ -346,7 +346,8 @@ int lm_head_of_rows(bd_ctx* c, const float* xrows, int M, int mode, bool skippab
 
 // A forward of more than 32 rows: the decode kernels stream the weights against at most two token tiles, so these go
 // through the large-M kernels (whole-chip tiled GEMMs per phase, attention with the forward's own visibility among the
-// new rows), then the decode path's LM head over all rows.
+// new rows, the LM head as one more product over all rows; contexts that do not hold its weights tile-major, lm_as_product, run the decode
+// path's LM head, as many rows at a time as its buffers hold).
 int forward_large(bd_ctx* c, int M, int mode, bool want_lm, const float* embeds, int n_embed, const int32_t* ids, int off,
                   int32_t* seed_tokens, uint8_t* seed_mask, const uint8_t* mask, bool skippable, int quad_B) {
   PfChunk p = chunk_args(c);
@@ -483,10 +484,6 @@ FinishArgs finish_args(bd_ctx* c, int B) {
 
 }  // namespace
 
-namespace {
-
-}  // namespace
-
 extern "C" {
 
 const char* bd_strerror(int code) {
@@ -515,7 +512,6 @@ int bd_create(const bd_config* cfg, void* hip_stream, bd_ctx** out) {
   if (k.mask_token_id >= k.vocab) return BD_E_ARG;
   if (!(k.rope_theta > 0.f) || !(k.rms_eps > 0.f)) return BD_E_ARG;
   {
-    // the attention phase works on groups of 2 or 4 column tiles (16 query columns each)
     // the attention phase works on pairs of column tiles (16 query columns each)
     const int G = k.n_q_heads / k.n_kv_heads;
     if (G % 2 != 0) return BD_E_ARG;
@@ -827,7 +823,7 @@ int bd_prefill(bd_ctx* c, const float* dev_embeds, int n_embed, const int32_t* d
   BD_TRY(check_launch());
   c->n = 0; c->prefilled = false; c->carry_valid = false;
   release_pages(c, 0);
-  const int step = c->cfg.max_block;                   // (at most 32 with e4m3 weights, checked at creation)
+  const int step = c->cfg.max_block;                   // (more than 32 with e4m3 weights only where the large-M kernels are, checked at creation)
   int off0 = 0;
   if (c->pf_on && total > kPfTokens) {
     // The whole prompt in large chunks; the last row's residual stream is then handed to the final norm + LM head.

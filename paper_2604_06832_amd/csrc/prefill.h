@@ -4,8 +4,9 @@
 // through them re-reads the model n/64 times.  For the bulk of the prompt this file provides the compute-bound
 // form: chunks of up to 8192 rows, each layer as a sequence of tiled MFMA GEMMs with the same fused epilogues as the
 // decode path (RMS factor, rotary + Q store + K/V store; residual add; SwiGLU) and a causal attention kernel that
-// walks the packed cache with the decode path's per-block routine.  Only the LM head, needed for the last row alone,
-// is the decode path's.
+// walks the packed cache with the decode path's per-block routine.  Blocks and quadratic steps of more than 32 rows go the same
+// way, with an LM head over all of their rows (pf_gemm_pipe_kernel_lm); a prompt needs it for its last rows alone, which
+// the decode path's LM head takes.
 //
 // Operand layout: both GEMM operands are kept as 1-KiB MFMA fragments (16 rows x 32 k, lane (row i, k-quarter kq)
 // holds 8 consecutive k at lane*16 bytes).  Weights: fragment (row tile T, k-step ks) of a layer's phase at

@@ -10,7 +10,8 @@ constexpr int kPfSplit = 4;           // K splits of the down projection over wo
 // Rows of a prompt chunk.  The longer the chunk, the larger the tiles that still fill the chip in whole rounds, and a round's
 // fixed part (launch, first loads, epilogue) is paid less often: 3B shape, 8192 rows in chunks of 1024 71.5 ms, of 2048 62, of 4096
 // 59.2, in one 55.5; 3000 rows in chunks of 1024 23.8 ms, in one 20.5.  The working buffers take 75 KB a row, twice what a position of the cache
-// does, so a context that reserves fewer than 4096 positions keeps those of 1024 rows (77 MB).
+// does.  Where the line lies is a choice of memory, not a crossing of times: a context that reserves 4096 positions or more takes buffers for
+// all of them (up to 8192: 307 to 614 MB), a smaller one 77 MB and chunks of 1024 rows, which cost a prompt of 3000 rows 16 %.
 constexpr int kPfShortRows = 1024, kPfLongContext = 4096;
 constexpr int kPfChunkRows = 8192;
 

@@ -130,9 +130,12 @@ constexpr int kStashGroup = 4;                   // fragments moved or requested
 // 5200 ticks, 96 of them in gate/up, and ring and stash hold 72.  So the stash is refilled while attention and O run, gate/up and
 // down request at a rate HBM can follow, and the requests nearly stop behind the last product of down.  With one rate throughout
 // (30 ticks, 10 while at most 24 fragments were buffered) the fast one fell on the down projection's cross-workgroup sum, a chain of
-// far round trips, although nothing is urgent between it and the next gate/up: 3B shape, 1024 keys, the down phase took 15.3 us
-// a layer at 32 rows, now 11.9.  The values are the best of a random search over all of them, whole forwards timed, and flat
-// around the optimum.  One forward before and after: 4 rows 1959 -> 1875 us, 32 rows 2151 -> 2003; e4m3 (half the fragments), 333
+// far round trips, although nothing is urgent between it and the next gate/up (3B shape, 1024 keys: first start to last arrival of the down
+// phase 15.2 us a layer at 32 rows; with the rates, 16 rows, 10.1).  The values are the best of a random search over all of them,
+// whole forwards timed on the 3B shape, and flat around the optimum (what the search found next to it is within 1 %:
+// profiles/streaming_forward_pace_search.txt).  They come from that shape's shares of a layer, not from a rule; the other shapes with this
+// attention (hidden 512 to 2048, FFN 1376 to 11008, four layers) are 1 to 8 % faster with them and the barrier below than with one rate.
+// One forward before and after: 4 rows 1959 -> 1875 us, 32 rows 2151 -> 2003; e4m3 (half the fragments), 333
 // keys, 32 rows 2031 -> 1968.  With e4m3 and one token tile there is so little to request that the one rate stays (1570 us, with a
 // rate per phase 1584: the kernel's registers spill over it).
 // The rates are those of the attention inside the XCDs.  Where it is split over the chip (LOCAL false: head counts that do not deal out over
