@@ -838,7 +838,7 @@ template <int MT> constexpr int mega_lds_bytes() {
 template <int MT, int D, int JT, bool QUAD = false>
 __global__ __launch_bounds__(kWGThreads, 1) void mega_kernel(MegaArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  __shared__ int s_flags[16];
+  __shared__ int s_flags[kFlagWords];
   const MegaPlan& P = a.P;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;   // wave id in an SGPR: all branches on it are scalar
   if (threadIdx.x == 0) {

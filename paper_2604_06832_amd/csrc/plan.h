@@ -11,6 +11,11 @@ namespace bd {
 constexpr int kMaxKW = 16;   // k-steps (of 32) one wavefront covers in a GEMM phase
 constexpr int kT = 2;        // 16-row tiles a wavefront accumulates side by side (one chunk of its stream)
 constexpr int kBarGroup = 16;
+// Row tiles of the residual stream (its K ranges are not split over workgroups: hidden is at most what four wavefronts hold), hence the most a
+// workgroup can have in the down phase, where the rows are dealt to nwg / ksplit groups (hidden 2048: 4 tiles up to FFN 16384, 16 from 32784 on).
+constexpr int kMaxRowTiles = kWavesPerWG * kMaxKW * 32 / 16;
+constexpr int kFlagWords = 8 + kMaxRowTiles;      // LDS flags of a workgroup: eight, and one per row tile in the down phase
+static_assert(kMaxRowTiles <= kWGThreads, "one thread per row tile");
 constexpr int kSpinLimit = 1 << 19;
 constexpr int kQuadMaxB = 32;      // largest block of a quadratic step: B (B + 1) = 1056 rows
 constexpr int kStreamRows = 32;    // rows of a forward the decode kernels stream the weights against (two token tiles)

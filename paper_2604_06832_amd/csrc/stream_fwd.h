@@ -649,14 +649,15 @@ __device__ inline void stream_gemm_phase(const MegaArgs& a, FwdCtx& fc, Ring& rg
     const int ver = 2 * fc.layer + 2;
     const int n_idx = n_tiles * MT;                           // (tile, row tile of tokens) pairs of this row range
     cbar(sy, lane, a.st);                                    // every consumer's partials are out
-    if (wave == 0 && lane < n_tiles) {
+    const int t = wave * 64 + lane;
+    if (t < n_tiles) {
       int last = 1;
       if (ksplit > 1) {
-        const unsigned old = __hip_atomic_fetch_add(a.cntD + (size_t)fc.layer * tiles + gt0 + lane, 1u, __ATOMIC_RELAXED,
+        const unsigned old = __hip_atomic_fetch_add(a.cntD + (size_t)fc.layer * tiles + gt0 + t, 1u, __ATOMIC_RELAXED,
                                                     __HIP_MEMORY_SCOPE_AGENT);
         last = old == (unsigned)ksplit - 1u;
       }
-      fc.s_flags[8 + lane] = last;
+      fc.s_flags[8 + t] = last;
     }
     cbar(sy, lane, a.st);
     const float* src = a.wsD + (size_t)fc.layer * a.wsD_layer_floats;
@@ -1304,7 +1305,7 @@ __global__ __launch_bounds__(kFwdThreads, 1) void stream_fwd_kernel(MegaArgs a) 
   static_assert(kWavesPerWG * (D / 16) * 1024 + (8 * 16 + 64 * 16 + 16) * 4 <= kShareBytes, "attention merge buffers exceed the shared region");
   extern __shared__ __attribute__((aligned(16))) char lds[];
   __shared__ unsigned s_sync[SY_WORDS];
-  __shared__ int s_flags[16];
+  __shared__ int s_flags[kFlagWords];
   __shared__ float s_part[kWavesPerWG * 64];
   __shared__ int4 s_plan[PH_LM * kWavesPerWG];
   const MegaPlan& P = a.P;

@@ -136,11 +136,30 @@ static void trace_leaves_out_two_token_tiles() {
   }
 }
 
+// Down phase: a workgroup's row tiles have a flag each, whatever hidden size and FFN the context has.
+static void down_phase_flags_hold_every_row_group() {
+  int most = 0;
+  for (int hidden = 32; hidden <= kMaxKW * kWavesPerWG * 32; hidden += 32)
+    for (int ksplit = 1; ksplit <= 256; ksplit *= 2) {      // (what FFNs of up to 524288 need)
+      MegaPlan P{};
+      P.nwg = 256;
+      P.ph[PH_DOWN].N = hidden;
+      P.ph[PH_DOWN].ksplit = ksplit;
+      for (int g = 0; g < P.nwg / ksplit; ++g) {
+        const int tiles = phase_tile0(P, PH_DOWN, g + 1) - phase_tile0(P, PH_DOWN, g);
+        CHECK(8 + tiles <= kFlagWords && tiles <= kWGThreads, "hidden %d, %d K splits: %d row tiles", hidden, ksplit, tiles);
+        most = tiles > most ? tiles : most;
+      }
+    }
+  CHECK(most == kMaxRowTiles, "%d", most);
+}
+
 int main(int argc, char** argv) {
   struct { const char* name; void (*run)(); } checks[] = {{"decode_rows", decode_rows_hold_every_forward}, {"barrier_words", barrier_words_wait_at_every_epoch},
                                                                   {"down_plan", down_projection_takes_measured_tiles}, {"norm", norm_takes_the_faster_kernel},
                                                                   {"lm_product", lm_head_product_fits_its_descriptor}, {"device_errors", every_device_error_has_its_text},
-                                                                  {"trace", trace_leaves_out_two_token_tiles}};
+                                                                  {"trace", trace_leaves_out_two_token_tiles},
+                                                                  {"down_flags", down_phase_flags_hold_every_row_group}};
   for (auto& c : checks)
     if (argc == 2 && std::strcmp(argv[1], c.name) == 0) {
       c.run();

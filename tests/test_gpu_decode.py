@@ -1501,6 +1501,31 @@ def test_prompts_of_up_to_128_rows_in_one_chunk(rows, block, dtype):
         assert float((a - b).norm()) <= 1.2e-2 * float(b.norm())
 
 
+def test_decode_kernels_with_16_row_tiles_a_workgroup_in_the_down_phase():
+    """FFN 33792: the decode kernels' down phase splits K over 32 workgroups, and each of the eight row groups of hidden 2048 has 16 tiles.
+    Keys, values and the last chunk's logits of the streaming and the register-ring kernel against the large-M kernels.  Bars as above."""
+    _say("FFN 33792, 16 row tiles a workgroup")
+    shape = inputs.ModelShape(n_layers=2, hidden=2048, n_q_heads=16, n_kv_heads=2, head_dim=128, ffn=33792, vocab=1024)
+    w = inputs.make_weights(shape, 4, "bf16", threads=8)
+    ids = torch.arange(100, 240, dtype=torch.int32, device="cuda")
+    res = []
+    for flags in (0, binding.BD_FLAG_PREFILL_DECODE, binding.BD_FLAG_PREFILL_DECODE | binding.BD_FLAG_REGISTER_RING):
+        ctx = binding.Context(shape, max_seq=176, max_block=32, flags=flags)
+        ctx.load_model(w, as_bf16_bits=True)
+        ctx.bd_debug_logits(True)
+        ctx.bd_prefill(None, ids)
+        k, v = ctx.bd_read_kv(1, 0, 140)
+        tok = torch.arange(7, 27, dtype=torch.int32, device="cuda")
+        ctx.bd_verify_block(tok, False)
+        res.append((k.clone(), v.clone(), ctx.bd_read_logits(20).clone()))
+        ctx.bd_status()
+        ctx.close()
+    for other in res[1:]:
+        for a, b in zip(res[0], other):
+            assert float((a - b).abs().max()) <= 2e-2 * float(b.abs().max())
+            assert float((a - b).norm()) <= 1.2e-2 * float(b.norm())
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 @pytest.mark.parametrize("rows", [1025, 3000, 4100])
 def test_long_chunks_on_scattered_pages(rows, dtype):

@@ -58,6 +58,10 @@ def test_phase_trace_leaves_out_two_token_tiles(program):
     _run(program, "trace")
 
 
+def test_down_phase_has_a_flag_for_every_row_tile(program):
+    _run(program, "down_flags")
+
+
 def test_timeline_of_17_to_32_rows_is_refused_before_anything_runs():
     for block in ("17", "32"):
         r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--timeline", "--block", block], stdout=subprocess.PIPE,
